@@ -217,11 +217,18 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const bf16*
 // consecutive output features of one token (8 with the row order described at big_row_feature:
 // 16-byte stores), and gate/up of the same feature in the same lane for the SwiGLU epilogue.
 //
+// With real operand values the chip holds the matrix pipes back for power, not for issue: a loop of nothing but
+// MFMAs on random data sustains 1.79 PFLOP/s with the 32x32x16 form and 2.05 with the 16x16x32 form (2.44 and
+// 2.42 on zeros), because the 16x16x32 form touches its accumulators half as often per product.  So the tile is
+// built of 16x16x32 products, 8 x 8 blocks of four accumulators per wave.  Against the same kernel built of 32x32x16
+// products (same tile, ring and loads), microseconds: 8192 rows, 8192 -> gate/up 28672 5326 -> 4943 (1.45 -> 1.56
+// PFLOP/s), down 2735 -> 2518, qkv 10240 963 -> 888; 4973 rows, 4096 -> gate/up 11008 663 -> 616, qkv 12288 383 -> 349.
+//
 // LDS is a ring of five 32 KiB slots, each holding one operand's 256 rows of one k-tile: the tile
 // being multiplied, the next one, and the activation half of the one after.  What decides the
 // schedule is the cost of ISSUING a load: a 1 KiB load holds its wave's instruction stream for
 // about 64 cycles when the four waves issue together (the address unit is shared), and a wave that
-// cannot issue cannot feed the matrix pipe either.  So loads go out one every four MFMAs, spread
+// cannot issue cannot feed the matrix pipe either.  So loads go out one every few MFMAs, spread
 // over the whole tile, into the two slots the previous tile released, and the wait before a
 // tile's barrier leaves the newest 32 KiB in flight.
 // ---------------------------------------------------------------------------------------------
@@ -233,28 +240,32 @@ __device__ __forceinline__ int swz(int row) { return (row & 7) ^ ((row >> 3) & 1
 typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 
-// Waves along the output-feature dimension: 2, i.e. four waves of 128x128 each, one per SIMD.  (Four - eight
-// waves of 128x64, two per SIMD - was measured slower: its LDS operand reads fill the LDS port.)
-constexpr int kBigWN = 2;
+// Which feature sits where.  A 16x16x32 MFMA leaves lane group h (lanes 16h .. 16h+15) of the output with rows
+// 4h .. 4h+3 of the row operand.  The weight rows of a 32-feature block pair are therefore laid into LDS in a permuted
+// order - row 4h + e of block b (b = 0, 1) holds feature 8h + 4b + e - so that a lane's four registers of block 0 and
+// four of block 1 are the 8 consecutive features 8h .. 8h+7 of one token: 16-byte output stores, 64 contiguous bytes
+// per token and instruction.  The permutation costs nothing: it only changes which global row a loader lane fetches.
+__device__ __forceinline__ int big_row_feature(int rho) {            // row inside a block pair -> feature inside it
+    const int b = rho >> 4, h = (rho >> 2) & 3, e = rho & 3;
+    return 8 * h + 4 * b + e;
+}
+
+// acc += w * x, one 16x16x32 product, accumulating in place.  Written out because the compiler, given 64 accumulators
+// that fill all 256 accumulation registers, takes the form with a separate destination and rotates the accumulators
+// through copies (196 register moves and 97 waits per k-tile).  The compiler still counts the LDS reads behind the
+// operands; what it no longer sees is the time until a result may be read by other instructions: mfma_settle().
+__device__ __forceinline__ void mfma16(f32x4& acc, const bf16x8& w, const bf16x8& x) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(x));
+}
+// Between the last mfma16 and the first other use of its results (a 4-pass product needs at most 11 wait states).
+__device__ __forceinline__ void mfma_settle() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 15");
+    __builtin_amdgcn_sched_barrier(0);
+}
 
 // logical tile id -> tile coordinates: groups of 4 tile rows, walked column by column, so that the
 // tiles running together on an XCD share operand rows in its L2
-// Which feature sits where.  A 32x32x16 MFMA leaves lane half h of the output with rows 8g + 4h + 0..3 of
-// the row operand (register group g = registers 4g..4g+3).  The weight rows of a 32-feature block are
-// therefore laid into LDS in a permuted order - operand row 8g + 4h + e holds feature
-// 16*(g/2) + 8h + 4*(g%2) + e - so that a lane's registers 8p..8p+7 are the 8 consecutive features
-// 16p + 8h + 0..7 of one token: 16-byte output stores, 32 contiguous bytes per token and instruction.  (In
-// operand-row order a lane would own 4 consecutive features; the L2 then takes the output as twice as many
-// partial-line writes, which is what bounds the epilogue.)  The permutation costs nothing: it only changes
-// which global row a loader lane fetches.
-__device__ __forceinline__ int big_row_feature(int rho) {            // operand row inside a block -> feature inside it
-    const int g = rho >> 3, h = (rho >> 2) & 1, e = rho & 3;
-    return 16 * (g >> 1) + 8 * h + 4 * (g & 1) + e;
-}
-__device__ __forceinline__ int big_group_feature(int g, int h) {     // first feature of register group g, lane half h
-    return 16 * (g >> 1) + 8 * h + 4 * (g & 1);
-}
-
 struct BigTile { int m0, n0; };
 template <int MODE>
 __device__ __forceinline__ BigTile big_tile_of(int pid, int tiles_m, int tiles_n) {
@@ -269,82 +280,29 @@ __device__ __forceinline__ BigTile big_tile_of(int pid, int tiles_m, int tiles_n
     return BigTile{tile_m * 256, tile_n * OUT_BN};
 }
 
-// Output of one 32-token block of a wave: lane holds token m and, of each 32-feature block j,
-// features fbase[j] + 8*g + 4*lk + 0..3 (accumulator registers 4g..4g+3).
-// `get(j, x)` returns accumulator register x of block j (a callable, so the caller's registers are read in place).
-template <int MODE, int NJ, class Get>
-__device__ __forceinline__ void big_store_block(Get get, int m, int n0, const int (&fbase)[NJ], int lk,
-                                                const bf16* R, bf16* C, int M, int N) {
-    if (m >= M) return;
-    bf16* crow = C + (size_t)m * N;
-    if ((N & 7) == 0 && MODE != 1) {                 // rows 16-byte aligned: 8 features (registers 8p..8p+7) per store
-        constexpr int NJE = (MODE == 2) ? NJ / 2 : NJ;
+// First output feature, inside the tile, of a wave's feature pair p (32 features; SwiGLU: of both factors).
+template <int MODE>
+__device__ __forceinline__ int big_pair_feature(int wn, int p) { return wn * (MODE == 2 ? 64 : 128) + p * 32; }
+
+// 8 consecutive output features n .. n+7 of one token: one 16-byte access when rows are multiples of 8 features,
+// else (N % 4 == 0) two of 8 bytes, each behind its own bound.
+__device__ __forceinline__ void big_store8(bf16* crow, int n, int N, const float (&o)[8]) {
+    bf16x8 w;
 #pragma unroll
-        for (int j = 0; j < NJE; ++j)
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                const int n = n0 + fbase[j] + 16 * p + 8 * lk;
-                if (n < N) {
-                    bf16x8 o;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const float v = get(j, 8 * p + e);
-                        if (MODE == 2) o[e] = (bf16)(silu_fast(v) * get(j + NJ / 2, 8 * p + e));
-                        else o[e] = (bf16)v;
-                    }
-                    *reinterpret_cast<bf16x8*>(crow + n) = o;
-                }
-            }
-        return;
-    }
-    if (MODE == 2) {
-#pragma unroll
-        for (int j = 0; j < NJ / 2; ++j)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int n = n0 + fbase[j] + big_group_feature(g, lk);
-                if (n < N) {
-                    bf16x4 o;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float gt = get(j, 4 * g + e), up = get(j + NJ / 2, 4 * g + e);
-                        o[e] = (bf16)(silu_fast(gt) * up);
-                    }
-                    *reinterpret_cast<bf16x4*>(crow + n) = o;
-                }
-            }
+    for (int e = 0; e < 8; ++e) w[e] = (bf16)o[e];
+    if ((N & 7) == 0) {
+        if (n < N) *reinterpret_cast<bf16x8*>(crow + n) = w;
     } else {
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int n = n0 + fbase[j] + big_group_feature(g, lk);
-                if (n < N) {
-                    bf16x4 o;
-                    if (MODE == 1) {
-                        const bf16x4 rv = *reinterpret_cast<const bf16x4*>(R + (size_t)m * N + n);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) o[e] = (bf16)(get(j, 4 * g + e) + (float)rv[e]);
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) o[e] = (bf16)get(j, 4 * g + e);
-                    }
-                    *reinterpret_cast<bf16x4*>(crow + n) = o;
-                }
-            }
+        if (n < N) *reinterpret_cast<bf16x4*>(crow + n) = __builtin_shufflevector(w, w, 0, 1, 2, 3);
+        if (n + 4 < N) *reinterpret_cast<bf16x4*>(crow + n + 4) = __builtin_shufflevector(w, w, 4, 5, 6, 7);
     }
 }
-
-template <int MODE, int NJ, int WN>
-__device__ __forceinline__ void big_feature_bases(int wn, int (&fbase)[NJ], int (&wrow)[NJ]) {
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-        int row;       // row of the weight tile (0..127 gate / plain, 128..255 up / plain)
-        if (MODE == 2) row = (j < NJ / 2) ? (wn * (NJ / 2) + j) * 32 : 128 + (wn * (NJ / 2) + (j - NJ / 2)) * 32;
-        else row = (wn * NJ + j) * 32;
-        fbase[j] = (MODE == 2 && j >= NJ / 2) ? row - 128 : row;     // output feature offset inside the tile
-        wrow[j] = row;
-    }
+// the same features of the residual; past the end a valid address is read and its value never used
+__device__ __forceinline__ bf16x8 big_load8(const bf16* rrow, int n, int N) {
+    if ((N & 7) == 0) return *reinterpret_cast<const bf16x8*>(rrow + (n > N - 8 ? N - 8 : n));
+    const bf16x4 lo = *reinterpret_cast<const bf16x4*>(rrow + (n > N - 4 ? N - 4 : n));
+    const bf16x4 hi = *reinterpret_cast<const bf16x4*>(rrow + (n + 4 > N - 4 ? N - 4 : n + 4));
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
 // Tile scheduling.  A launch runs one workgroup per CU at a time, so `tiles` whole tiles take
@@ -354,16 +312,15 @@ __device__ __forceinline__ void big_feature_bases(int wn, int (&fbase)[NJ], int 
 // which starts as the first drains), which write fp32 partial tiles to `ws`; a small third kernel
 // adds the partial tiles in range order and applies the epilogue.  The cut is a function of the
 // problem shape only.
-template <int MODE, int WN, bool PARTIAL>
-__global__ __launch_bounds__(128 * WN, 1) void gemm_big_kernel(const bf16* __restrict__ A, const bf16* __restrict__ W,
-                                                                const bf16* R, bf16* C, int M, int N, int K,
-                                                                int tiles_m, int tiles_n, int n_dp, int splits,
-                                                                float* __restrict__ ws) {
-    constexpr int NWAVES = 2 * WN;
-    constexpr int NJ = 8 / WN;                 // 32-wide feature blocks per wave (gate+up blocks in SwiGLU mode)
-    constexpr int NCH = 32 / NWAVES;           // 1 KiB chunks of each tile filled by one wave
-    constexpr int NMMA = 4 * NJ;               // MFMAs per k-step
-    constexpr int NFETCH = 4 + NJ;             // LDS operand reads per k-step
+template <int MODE, bool PARTIAL>
+__global__ __launch_bounds__(256, 1) void gemm_big_kernel(const bf16* __restrict__ A, const bf16* __restrict__ W,
+                                                           const bf16* R, bf16* C, int M, int N, int K,
+                                                           int tiles_m, int tiles_n, int n_dp, int splits,
+                                                           float* __restrict__ ws) {
+    constexpr int NCH = 8;                     // 1 KiB chunks of each tile filled by one wave
+    constexpr int NB = 8;                      // 16-wide blocks of a wave's 128 features / tokens
+    constexpr int NMMA = NB * NB;              // MFMAs per k-step of 32
+    constexpr int NFETCH = 2 * NB;             // LDS operand reads per k-step
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
 
     const int nk = K / kBK;
@@ -381,8 +338,8 @@ __global__ __launch_bounds__(128 * WN, 1) void gemm_big_kernel(const bf16* __res
     const int m0 = bt.m0, n0 = bt.n0;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WN, wn = wave % WN;
-    const int lrow = lane & 31, lk = lane >> 5;
+    const int wm = wave >> 1, wn = wave & 1;
+    const int lrow = lane & 15, lg = lane >> 4;
 
     // ---- loader: this wave fills chunks q = wave*NCH + j (rows 8q .. 8q+7) of both tiles.  Addresses
     // are a uniform base (advanced per K tile) plus a per-lane 32-bit byte offset.
@@ -431,68 +388,57 @@ __global__ __launch_bounds__(128 * WN, 1) void gemm_big_kernel(const bf16* __res
         for (int q = 0; q < NCH; ++q) issue_piece(kt, slot, weights, q);
     };
 
-    f32x16 acc[NJ][4];      // [feature block][token block]
+    f32x4 acc[NB][NB];      // [feature block][token block]
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
+    for (int j = 0; j < NB; ++j)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < NB; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[j][i][r] = 0.f;
+            for (int r = 0; r < 4; ++r) acc[j][i][r] = 0.f;
 
-    // ---- operand addresses inside a stage
-    int x_off[4], w_off[NJ], k_off[4], fbase[NJ];
-    const int sw = swz(lrow);
+    // ---- operand addresses inside a slot: per-lane part in one register per k-step and operand, the 16-row blocks
+    // being immediate offsets from it (block j of the weights: 16j rows on; SwiGLU: blocks 4..7 are the up factor,
+    // 128 rows further)
+    int xk[2], wk[2];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) x_off[i] = (wm * 128 + i * 32 + lrow) * 128;
-    {
-        int wrow[NJ];
-        big_feature_bases<MODE, NJ, WN>(wn, fbase, wrow);
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) w_off[j] = (wrow[j] + lrow) * 128;
+    for (int ks = 0; ks < 2; ++ks) {
+        const int piece = ((ks * 4 + lg) ^ swz(lrow)) * 16;
+        xk[ks] = (wm * 128 + lrow) * 128 + piece;
+        wk[ks] = (wn * (MODE == 2 ? 64 : 128) + lrow) * 128 + piece;
     }
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) k_off[ks] = ((ks * 2 + lk) ^ sw) * 16;
+    constexpr int kBlk = 16 * 128;
+    auto w_blk = [](int j) { return (MODE == 2 && j >= NB / 2) ? 128 * 128 + (j - NB / 2) * kBlk : j * kBlk; };
 
-    // ---- main loop.  Every k-step is NMMA MFMAs in a fixed order; between them, one by one, go the
-    // LDS reads that fetch the operands of the NEXT k-step (first half of the k-step) and, after every
-    // second MFMA of the other half, one global->LDS load (a load behind an MFMA that already has an LDS
-    // read behind it makes the next MFMA late: 1-2.5 % on the four projections).  The order is pinned with scheduling barriers so the matrix pipe never waits
-    // behind a burst of memory instructions.  The tile barrier sits before the last k-step, whose
-    // operands are already in registers; it is a bare s_barrier (the waits are written out here; a
-    // full __syncthreads would drain the loads that are meant to stay in flight).
+    // ---- main loop.  Every k-step is NMMA MFMAs in a fixed order; between them, one by one, go the LDS reads that
+    // fetch the operands of the NEXT k-step (behind every second MFMA of the first half) and the global->LDS loads
+    // (behind every eighth MFMA, one that has no LDS read behind it).  The order is pinned with scheduling barriers so
+    // the matrix pipe never waits behind a burst of memory instructions.  Other spacings (reads every third MFMA, loads
+    // in the second half only, the four waves' loads a few MFMAs apart) measure within 1 % of this one: the loop is
+    // bound by power, not by issue.  On random data, 8192x8192 into gate/up of 28672, a tile's k-step stream without its
+    // global->LDS loads runs 15 % faster, without its LDS reads 9 %, without both at the rate of bare MFMAs; with every
+    // load hitting the L2 6 %.  The tile barrier sits before the second k-step, whose operands are already in
+    // registers; it is a bare s_barrier (the waits are written out here; a full __syncthreads would drain the loads
+    // that are meant to stay in flight).
     //
-    // The two slots tile i - 1 released at its barrier are refilled as follows: last k-step of tile
-    // i - 1 and first of tile i: weights of tile i + 1 (needed first); k-steps 1 and 2 of tile i:
-    // activations of tile i + 2.  Before the barrier of tile i everything but those activations must
-    // have landed.
-    bf16x8 xf[2][4], wf[2][NJ];
-    // per-lane part of every operand address, one register per k-step and operand: a fetch then costs one vector
-    // add (slot base + this), the 32-row blocks being immediate offsets from it (worth another 0.6 %)
-    int xk[4], wk[4];
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-        xk[ks] = x_off[0] + k_off[ks];
-        wk[ks] = w_off[0] + k_off[ks];
-    }
+    // The two slots tile i - 1 released at its barrier are refilled as follows: second k-step of tile i - 1: weights
+    // of tile i + 1 (needed first); first k-step of tile i: activations of tile i + 2.  Before the barrier of tile i
+    // everything but those activations must have landed.
+    bf16x8 xf[2][NB], wf[2][NB];
     auto fetch_piece = [&](const unsigned char* sx, const unsigned char* sw_, int ks, int buf, int q) {   // order of first use
         if (q == 0) wf[buf][0] = *reinterpret_cast<const bf16x8*>(sw_ + wk[ks]);
-        else if (q <= 4) xf[buf][q - 1] = *reinterpret_cast<const bf16x8*>(sx + xk[ks] + (q - 1) * 4096);
-        else wf[buf][q - 4] = *reinterpret_cast<const bf16x8*>(sw_ + wk[ks] + (w_off[q - 4] - w_off[0]));
+        else if (q <= NB) xf[buf][q - 1] = *reinterpret_cast<const bf16x8*>(sx + xk[ks] + (q - 1) * kBlk);
+        else wf[buf][q - NB] = *reinterpret_cast<const bf16x8*>(sw_ + wk[ks] + w_blk(q - NB));
     };
-    constexpr int PER = NCH / 2;                       // loads per wave per k-step
-    constexpr int LGAP = (NMMA - NFETCH) / PER;        // MFMAs between two loads of a wave
-    static_assert(LGAP >= 1 && LGAP * PER == NMMA - NFETCH, "the loads of a k-step go behind its LDS reads");
     // one k-step: MFMAs from buffer `cur`; fetch k-step `nks` of the tile in slots (sx, sw_) into the
-    // other buffer; request pieces p0 .. p0 + PER - 1 of one operand of k-tile `ikt` into slot `islot`
-    auto kstep = [&](int cur, const unsigned char* sx, const unsigned char* sw_, int nks, int ikt, int islot, bool iweights,
-                     int p0) {
+    // other buffer; request the NCH pieces of one operand of k-tile `ikt` into slot `islot`
+    auto kstep = [&](int cur, const unsigned char* sx, const unsigned char* sw_, int nks, int ikt, int islot, bool iweights) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int q = 0; q < NMMA; ++q) {
-            const int j = q >> 2, i = q & 3;
-            acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[cur][j], xf[cur][i], acc[j][i], 0, 0, 0);
-            if (q < NFETCH) fetch_piece(sx, sw_, nks, cur ^ 1, q);
-            if (q >= NFETCH && (q - NFETCH) % LGAP == LGAP - 1) issue_piece(ikt, islot, iweights, p0 + (q - NFETCH) / LGAP);
+            const int j = q >> 3, i = q & 7;
+            mfma16(acc[j][i], wf[cur][j], xf[cur][i]);
+            if (q % 2 == 0 && q / 2 < NFETCH) fetch_piece(sx, sw_, nks, cur ^ 1, q / 2);
+            if (q % 8 == 5) issue_piece(ikt, islot, iweights, q / 8);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -502,10 +448,8 @@ __global__ __launch_bounds__(128 * WN, 1) void gemm_big_kernel(const bf16* __res
     issue_unit(kt0, 0, false);
     issue_unit(kt0, 1, true);
     issue_unit(kt0 + 1, 2, false);
-#pragma unroll
-    for (int q = 0; q < NCH / 2; ++q) issue_piece(kt0 + 1, 3, true, q);
-    static_assert(WN == 2 && NCH == 8, "the hand-written wait counts below assume four waves filling eight chunks each");
-    __builtin_amdgcn_s_waitcnt(0x0F7C);                // vmcnt(12): tile kt0 landed
+    issue_unit(kt0 + 1, 3, true);
+    __builtin_amdgcn_s_waitcnt(0x4F70);                // vmcnt(16): tile kt0 landed
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -516,176 +460,136 @@ __global__ __launch_bounds__(128 * WN, 1) void gemm_big_kernel(const bf16* __res
         const int na = (sa + 2 >= kBigSlots) ? sa + 2 - kBigSlots : sa + 2;      // next tile's slots
         const int nw = (sa + 3 >= kBigSlots) ? sa + 3 - kBigSlots : sa + 3;
         const int fa2 = (sa + 4 >= kBigSlots) ? sa + 4 - kBigSlots : sa + 4;     // where tile i + 2's activations go
-        const unsigned char* sx = smem_raw + sa * kBigSlot;
-        const unsigned char* sww = smem_raw + sw1 * kBigSlot;
-        kstep(0, sx, sww, 1, kt0 + i + 1, nw, true, NCH / 2);
-        kstep(1, sx, sww, 2, kt0 + i + 2, fa2, false, 0);
-        kstep(0, sx, sww, 3, kt0 + i + 2, fa2, false, NCH / 2);
+        kstep(0, smem_raw + sa * kBigSlot, smem_raw + sw1 * kBigSlot, 1, kt0 + i + 2, fa2, false);
         // tile i + 1 has landed (only the NCH newest loads, activations of tile i + 2, may be in flight);
         // own LDS reads of tile i are done
         __builtin_amdgcn_s_waitcnt(0x0078);            // vmcnt(8) lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        // tile i + 2's weights, first half, into the slot this tile's activations just left
-        kstep(1, smem_raw + na * kBigSlot, smem_raw + nw * kBigSlot, 0, kt0 + i + 2, sa, true, 0);
+        // tile i + 2's weights into the slot this tile's activations just left
+        kstep(1, smem_raw + na * kBigSlot, smem_raw + nw * kBigSlot, 0, kt0 + i + 2, sa, true);
         sa = na;
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);                // no LDS write may be in flight when the workgroup ends
+    mfma_settle();
 
     if (PARTIAL) {
-        // partial tile in accumulator order: every (wave, j, i, r) is one 256-byte row of `ws`
-        float* base = ws + (size_t)slot * 65536 + (size_t)wave_u * NJ * 4 * 16 * 64;     // wave-uniform
+        // partial tile in accumulator order: every (wave, j, i) is 1 KiB of `ws`, four values per lane
+        float* base = ws + (size_t)slot * 65536 + (size_t)wave_u * (NB * NB * 256) + lane * 4;
 #pragma unroll
-        for (int j = 0; j < NJ; ++j)
+        for (int i = 0; i < NB; ++i) {
+            // a 16-token block wholly past the last row is never read back (a few hundred rows fill
+            // only part of a 256-row tile, and the partial tiles are most of the traffic then)
+            if (m0 + (wave_u >> 1) * 128 + i * 16 < M) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                // a 32-token block wholly past the last row is never read back (a few hundred rows fill
-                // only part of a 256-row tile, and the partial tiles are most of the traffic then)
-                if (m0 + (wave_u / WN) * 128 + i * 32 < M) {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) base[((j * 4 + i) * 16 + r) * 64 + lane] = acc[j][i][r];
-                }
-                __builtin_amdgcn_sched_barrier(0);     // one block at a time: few registers besides the accumulators are free
+                for (int j = 0; j < NB; ++j) *reinterpret_cast<f32x4*>(base + (j * NB + i) * 256) = acc[j][i];
             }
-        return;
-    }
-    if (MODE == 1 && (N & 7) == 0) {
-        // R may be C itself (the residual stream is updated in place); a lane reads exactly the addresses it
-        // writes, so a token block's residual values are fetched together, and the next block's before this
-        // block's stores go out (written as load-then-store the loads would queue behind the stores).
-        // 16-byte form: registers 8p..8p+7 of feature block j are features 16p + 8*lk + 0..7.
-        bf16x8 rv[2][NJ * 2];
-        auto load_r = [&](int i, int buf) {
-            int m = m0 + wm * 128 + i * 32 + lrow;
-            if (m > M - 1) m = M - 1;                   // rows and features past the end: a valid address, value unused
-            const bf16* rrow = R + (size_t)m * N;
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-#pragma unroll
-                for (int p = 0; p < 2; ++p) {
-                    int n = n0 + fbase[j] + 16 * p + 8 * lk;
-                    if (n > N - 8) n = N - 8;
-                    rv[buf][j * 2 + p] = *reinterpret_cast<const bf16x8*>(rrow + n);
-                }
-        };
-        load_r(0, 0);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (i + 1 < 4) load_r(i + 1, (i + 1) & 1);
-            __builtin_amdgcn_sched_barrier(0);
-            const int m = m0 + wm * 128 + i * 32 + lrow;
-            if (m < M) {
-                bf16* crow = C + (size_t)m * N;
-#pragma unroll
-                for (int j = 0; j < NJ; ++j)
-#pragma unroll
-                    for (int p = 0; p < 2; ++p) {
-                        const int n = n0 + fbase[j] + 16 * p + 8 * lk;
-                        if (n < N) {
-                            bf16x8 o;
-#pragma unroll
-                            for (int e = 0; e < 8; ++e) o[e] = (bf16)(acc[j][i][8 * p + e] + (float)rv[i & 1][j * 2 + p][e]);
-                            *reinterpret_cast<bf16x8*>(crow + n) = o;
-                        }
-                    }
-            }
-            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_sched_barrier(0);         // one block at a time: few registers besides the accumulators are free
         }
         return;
     }
-    // 8-byte form (N not a multiple of 8; a residual is then read element group by element group)
+    constexpr int NP = (MODE == 2) ? 2 : 4;            // feature pairs a wave writes
+    // R may be C itself (the residual stream is updated in place); a lane reads exactly the addresses it
+    // writes, so a token block's residual values are fetched together, and the next block's before this
+    // block's stores go out (written as load-then-store the loads would queue behind the stores).
+    bf16x8 rv[2][NP];
+    auto load_r = [&](int i, int buf) {
+        int m = m0 + wm * 128 + i * 16 + lrow;
+        if (m > M - 1) m = M - 1;                       // rows past the end: a valid address, value unused
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-        big_store_block<MODE, NJ>([&](int j, int x) { return acc[j][i][x]; }, m0 + wm * 128 + i * 32 + lrow, n0, fbase,
-                                  lk, R, C, M, N);
+        for (int p = 0; p < NP; ++p)
+            rv[buf][p] = big_load8(R + (size_t)m * N, n0 + big_pair_feature<MODE>(wn, p) + 8 * lg, N);
+    };
+    if (MODE == 1) load_r(0, 0);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        if (MODE == 1 && i + 1 < NB) load_r(i + 1, (i + 1) & 1);
+        __builtin_amdgcn_sched_barrier(0);
+        const int m = m0 + wm * 128 + i * 16 + lrow;
+        if (m < M) {
+            bf16* crow = C + (size_t)m * N;
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                float o[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float v = acc[2 * p + (e >> 2)][i][e & 3];
+                    if (MODE == 2) o[e] = silu_fast(v) * acc[NB / 2 + 2 * p + (e >> 2)][i][e & 3];
+                    else if (MODE == 1) o[e] = v + (float)rv[i & 1][p][e];
+                    else o[e] = v;
+                }
+                big_store8(crow, n0 + big_pair_feature<MODE>(wn, p) + 8 * lg, N, o);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
 }
 
-// Adds the partial tiles of one split tile in range order and applies the epilogue.  One wave per
-// (wave of the main kernel, feature block j, token block i, piece of the block's 16 registers): a lane sums
-// the values behind one output store, 8 consecutive features (registers 8p..8p+7, a 16-byte store) when
-// WIDE - rows of N % 8 == 0 features - else 4 (registers 4g..4g+3).  The ranges are taken four at a time,
-// then two, then one, every batch's loads going out together; the sums run in range order whatever the
-// batching.  Grid (split tiles, units / 4).
-template <int MODE, int WN, bool WIDE>
+// Adds the partial tiles of one split tile in range order and applies the epilogue.  One wave per (wave of the
+// main kernel, feature pair p, token block i): a lane sums the 8 values behind one token's 8 consecutive features.
+// The ranges are taken four at a time, then two, then one, every batch's loads going out together; the sums run in
+// range order whatever the batching.  Grid (split tiles, units / 4).
+template <int MODE>
 __global__ __launch_bounds__(256) void gemm_big_fixup(const float* __restrict__ ws, const bf16* R, bf16* C, int M,
                                                       int N, int tiles_m, int tiles_n, int n_dp, int splits) {
-    constexpr int NJ = 8 / WN;
-    constexpr int NJE = (MODE == 2) ? NJ / 2 : NJ;      // output blocks per wave of the main kernel
-    constexpr int NV = (MODE == 2) ? 2 : 1;             // accumulator blocks behind one output block
-    constexpr int GV = WIDE ? 8 : 4;                    // values per lane and accumulator block
-    constexpr int PB = WIDE ? 1 : 2;                    // bits of the piece index
+    constexpr int NB = 8;
+    constexpr int NP = (MODE == 2) ? 2 : 4;             // feature pairs per wave of the main kernel
+    constexpr int NV = (MODE == 2) ? 2 : 1;             // factors behind one output
     const int tile = blockIdx.x;
     const BigTile bt = big_tile_of<MODE>(n_dp + tile, tiles_m, tiles_n);
     const int lane = threadIdx.x & 63;
     const int u = blockIdx.y * 4 + (threadIdx.x >> 6);
-    const int piece = u & ((1 << PB) - 1), i = (u >> PB) & 3, j = (u >> (PB + 2)) % NJE, wave = (u >> (PB + 2)) / NJE;
-    const int wm = wave / WN, wn = wave % WN;
-    const int lrow = lane & 31, lk = lane >> 5;
-    int fbase[NJ], wrow[NJ];
-    big_feature_bases<MODE, NJ, WN>(wn, fbase, wrow);
-    int fb = 0;
-#pragma unroll
-    for (int jj = 0; jj < NJE; ++jj) fb = (jj == j) ? fbase[jj] : fb;
-    if (bt.m0 + wm * 128 + i * 32 >= M) return;          // block past the last row: nothing was stored for it
-    const int m = bt.m0 + wm * 128 + i * 32 + lrow;
-    const int n = bt.n0 + fb + (WIDE ? 16 * piece + 8 * lk : big_group_feature(piece, lk));
-    // the residual does not depend on the sums: requested first (rows and features past the end: a valid
-    // address, value unused)
-    bf16x8 rv8;
-    bf16x4 rv4;
-    if (MODE == 1) {
-        const int mc = m < M ? m : M - 1;
-        int nc = n;
-        if (nc > N - GV) nc = N - GV;
-        if (WIDE) rv8 = *reinterpret_cast<const bf16x8*>(R + (size_t)mc * N + nc);
-        else rv4 = *reinterpret_cast<const bf16x4*>(R + (size_t)mc * N + nc);
-    }
-    float acc[NV][GV];
+    const int i = u & 7, p = (u >> 3) % NP, wave = (u >> 3) / NP;
+    const int wm = wave >> 1, wn = wave & 1;
+    const int lrow = lane & 15, lg = lane >> 4;
+    if (bt.m0 + wm * 128 + i * 16 >= M) return;          // block past the last row: nothing was stored for it
+    const int m = bt.m0 + wm * 128 + i * 16 + lrow;
+    const int n = bt.n0 + big_pair_feature<MODE>(wn, p) + 8 * lg;
+    // the residual does not depend on the sums: requested first
+    bf16x8 rv;
+    if (MODE == 1) rv = big_load8(R + (size_t)(m < M ? m : M - 1) * N, n, N);
+    f32x4 acc[NV][2];
 #pragma unroll
     for (int v = 0; v < NV; ++v)
 #pragma unroll
-        for (int e = 0; e < GV; ++e) acc[v][e] = 0.f;
-    const float* base = ws + (size_t)tile * splits * 65536 + (size_t)wave * NJ * 4 * 16 * 64 + lane;
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[v][b][e] = 0.f;
+    const float* base = ws + (size_t)tile * splits * 65536 + (size_t)wave * (NB * NB * 256) + lane * 4;
     auto batch = [&](int s0, auto nb) {
-        constexpr int NB = decltype(nb)::value;
-        float t[NB][NV][GV];
+        constexpr int NS = decltype(nb)::value;
+        f32x4 t[NS][NV][2];
 #pragma unroll
-        for (int q = 0; q < NB; ++q)
-#pragma unroll
-            for (int v = 0; v < NV; ++v)
-#pragma unroll
-                for (int e = 0; e < GV; ++e)
-                    t[q][v][e] = base[(size_t)(s0 + q) * 65536 + (((j + v * (NJ / 2)) * 4 + i) * 16 + GV * piece + e) * 64];
-#pragma unroll
-        for (int q = 0; q < NB; ++q)
+        for (int q = 0; q < NS; ++q)
 #pragma unroll
             for (int v = 0; v < NV; ++v)
 #pragma unroll
-                for (int e = 0; e < GV; ++e) acc[v][e] += t[q][v][e];
+                for (int b = 0; b < 2; ++b)
+                    t[q][v][b] = *reinterpret_cast<const f32x4*>(base + (size_t)(s0 + q) * 65536 +
+                                                                 ((v * (NB / 2) + 2 * p + b) * NB + i) * 256);
+#pragma unroll
+        for (int q = 0; q < NS; ++q)
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[v][b][e] += t[q][v][b][e];
     };
     int s0 = 0;
     for (; s0 + 4 <= splits; s0 += 4) batch(s0, std::integral_constant<int, 4>());
     if (s0 + 2 <= splits) { batch(s0, std::integral_constant<int, 2>()); s0 += 2; }
     if (s0 < splits) batch(s0, std::integral_constant<int, 1>());
-    if (m >= M || n >= N) return;
-    float o[GV];
+    if (m >= M) return;
+    float o[8];
 #pragma unroll
-    for (int e = 0; e < GV; ++e) {
-        if (MODE == 2) o[e] = silu_fast(acc[0][e]) * acc[NV - 1][e];
-        else if (MODE == 1) o[e] = acc[0][e] + (float)(WIDE ? rv8[e] : rv4[e]);
-        else o[e] = acc[0][e];
+    for (int e = 0; e < 8; ++e) {
+        const float v = acc[0][e >> 2][e & 3];
+        if (MODE == 2) o[e] = silu_fast(v) * acc[NV - 1][e >> 2][e & 3];
+        else if (MODE == 1) o[e] = v + (float)rv[e];
+        else o[e] = v;
     }
-    if (WIDE) {
-        bf16x8 w;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) w[e] = (bf16)o[e];
-        *reinterpret_cast<bf16x8*>(C + (size_t)m * N + n) = w;
-    } else {
-        bf16x4 w;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) w[e] = (bf16)o[e];
-        *reinterpret_cast<bf16x4*>(C + (size_t)m * N + n) = w;
-    }
+    big_store8(C + (size_t)m * N, n, N, o);
 }
 
 struct BigPlan {
@@ -736,8 +640,8 @@ template <int MODE>
 static bool big_available() {
     constexpr int LDS = kBigSlots * kBigSlot;
     static LdsLimit whole, partial;
-    const bool a = whole.raise(reinterpret_cast<const void*>(gemm_big_kernel<MODE, kBigWN, false>), LDS);
-    const bool b = partial.raise(reinterpret_cast<const void*>(gemm_big_kernel<MODE, kBigWN, true>), LDS);
+    const bool a = whole.raise(reinterpret_cast<const void*>(gemm_big_kernel<MODE, false>), LDS);
+    const bool b = partial.raise(reinterpret_cast<const void*>(gemm_big_kernel<MODE, true>), LDS);
     return a && b;
 }
 
@@ -745,8 +649,8 @@ template <int MODE>
 static void launch_big(const bf16* a, const bf16* w, const bf16* r, bf16* c, int M, int N, int K, float* ws,
                        size_t ws_bytes, hipStream_t st) {
     constexpr int LDS = kBigSlots * kBigSlot;
-    auto kern = gemm_big_kernel<MODE, kBigWN, false>;
-    auto kern_part = gemm_big_kernel<MODE, kBigWN, true>;
+    auto kern = gemm_big_kernel<MODE, false>;
+    auto kern_part = gemm_big_kernel<MODE, true>;
     BigPlan p = big_plan(MODE, M, N, K);
     if (p.tail > 0 && (ws == nullptr || ws_bytes < p.ws_bytes)) {     // no scratch: every tile whole
         p.n_dp = p.tiles_m * p.tiles_n;
@@ -754,18 +658,14 @@ static void launch_big(const bf16* a, const bf16* w, const bf16* r, bf16* c, int
         p.splits = 1;
     }
     if (p.n_dp > 0)
-        hipLaunchKernelGGL(kern, dim3(p.n_dp), dim3(128 * kBigWN), LDS, st, a, w, r, c, M, N, K, p.tiles_m, p.tiles_n,
+        hipLaunchKernelGGL(kern, dim3(p.n_dp), dim3(256), LDS, st, a, w, r, c, M, N, K, p.tiles_m, p.tiles_n,
                            p.n_dp, p.splits, ws);
     if (p.tail > 0) {
-        hipLaunchKernelGGL(kern_part, dim3(p.tail * p.splits), dim3(128 * kBigWN), LDS, st, a, w, r, c, M, N, K,
+        hipLaunchKernelGGL(kern_part, dim3(p.tail * p.splits), dim3(256), LDS, st, a, w, r, c, M, N, K,
                            p.tiles_m, p.tiles_n, p.n_dp, p.splits, ws);
-        constexpr int kUnits = 2 * kBigWN * ((MODE == 2) ? 4 / kBigWN : 8 / kBigWN) * 16;   // waves * blocks * (i, g)
-        if ((N & 7) == 0)
-            hipLaunchKernelGGL((gemm_big_fixup<MODE, kBigWN, true>), dim3(p.tail, kUnits / 8), dim3(256), 0, st, ws, r, c,
-                               M, N, p.tiles_m, p.tiles_n, p.n_dp, p.splits);
-        else
-            hipLaunchKernelGGL((gemm_big_fixup<MODE, kBigWN, false>), dim3(p.tail, kUnits / 4), dim3(256), 0, st, ws, r, c,
-                               M, N, p.tiles_m, p.tiles_n, p.n_dp, p.splits);
+        constexpr int kUnits = 4 * ((MODE == 2) ? 2 : 4) * 8;           // waves * feature pairs * token blocks
+        hipLaunchKernelGGL(gemm_big_fixup<MODE>, dim3(p.tail, kUnits / 4), dim3(256), 0, st, ws, r, c, M, N, p.tiles_m,
+                           p.tiles_n, p.n_dp, p.splits);
     }
 }
 

@@ -112,6 +112,14 @@ def test_gemm_random_problems(torch, case):
             test_gemm(torch, fp32, mode, M, N, K)
 
 
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("M,N,K", [(65, 4, 64), (272, 252, 128), (511, 260, 192), (513, 1004, 448), (769, 520, 640)])
+def test_gemm_large_tile_edges(torch, mode, M, N, K):
+    """The large-tile kernel around its 16-row blocks and 256-wide tiles, rows of 8k and 8k + 4 features, one k-tile
+    and a few, whole tiles and split ones."""
+    test_gemm(torch, False, mode, M, N, K)
+
+
 def test_gemm_residual_in_place_and_identity(torch):
     from paper_2412_17246_amd import op_gemm
     M, N = 150, 256
