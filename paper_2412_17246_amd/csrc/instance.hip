@@ -84,19 +84,28 @@ void ws_layout(const bz_config* c, WsLayout* w) {
     w->act = take(T * c->ffn * e);
     const size_t chunks = (c->max_seq_len + kDecodeChunk - 1) / kDecodeChunk;
     w->partial = take((size_t)c->max_seqs * c->n_q_heads * chunks * decode_partial_stride(c->head_dim) * sizeof(float));
-    {   // fp32 scratch of the GEMMs: the largest need of the four projections over every row count a
-        // call may bring (up to 256 rows: split-K partial sums, a plan per number of 64-row blocks and linear
-        // in the rows; beyond: partial tiles of split tiles, which depend on the number of 256-row tiles only)
+    {   // fp32 scratch of the GEMMs: the largest need of the four projections over every row count a call may bring.
+        // Up to 64 rows and beyond 2048 it does not fall with the rows (of a 256-row tile).  Between, every tile is a
+        // multiple of 32 rows, so within 32 rows the forms that compete stay the same and a form with fewer ranges of K, whose
+        // cost grows slower with the rows, can only replace one with more: what the first row count takes per row, times the
+        // last row count, bounds them all (asking for each of them would cost 2 ms of instance creation).
         const int qd = c->n_q_heads * c->head_dim;
         size_t g = 0;
-        auto need = [&](int M) {
-            size_t t = gemm_workspace_bytes(0, M, (int)nqkv, c->hidden); if (t > g) g = t;
-            t = gemm_workspace_bytes(1, M, c->hidden, qd); if (t > g) g = t;
-            t = gemm_workspace_bytes(2, M, c->ffn, c->hidden); if (t > g) g = t;
-            t = gemm_workspace_bytes(1, M, c->hidden, c->ffn); if (t > g) g = t;
+        auto need = [&](int M, int upto) {
+            for (const size_t t : {gemm_workspace_bytes(0, M, (int)nqkv, c->hidden), gemm_workspace_bytes(1, M, c->hidden, qd),
+                                   gemm_workspace_bytes(2, M, c->ffn, c->hidden), gemm_workspace_bytes(1, M, c->hidden, c->ffn)}) {
+                const size_t all = upto > M ? (t / M + 1) * upto : t;
+                if (all > g) g = all;
+            }
         };
-        for (int M = 64; M <= 256; M += 64) need(M < c->max_tokens ? M : c->max_tokens);   // split-K kernel: per 64-row block
-        for (int M = 256; M < c->max_tokens + 256; M += 256) need(M < c->max_tokens ? M : c->max_tokens);
+        const int most = c->max_tokens;
+        need(most < 64 ? most : 64, 0);
+        for (int M = 65; M <= 2048 && M <= most; M += 32) {
+            const int last = M + 31 < most ? M + 31 : most;
+            need(M, last);
+            need(last, 0);
+        }
+        for (int M = 2304; M < most + 256; M += 256) need(M < most ? M : most, 0);
         w->gemm_ws_bytes = g;
         w->gemm_ws = take(g);
     }

@@ -2,9 +2,9 @@
 // the matrix cores (v_mfma_f32_32x32x16_bf16), and three epilogues: plain, + residual, SwiGLU.
 //
 // Both operands are K-contiguous, so a lane's MFMA operand (8 consecutive k of one row / column)
-// is one 16-byte LDS read.  Three kernels share the work: gemm_big_kernel (prefill-sized problems: 256x256
-// tiles, operands global -> LDS by DMA into a five-slot ring), gemm_skinny_kernel (up to 256 rows: the
-// weights are streamed once, split over K) and gemm_kernel below (everything else: K tails, odd widths,
+// is one 16-byte LDS read.  Four kernels share the work: gemm_big_kernel (prefill-sized problems: 256x256
+// tiles, operands global -> LDS by DMA into a five-slot ring), gemm_mid_kernel (65 to 2048 rows: tiles sized to the
+// batch), gemm_skinny_kernel (up to 64 rows: the weights are streamed once, split over K) and gemm_kernel below (everything else: K tails, odd widths,
 // no workspace), which stages tiles global -> registers -> LDS, double buffered, one barrier per 64-wide
 // K step, LDS rows padded by 16 bytes so that the operand reads of 16 consecutive rows fall in distinct banks.
 #include <type_traits>
@@ -670,7 +670,377 @@ static void launch_big(const bf16* a, const bf16* w, const bf16* r, bf16* c, int
 }
 
 // ---------------------------------------------------------------------------------------------
-// Skinny kernel for decode-sized problems (M <= 256 rows): the weights are read from HBM exactly
+// Mid-sized kernel: 65 to 2048 rows (K a multiple of 64, N of 4).  The decode kernel would re-read the weights once
+// per 64 rows, and of 256x256 tiles half would be padding and fewer exist than CUs.  The tile is BM tokens x BN weight
+// rows, both chosen by mid_plan so that the padded problem is one round (or a few full ones) of workgroups, over one
+// or several ranges of K.  Four waves, WT of them along the tokens; a wave multiplies NBT x NBF blocks of 16x16x32.
+//
+// What bounds it is the delivery of the operands into LDS: a workgroup moves (BM + BN) * 128 bytes per k-tile at 57
+// bytes per ns and CU (13 TB/s over the chip, weights from HBM, activations from L2).  Leaving the MFMAs out changes
+// nothing (7B gate/up at 301 rows: 59.0 -> 59.4 us), and neither do four more waves that do nothing but request; with both
+// operands served by the L2 it takes 44 us.  So tiles are as square as filling the chip allows.
+// Cold weights, against the kernels that took these sizes before, microseconds at 161 / 301 / 552 rows: 7B qkv 44 -> 30 /
+// 62 -> 42 / 80 -> 54, o 19 -> 15 / 34 -> 23 / 43 -> 28, gate/up 84 -> 47 / 83 -> 59 / 111 -> 101, down 36 -> 31 / 50 -> 40 /
+// 81 -> 58; 8B-GQA gate/up 90 -> 56 / 96 -> 72 / 147 -> 120.
+//
+// A ring of as many whole stages (activations + weights of one 64-wide k-tile) as the CU's LDS holds, filled by
+// direct global->LDS loads.  The barrier of tile i sits between its two k-steps, whose second one runs from
+// registers: from there on tile i's stage is free, and tile i + kStages is requested into it over the following
+// two k-steps, so kStages - 2 whole tiles stay in flight across every barrier.  Operands of the next k-step are
+// read from LDS under the MFMAs of the present one.
+// ---------------------------------------------------------------------------------------------
+template <int WT, int NBT, int NBF> struct MidCfg {
+    static constexpr int WF = 4 / WT;
+    static constexpr int BM = WT * NBT * 16, BN = WF * NBF * 16;
+    static constexpr int kXBytes = BM * kBK * (int)sizeof(bf16);
+    static constexpr int kStage = (BM + BN) * kBK * (int)sizeof(bf16);
+    static constexpr int kFit = 160 * 1024 / kStage;
+    static constexpr int kStages = kFit < 5 ? kFit : 5;
+    static constexpr int kLds = kStage * kStages;
+    static_assert(NBF % 2 == 0 && BM % 32 == 0 && kStages >= 2, "tile");
+};
+
+// vmcnt(n) lgkmcnt(0), n < 64
+__device__ __forceinline__ constexpr int lds_wait(int n) { return ((n >> 4) << 14) | 0x0070 | (n & 15); }
+
+// GU (gate/up projection): weight rows come as N gate rows, then N up rows; a tile takes BN / 2 features, and of every
+// 32 LDS rows 16 hold gate and 16 the same features' up rows, so a lane holds both factors.
+// `partial` != nullptr: fp32 partial sums partial[range][M][Nrows]; else C, with the residual R unless null.
+template <bool GU, bool NT, int WT, int NBT, int NBF>
+__global__ __launch_bounds__(256, 1) void gemm_mid_kernel(const bf16* __restrict__ X, const bf16* __restrict__ W,
+                                                          float* __restrict__ partial, const bf16* R, bf16* C, int M,
+                                                          int Nrows, int K, int n_tiles, int m_tiles, int kt_per_split,
+                                                          int units) {
+    using Cfg = MidCfg<WT, NBT, NBF>;
+    constexpr int BM = Cfg::BM, BN = Cfg::BN, S = Cfg::kStages;
+    constexpr int PX = BM / 32, PW = BN / 32, P = PX + PW;      // 1 KiB pieces (8 rows) a wave requests per k-tile
+    constexpr int NMMA = NBT * NBF, NFETCH = NBT + NBF;
+    static_assert((S - 1) * P < 64, "loads in flight must be countable");
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
+    // A unit is one (weight tile, K range); its m_tiles workgroups get ids 8 apart, hence one XCD, one after the
+    // other, so that the later ones find the weights in that XCD's L2.
+    const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
+    const int unit = (seq / m_tiles) * 8 + xcd;
+    if (unit >= units) return;
+    const int m0 = (seq % m_tiles) * BM;
+    const int tile_n = unit % n_tiles, split = unit / n_tiles;
+    const int Nh = Nrows >> 1;                                  // GU: features per factor
+    const int n0 = tile_n * (GU ? BN / 2 : BN);
+    const int nk = K / kBK;
+    const int kt0 = split * kt_per_split;
+    const int kt1 = (kt0 + kt_per_split < nk) ? kt0 + kt_per_split : nk;
+    const int n = kt1 - kt0;                                    // >= 1
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wt = wave % WT, wf = wave / WT;
+    const int lrow = lane & 15, lg = lane >> 4;
+    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+
+    uint32_t x_off[PX], w_off[PW];
+#pragma unroll
+    for (int j = 0; j < PX; ++j) {
+        const int row = (wave * PX + j) * 8 + (lane >> 3);
+        int xr = m0 + row;
+        if (xr > M - 1) xr = M - 1;
+        x_off[j] = ((uint32_t)xr * (uint32_t)K + ((lane & 7) ^ swz(row)) * 8) * 2u;
+    }
+#pragma unroll
+    for (int j = 0; j < PW; ++j) {
+        const int row = (wave * PW + j) * 8 + (lane >> 3);
+        int wr;
+        if (GU) {
+            int f = n0 + (row >> 5) * 16 + (row & 15);
+            if (f > Nh - 1) f = Nh - 1;
+            wr = (row & 16) ? Nh + f : f;
+        } else {
+            wr = n0 + ((row & ~31) | big_row_feature(row & 31));
+            if (wr > Nrows - 1) wr = Nrows - 1;
+        }
+        w_off[j] = ((uint32_t)wr * (uint32_t)K + ((lane & 7) ^ swz(row)) * 8) * 2u;
+    }
+    const __amdgpu_buffer_rsrc_t rsrc_x =
+        __builtin_amdgcn_make_buffer_rsrc((void*)X, 0, (int)((uint32_t)M * (uint32_t)K * 2u), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsrc_w =
+        __builtin_amdgcn_make_buffer_rsrc((void*)W, 0, (int)((uint32_t)Nrows * (uint32_t)K * 2u), 0x00020000);
+    // piece q of the k-tile at byte offset `koff` into stage `st`: weights (from memory) first, then activations
+    auto issue_piece = [&](int koff, unsigned char* st, int q) {
+        if (q < PW)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_w, (lptr_t)(st + Cfg::kXBytes + (wave_u * PW + q) * 1024), 16,
+                                                     (int)w_off[q], koff, 0, NT ? 2 : 0);
+        else
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_x, (lptr_t)(st + (wave_u * PX + q - PW) * 1024), 16,
+                                                     (int)x_off[q - PW], koff, 0, 0);
+    };
+
+    f32x4 acc[NBF][NBT];
+#pragma unroll
+    for (int j = 0; j < NBF; ++j)
+#pragma unroll
+        for (int i = 0; i < NBT; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[j][i][r] = 0.f;
+
+    int xk[2], wk[2];                                           // operand addresses inside a stage, per k-step
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        const int piece = ((ks * 4 + lg) ^ swz(lrow)) * 16;
+        xk[ks] = (wt * NBT * 16 + lrow) * 128 + piece;
+        wk[ks] = Cfg::kXBytes + (wf * NBF * 16 + lrow) * 128 + piece;
+    }
+    bf16x8 xf[2][NBT], wfr[2][NBF];
+    auto fetch = [&](const unsigned char* st, int ks, int buf, int q) {        // in the order of first use
+        if (q == 0) wfr[buf][0] = *reinterpret_cast<const bf16x8*>(st + wk[ks]);
+        else if (q <= NBT) xf[buf][q - 1] = *reinterpret_cast<const bf16x8*>(st + xk[ks] + (q - 1) * 2048);
+        else wfr[buf][q - NBT] = *reinterpret_cast<const bf16x8*>(st + wk[ks] + (q - NBT) * 2048);
+    };
+    // One k-step: the MFMAs from buffer `cur`; between them the LDS reads of k-step `nks` of stage `st` into the other
+    // buffer, over the first three quarters, and the requests for pieces q0 .. q1 - 1, spread evenly.
+    auto kstep = [&](auto cur_, auto fetch_, const unsigned char* st, int nks, auto issue_, int koff, unsigned char* dst,
+                     int q0, int q1) {
+        constexpr int cur = decltype(cur_)::value;
+        constexpr bool do_fetch = decltype(fetch_)::value, do_issue = decltype(issue_)::value;
+        __builtin_amdgcn_sched_barrier(0);
+        auto fetch_upto = [](int q) { return q < 0 ? 0 : ((q + 1) * NFETCH * 4 + 3 * NMMA - 1) / (3 * NMMA); };
+        auto issue_upto = [&](int q) { return q0 + ((q + 1) * (q1 - q0)) / NMMA; };
+#pragma unroll
+        for (int q = 0; q < NMMA; ++q) {
+            acc[q / NBT][q % NBT] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wfr[cur][q / NBT], xf[cur][q % NBT],
+                                                                          acc[q / NBT][q % NBT], 0, 0, 0);
+            if (do_fetch) {
+#pragma unroll
+                for (int f = 0; f < NFETCH; ++f)
+                    if (f >= fetch_upto(q - 1) && f < fetch_upto(q)) fetch(st, nks, cur ^ 1, f);
+            }
+            if (do_issue) {
+#pragma unroll
+                for (int f = 0; f < P; ++f)
+                    if (f >= issue_upto(q - 1) && f < issue_upto(q)) issue_piece(koff, dst, f);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // all but the newest `tiles` k-tiles requested have landed, own LDS reads are done; then everyone's
+    auto wait_barrier = [&](int tiles) {
+        if (S > 4 && tiles >= 4) __builtin_amdgcn_s_waitcnt(lds_wait(S > 4 ? 4 * P : 0));
+        else if (S > 3 && tiles == 3) __builtin_amdgcn_s_waitcnt(lds_wait(S > 3 ? 3 * P : 0));
+        else if (S > 2 && tiles == 2) __builtin_amdgcn_s_waitcnt(lds_wait(S > 2 ? 2 * P : 0));
+        else if (tiles == 1) __builtin_amdgcn_s_waitcnt(lds_wait(P));
+        else __builtin_amdgcn_s_waitcnt(lds_wait(0));
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    using C0 = std::integral_constant<int, 0>;
+    using C1 = std::integral_constant<int, 1>;
+    using Yes = std::true_type;
+    using No = std::false_type;
+
+    // With one row of tiles the walk over K starts tile_n / n_tiles of the way in when the row pitch is a power of two, as
+    // in the decode kernel below and for its reason (161 rows: 7B gate/up 47.4 -> 44.7 us, 8B-GQA 55.7 -> 51.7).  With several, the
+    // workgroups that share a weight tile and those that share activations do better in step (552 rows: 8B-GQA qkv 34.5 in
+    // step, 40.8 shifted).
+    const int rot = (m_tiles == 1 && (K & (K - 1)) == 0 && n >= 32) ? (int)(((long long)tile_n * n) / n_tiles) : 0;
+    auto koff_of = [&](int j) { const int r = j + rot; return (kt0 + (r >= n ? r - n : r)) * (kBK * 2); };
+    const int first = n < S ? n : S;
+#pragma unroll
+    for (int t = 0; t < S; ++t)
+        if (t < n) {
+            const int koff = koff_of(t);
+#pragma unroll
+            for (int q = 0; q < P; ++q) issue_piece(koff, smem_raw + t * Cfg::kStage, q);
+        }
+    wait_barrier(first - 1);
+#pragma unroll
+    for (int q = 0; q < NFETCH; ++q) fetch(smem_raw, 0, 0, q);
+    kstep(C0(), Yes(), smem_raw, 1, No(), 0, smem_raw, 0, 0);
+    int s = 0;
+    int i = 0;
+    for (; i < n - S; ++i) {
+        wait_barrier(S - 2);
+        const int nx = s + 1 == S ? 0 : s + 1;
+        const int koff = koff_of(i + S);
+        const unsigned char* next = smem_raw + nx * Cfg::kStage;
+        unsigned char* dst = smem_raw + s * Cfg::kStage;
+        kstep(C1(), Yes(), next, 0, Yes(), koff, dst, 0, (P + 1) / 2);
+        kstep(C0(), Yes(), next, 1, Yes(), koff, dst, (P + 1) / 2, P);
+        s = nx;
+    }
+    for (; i < n - 1; ++i) {
+        wait_barrier(n - 2 - i);
+        const int nx = s + 1 == S ? 0 : s + 1;
+        const unsigned char* next = smem_raw + nx * Cfg::kStage;
+        kstep(C1(), Yes(), next, 0, No(), 0, smem_raw, 0, 0);
+        kstep(C0(), Yes(), next, 1, No(), 0, smem_raw, 0, 0);
+        s = nx;
+    }
+    kstep(C1(), No(), smem_raw, 0, No(), 0, smem_raw, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+
+    // A lane holds, of token block i, token i*16 + lane%16, and of block pair p either 8 consecutive weight rows or
+    // (GU) 4 consecutive features of both factors.
+#pragma unroll
+    for (int i = 0; i < NBT; ++i) {
+        const int m = m0 + (wt * NBT + i) * 16 + lrow;
+        if (m < M) {
+            if (partial != nullptr) {
+                float* prow = partial + ((size_t)split * M + m) * Nrows;
+#pragma unroll
+                for (int p = 0; p < NBF / 2; ++p) {
+                    if (GU) {
+                        const int f = n0 + (wf * (NBF / 2) + p) * 16 + 4 * lg;
+                        if (f < Nh) {
+                            *reinterpret_cast<f32x4*>(prow + f) = acc[2 * p][i];
+                            *reinterpret_cast<f32x4*>(prow + Nh + f) = acc[2 * p + 1][i];
+                        }
+                    } else {
+                        const int f = n0 + wf * NBF * 16 + p * 32 + 8 * lg;
+                        if (f < Nrows) *reinterpret_cast<f32x4*>(prow + f) = acc[2 * p][i];
+                        if (f + 4 < Nrows) *reinterpret_cast<f32x4*>(prow + f + 4) = acc[2 * p + 1][i];
+                    }
+                }
+            } else if (GU) {
+                bf16* crow = C + (size_t)m * Nh;
+#pragma unroll
+                for (int p = 0; p < NBF / 2; ++p) {
+                    const int f = n0 + (wf * (NBF / 2) + p) * 16 + 4 * lg;
+                    bf16x4 o;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e] = (bf16)(silu_fast(acc[2 * p][i][e]) * acc[2 * p + 1][i][e]);
+                    if (f < Nh) *reinterpret_cast<bf16x4*>(crow + f) = o;
+                }
+            } else {
+                // R may be C itself: a token's residual values are read before its results are written
+                bf16x8 rv[NBF / 2];
+                if (R != nullptr) {
+#pragma unroll
+                    for (int p = 0; p < NBF / 2; ++p)
+                        rv[p] = big_load8(R + (size_t)m * Nrows, n0 + wf * NBF * 16 + p * 32 + 8 * lg, Nrows);
+                }
+#pragma unroll
+                for (int p = 0; p < NBF / 2; ++p) {
+                    float o[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        o[e] = acc[2 * p + (e >> 2)][i][e & 3];
+                        if (R != nullptr) o[e] += (float)rv[p][e];
+                    }
+                    big_store8(C + (size_t)m * Nrows, n0 + wf * NBF * 16 + p * 32 + 8 * lg, Nrows, o);
+                }
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// Tiles that exist.  Chosen so that over 65 .. 1600 rows of six projection shapes the best of them is within 1 % of the
+// best of 34 measured.
+struct MidTile { int wt, nbt, nbf; };
+#define BZ_MID_TILES(X) X(2, 3, 4) X(4, 2, 4) X(4, 2, 6) X(4, 3, 6) X(4, 3, 8) X(2, 5, 4) X(2, 5, 6) X(2, 6, 6) X(2, 7, 6) \
+                        X(2, 5, 8) X(2, 8, 4) X(4, 4, 6) X(4, 5, 6)
+constexpr MidTile kMidTiles[] = {
+#define BZ_MID_ENTRY(a, b, c) {a, b, c},
+    BZ_MID_TILES(BZ_MID_ENTRY)
+#undef BZ_MID_ENTRY
+};
+constexpr int kMidMinM = 65, kMidMaxM = 2048;
+// Partial sums stay within what every caller's scratch could always hold.
+constexpr size_t kMidMaxPartial = (size_t)64 << 20;
+
+struct MidPlan {
+    int tile, m_tiles, n_tiles, kt_per_split, ksplit;
+    float us;                    // what the model expects, with the cost of folding the partial sums
+    size_t ws_bytes;
+};
+
+// Time model, microseconds, fitted to 900 measurements (9 % rms): a k-tile costs 0.14 + 0.48e-3 (BM + BN) + 1.33e-5 BM BN, a
+// round of 256 workgroups 2.8 more, the whole at least the weights at 4.8 TB/s; a MB of partial sums 0.27 to write and 0.25
+// to read in the kernel that folds it.  Picking by it costs 2 to 4 % against picking the fastest measured form.
+static MidPlan mid_plan(int mode, int M, int N, int K, bool may_split) {
+    const int Nrows = (mode == 2) ? 2 * N : N, nk = K / kBK;
+    constexpr int kCUs = 256, kMinKt = 4;
+    MidPlan best{};
+    best.us = -1.f;
+    for (int t = 0; t < (int)(sizeof(kMidTiles) / sizeof(kMidTiles[0])); ++t) {
+        const int bm = kMidTiles[t].wt * kMidTiles[t].nbt * 16, bn = (4 / kMidTiles[t].wt) * kMidTiles[t].nbf * 16;
+        const int mt = (M + bm - 1) / bm, nt = (Nrows + bn - 1) / bn;
+        const float tk = 0.14f + 0.48e-3f * (float)(bm + bn) + 1.33e-5f * (float)(bm * bn);
+        int most = may_split ? kCUs / (mt * nt) : 1;
+        if (most > 16) most = 16;
+        if (most > nk / kMinKt) most = nk / kMinKt;
+        for (int ks = 1; ks == 1 || ks <= most; ++ks) {
+            const int per = (nk + ks - 1) / ks;
+            if ((nk + per - 1) / per != ks) continue;           // same ranges as a smaller number of them
+            const size_t bytes = ks > 1 ? (size_t)ks * M * Nrows * sizeof(float) : 0;
+            if (bytes > kMidMaxPartial) break;
+            const int rounds = (mt * nt * ks + kCUs - 1) / kCUs;
+            float body = (float)rounds * (float)per * tk;
+            const float stream = (float)Nrows * (float)K * 2.0f / 4.8e6f;
+            if (body < stream) body = stream;
+            const float us = 2.1f + body + 2.8f * (float)rounds + 0.52e-6f * (float)bytes;
+            if (best.us < 0.f || us < best.us) best = MidPlan{t, mt, nt, per, ks, us, bytes};
+        }
+    }
+    return best;
+}
+
+// The large-tile kernel on the same scale: 1.4 us per k-tile and round; split tiles add a fix-up launch and their traffic.
+static float big_us(int mode, int M, int N, int K) {
+    const BigPlan p = big_plan(mode, M, N, K);
+    const int nk = K / kBK;
+    float us = 3.0f + (float)((p.n_dp + 255) / 256 * nk) * 1.4f;
+    if (p.tail > 0) us += (float)((nk + p.splits - 1) / p.splits) * 1.4f + 8.0f + (float)p.ws_bytes * 0.35e-6f;
+    return us;
+}
+
+// Whether the mid-sized kernel takes the problem: always up to 256 rows (the large tiles never win there), beyond where the
+// models say so.  301 .. 1600 rows of the measured shapes: the choice is within 3 % of the better of the two on average.
+static bool mid_takes(int mode, int M, int N, int K, MidPlan& p) {
+    if (M < kMidMinM || M > kMidMaxM || !big_ok(M, N, K)) return false;
+    p = mid_plan(mode, M, N, K, true);
+    return M <= 256 || p.us < big_us(mode, M, N, K);
+}
+
+struct MidArgs {
+    const bf16* x; const bf16* w; float* partial; const bf16* r; bf16* c;
+    int M, Nrows, K, n_tiles, m_tiles, kt_per_split, units;
+};
+
+// false: the runtime does not grant the kernel its LDS
+template <bool GU, int WT, int NBT, int NBF>
+static bool mid_go(hipStream_t st, const MidArgs& g) {
+    using Cfg = MidCfg<WT, NBT, NBF>;
+    const dim3 grid((g.units + 7) / 8 * 8 * g.m_tiles);
+    // weights that one workgroup reads and nobody else are loaded with the non-temporal policy (1.5 - 3 % at 65 .. 301 rows)
+    if (g.m_tiles == 1) {
+        static LdsLimit limit;
+        if (!limit.raise(reinterpret_cast<const void*>(gemm_mid_kernel<GU, true, WT, NBT, NBF>), Cfg::kLds)) return false;
+        hipLaunchKernelGGL((gemm_mid_kernel<GU, true, WT, NBT, NBF>), grid, dim3(256), Cfg::kLds, st, g.x, g.w, g.partial, g.r,
+                           g.c, g.M, g.Nrows, g.K, g.n_tiles, g.m_tiles, g.kt_per_split, g.units);
+    } else {
+        static LdsLimit limit;
+        if (!limit.raise(reinterpret_cast<const void*>(gemm_mid_kernel<GU, false, WT, NBT, NBF>), Cfg::kLds)) return false;
+        hipLaunchKernelGGL((gemm_mid_kernel<GU, false, WT, NBT, NBF>), grid, dim3(256), Cfg::kLds, st, g.x, g.w, g.partial, g.r,
+                           g.c, g.M, g.Nrows, g.K, g.n_tiles, g.m_tiles, g.kt_per_split, g.units);
+    }
+    return true;
+}
+
+// Partial sums into `ws` when the plan has several ranges of K, else the result itself into `c` (r: the residual or null).
+static bool launch_mid(int mode, const MidPlan& p, const bf16* x, const bf16* w, const bf16* r, bf16* c, int M, int N, int K,
+                       float* ws, hipStream_t st) {
+    using Fn = bool (*)(hipStream_t, const MidArgs&);
+#define BZ_MID_FN(a, b, c) mid_go<false, a, b, c>,
+#define BZ_MID_FN_GU(a, b, c) mid_go<true, a, b, c>,
+    static constexpr Fn plain[] = {BZ_MID_TILES(BZ_MID_FN)};
+    static constexpr Fn gated[] = {BZ_MID_TILES(BZ_MID_FN_GU)};
+#undef BZ_MID_FN
+#undef BZ_MID_FN_GU
+    const MidArgs g{x, w, p.ksplit > 1 ? ws : nullptr, mode == 1 ? r : nullptr, c, M, (mode == 2) ? 2 * N : N, K,
+                    p.n_tiles, p.m_tiles, p.kt_per_split, p.n_tiles * p.ksplit};
+    return (mode == 2 ? gated : plain)[p.tile](st, g);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Skinny kernel for decode-sized problems (M <= 64 rows): the weights are read from HBM exactly
 // once and that read is the whole cost, so the job is to keep every CU streaming.  Work is cut
 // into tiles of 64 * RB weight rows times KSPLIT slices of K (a function of the shape only); each
 // workgroup streams its weight slice and the matching activation slice through a ring of LDS
@@ -687,12 +1057,10 @@ static void launch_big(const bf16* a, const bf16* w, const bf16* r, bf16* c, int
 // 70B qkv 40.9 -> 37.1, o 36.1 -> 37.8, gate/up 185 -> 168, down 96.5 -> 78.5 us.  (Three stages and
 // two workgroups per CU win on some of these shapes and lose on others.)
 // ---------------------------------------------------------------------------------------------
-// TB = 32-row blocks of activation rows per wave: a workgroup covers 64 * TB rows (64 when the batch
-// has no more; 128 beyond, so that 65..128 rows still read every weight once and 129..256 rows twice).
-template <int RB, int TB> struct SkCfg {
-    static constexpr int kXBytes = 64 * TB * kBK * (int)sizeof(bf16);         // activations of a stage: 8 KiB * TB
+template <int RB> struct SkCfg {
+    static constexpr int kXBytes = 64 * kBK * (int)sizeof(bf16);              // activations of a stage: 8 KiB
     static constexpr int kStage = kXBytes + 64 * RB * kBK * (int)sizeof(bf16);  // + weights 8 KiB * RB
-    static constexpr int kStages = (RB == 1 && TB == 1) ? 4 : 5;
+    static constexpr int kStages = RB == 1 ? 4 : 5;
     static constexpr int kLds = kStage * kStages;
     static constexpr int kPerCu = kLds * 2 <= 160 * 1024 ? 2 : 1;
     static constexpr int kSlots = 256 * kPerCu;                               // workgroups the chip holds at a time
@@ -702,35 +1070,22 @@ template <int RB, int TB> struct SkCfg {
 // a short one does not or gets slower).
 constexpr size_t kSkStreamBytes = (size_t)64 << 20;
 
-// vmcnt(n) lgkmcnt(0), n < 64
-__device__ __forceinline__ constexpr int sk_wait(int n) { return ((n >> 4) << 14) | 0x0070 | (n & 15); }
-
 // GU (gate/up projection): a tile is 32 * RB gate features (weight rows n0..) and the matching up
 // features (rows N + n0..), so that with a single k-slice the workgroup holds both factors of
 // silu(gate) * up and writes the activation itself (C != nullptr) instead of partial sums.
 // NT: the weight loads carry the non-temporal cache policy.
-template <bool GU, bool NT, int RB, int TB>
-__global__ __launch_bounds__(256, (SkCfg<RB, TB>::kPerCu)) void gemm_skinny_kernel(const bf16* __restrict__ X,
-                                                                                   const bf16* __restrict__ W,
-                                                                                   float* __restrict__ partial,
-                                                                                   bf16* __restrict__ C, int M, int Nrows,
-                                                                                   int K, int n_tiles, int kt_per_split,
-                                                                                   int rows, int m_blocks, int units) {
-    using Cfg = SkCfg<RB, TB>;
+template <bool GU, bool NT, int RB>
+__global__ __launch_bounds__(256, SkCfg<RB>::kPerCu) void gemm_skinny_kernel(const bf16* __restrict__ X,
+                                                                             const bf16* __restrict__ W,
+                                                                             float* __restrict__ partial,
+                                                                             bf16* __restrict__ C, int M, int Nrows, int K,
+                                                                             int n_tiles, int kt_per_split, int rows) {
+    using Cfg = SkCfg<RB>;
     constexpr int kStage = Cfg::kStage, kStages = Cfg::kStages, kXBytes = Cfg::kXBytes;
-    constexpr int LPS = 2 * TB + 2 * RB;              // loads per wave and stage
+    constexpr int LPS = 2 + 2 * RB;                   // loads per wave and stage
     constexpr int HALF = 32 * RB;                     // rows per wave along the features (GU: rows per factor)
-    constexpr int MT = 64 * TB;                       // activation rows per workgroup
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
-    // A unit is one (tile, k-slice); with more activation rows than a workgroup covers it is worked on by
-    // m_blocks workgroups.  Workgroups are handed to the eight XCDs in turn, so the workgroups of a
-    // unit are given ids 8 apart: same XCD, one right after the other, and the weights the first one
-    // pulls from HBM are found in that XCD's L2 by the others.
-    const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
-    const int unit = (seq / m_blocks) * 8 + xcd;
-    if (unit >= units) return;
-    const int m0 = (seq % m_blocks) * MT;
-    const int tile_n = unit % n_tiles, split = unit / n_tiles;
+    const int tile_n = blockIdx.x % n_tiles, split = blockIdx.x / n_tiles;
     // `rows` <= 64 * RB weight rows of those the tile has room for are real (GU: rows / 2 of each factor);
     // the launcher picks it so that the grid fills the chip's workgroup slots evenly
     const int tr = GU ? rows >> 1 : rows;             // real rows per factor (GU) or per tile
@@ -746,13 +1101,13 @@ __global__ __launch_bounds__(256, (SkCfg<RB, TB>::kPerCu)) void gemm_skinny_kern
     const int lrow = lane & 31, lk = lane >> 5;
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
 
-    // loader: 1 KiB chunks of 8 rows; the first 8 * TB chunks of a stage hold the activation rows, the
-    // 8 * RB after them the weight rows; this wave fills 2 * TB of the former and 2 * RB of the latter
-    uint32_t x_src[2 * TB], w_src[2 * RB];
+    // loader: 1 KiB chunks of 8 rows; the first 8 chunks of a stage hold the activation rows, the
+    // 8 * RB after them the weight rows; this wave fills 2 of the former and 2 * RB of the latter
+    uint32_t x_src[2], w_src[2 * RB];
 #pragma unroll
-    for (int j = 0; j < 2 * TB; ++j) {
-        const int row = (wave * 2 * TB + j) * 8 + (lane >> 3);
-        int xr = m0 + row;
+    for (int j = 0; j < 2; ++j) {
+        const int row = (wave * 2 + j) * 8 + (lane >> 3);
+        int xr = row;
         if (xr > M - 1) xr = M - 1;
         x_src[j] = ((uint32_t)xr * (uint32_t)K + ((lane & 7) ^ swz(row)) * 8) * 2u;
     }
@@ -777,23 +1132,21 @@ __global__ __launch_bounds__(256, (SkCfg<RB, TB>::kPerCu)) void gemm_skinny_kern
         const char* wk = reinterpret_cast<const char*>(W + (size_t)kt * kBK);
         unsigned char* sb = smem_raw + stage * kStage;
 #pragma unroll
-        for (int j = 0; j < 2 * TB; ++j)
-            __builtin_amdgcn_global_load_lds((gptr_t)(xk + x_src[j]), (lptr_t)(sb + (wave_u * 2 * TB + j) * 1024), 16, 0, 0);
+        for (int j = 0; j < 2; ++j)
+            __builtin_amdgcn_global_load_lds((gptr_t)(xk + x_src[j]), (lptr_t)(sb + (wave_u * 2 + j) * 1024), 16, 0, 0);
 #pragma unroll
         for (int j = 0; j < 2 * RB; ++j)
             __builtin_amdgcn_global_load_lds((gptr_t)(wk + w_src[j]), (lptr_t)(sb + kXBytes + (wave_u * 2 * RB + j) * 1024),
                                              16, 0, NT ? 2 : 0);
     };
 
-    f32x16 acc[RB][TB];
+    f32x16 acc[RB];
 #pragma unroll
     for (int b = 0; b < RB; ++b)
 #pragma unroll
-        for (int t = 0; t < TB; ++t)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[b][t][r] = 0.f;
+        for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
     const int sw = swz(lrow);
-    const int x_off = (wt * 32 * TB + lrow) * 128;
+    const int x_off = (wt * 32 + lrow) * 128;
     const int w_off = kXBytes + (wf * HALF + lrow) * 128;
 
     // Every workgroup would walk its k-tiles in the same order at about the same pace, so that at any moment the
@@ -813,11 +1166,11 @@ __global__ __launch_bounds__(256, (SkCfg<RB, TB>::kPerCu)) void gemm_skinny_kern
     for (int i = 0; i < n; ++i) {
         // tile i must have landed; the tiles requested after it (LPS loads each) may still be in flight
         const int later = (n - 1 - i < kStages - 2) ? n - 1 - i : kStages - 2;
-        if (later >= 4) __builtin_amdgcn_s_waitcnt(sk_wait(4 * LPS));
-        else if (later == 3) __builtin_amdgcn_s_waitcnt(sk_wait(3 * LPS));
-        else if (later == 2) __builtin_amdgcn_s_waitcnt(sk_wait(2 * LPS));
-        else if (later == 1) __builtin_amdgcn_s_waitcnt(sk_wait(LPS));
-        else __builtin_amdgcn_s_waitcnt(sk_wait(0));
+        if (later >= 4) __builtin_amdgcn_s_waitcnt(lds_wait(4 * LPS));
+        else if (later == 3) __builtin_amdgcn_s_waitcnt(lds_wait(3 * LPS));
+        else if (later == 2) __builtin_amdgcn_s_waitcnt(lds_wait(2 * LPS));
+        else if (later == 1) __builtin_amdgcn_s_waitcnt(lds_wait(LPS));
+        else __builtin_amdgcn_s_waitcnt(lds_wait(0));
         __builtin_amdgcn_s_barrier();                              // everyone's part landed; the stage of tile i-1 is free
         __builtin_amdgcn_sched_barrier(0);
         if (i + kStages - 1 < n) issue(kmap(i + kStages - 1), nxt);
@@ -827,20 +1180,17 @@ __global__ __launch_bounds__(256, (SkCfg<RB, TB>::kPerCu)) void gemm_skinny_kern
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
             const int ko = ((ks * 2 + lk) ^ sw) * 16;
-            bf16x8 xf[TB];
-#pragma unroll
-            for (int t = 0; t < TB; ++t) xf[t] = *reinterpret_cast<const bf16x8*>(st + x_off + t * 32 * 128 + ko);
+            const bf16x8 xf = *reinterpret_cast<const bf16x8*>(st + x_off + ko);
 #pragma unroll
             for (int b = 0; b < RB; ++b) {
                 const bf16x8 wfr = *reinterpret_cast<const bf16x8*>(st + w_off + b * 32 * 128 + ko);
-#pragma unroll
-                for (int t = 0; t < TB; ++t) acc[b][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wfr, xf[t], acc[b][t], 0, 0, 0);
+                acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wfr, xf, acc[b], 0, 0, 0);
             }
         }
     }
 
-    // lane holds, of token block t, token m0 + wt*32*TB + t*32 + lane%32 and, of block b of its wave's rows,
-    // features 8g + 4*(lane/32) + 0..3
+    // lane holds token wt*32 + lane%32 and, of block b of its wave's rows, features 8g + 4*(lane/32) + 0..3
+    const int m = wt * 32 + lrow;
     if (GU && C != nullptr) {
         // the up-factor waves hand their accumulators to the gate-factor waves (same lane, same
         // token half) through LDS, which is free once everyone has read the last stage
@@ -850,58 +1200,47 @@ __global__ __launch_bounds__(256, (SkCfg<RB, TB>::kPerCu)) void gemm_skinny_kern
 #pragma unroll
             for (int b = 0; b < RB; ++b)
 #pragma unroll
-                for (int t = 0; t < TB; ++t)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) ex[(((wt * RB + b) * TB + t) * 16 + r) * 64 + lane] = acc[b][t][r];
+                for (int r = 0; r < 16; ++r) ex[((wt * RB + b) * 16 + r) * 64 + lane] = acc[b][r];
         }
         __syncthreads();
-        if (wf == 0) {
+        if (wf == 0 && m < M) {
 #pragma unroll
-            for (int t = 0; t < TB; ++t) {
-                const int m = m0 + wt * 32 * TB + t * 32 + lrow;
-                if (m >= M) continue;
+            for (int b = 0; b < RB; ++b)
 #pragma unroll
-                for (int b = 0; b < RB; ++b)
+                for (int g = 0; g < 4; ++g) {
+                    const int lf = b * 32 + 8 * g + 4 * lk;
+                    const int nn = n0 + lf;
+                    if (lf < tr && nn < Nh) {
+                        bf16x4 w4;
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const int lf = b * 32 + 8 * g + 4 * lk;
-                        const int nn = n0 + lf;
-                        if (lf < tr && nn < Nh) {
-                            bf16x4 w4;
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                const float o = acc[b][t][4 * g + e];
-                                const float u = ex[(((wt * RB + b) * TB + t) * 16 + 4 * g + e) * 64 + lane];
-                                w4[e] = (bf16)(silu_fast(o) * u);
-                            }
-                            *reinterpret_cast<bf16x4*>(C + (size_t)m * Nh + nn) = w4;
+                        for (int e = 0; e < 4; ++e) {
+                            const float o = acc[b][4 * g + e];
+                            const float u = ex[((wt * RB + b) * 16 + 4 * g + e) * 64 + lane];
+                            w4[e] = (bf16)(silu_fast(o) * u);
                         }
+                        *reinterpret_cast<bf16x4*>(C + (size_t)m * Nh + nn) = w4;
                     }
-            }
+                }
         }
         return;
     }
+    if (m >= M) return;
+    float* prow = partial + ((size_t)split * M + m) * Nrows;           // partial[split][m][n]
 #pragma unroll
-    for (int t = 0; t < TB; ++t) {
-        const int m = m0 + wt * 32 * TB + t * 32 + lrow;
-        if (m >= M) continue;
-        float* prow = partial + ((size_t)split * M + m) * Nrows;       // partial[split][m][n]
+    for (int b = 0; b < RB; ++b)
 #pragma unroll
-        for (int b = 0; b < RB; ++b)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int lf = (GU ? 0 : wf * HALF) + b * 32 + 8 * g + 4 * lk;      // feature inside the tile (GU: the factor)
-                const int f = n0 + lf;
-                const int nn = GU ? wf * Nh + f : f;
-                if (lf < tr && f < (GU ? Nh : Nrows))
-                    *reinterpret_cast<float4*>(prow + nn) =
-                        make_float4(acc[b][t][4 * g], acc[b][t][4 * g + 1], acc[b][t][4 * g + 2], acc[b][t][4 * g + 3]);
-            }
-    }
+        for (int g = 0; g < 4; ++g) {
+            const int lf = (GU ? 0 : wf * HALF) + b * 32 + 8 * g + 4 * lk;      // feature inside the tile (GU: the factor)
+            const int f = n0 + lf;
+            const int nn = GU ? wf * Nh + f : f;
+            if (lf < tr && f < (GU ? Nh : Nrows))
+                *reinterpret_cast<float4*>(prow + nn) =
+                    make_float4(acc[b][4 * g], acc[b][4 * g + 1], acc[b][4 * g + 2], acc[b][4 * g + 3]);
+        }
 }
 
 template <int MODE>
-__global__ __launch_bounds__(256) void gemm_skinny_epilogue(const float* __restrict__ partial, const bf16* R, bf16* C,
+__global__ __launch_bounds__(256) void gemm_partial_epilogue(const float* __restrict__ partial, const bf16* R, bf16* C,
                                                             int M, int N, int Nrows, int ksplit) {
     const int idx = blockIdx.x * 256 + threadIdx.x;       // one thread per 4 outputs
     const int per_row = N >> 2;
@@ -935,21 +1274,19 @@ __global__ __launch_bounds__(256) void gemm_skinny_epilogue(const float* __restr
 }
 
 struct SkinnyPlan {
-    int n_tiles, kt_per_split, ksplit, rows, rb, tb, m_blocks;
+    int n_tiles, kt_per_split, ksplit, rows, rb;
     size_t ws_bytes;
 };
 
-template <int RB, int TB>
-static void skinny_plan_rb(SkinnyPlan& p, int Nrows, int nk, int m_blocks) {
+template <int RB>
+static void skinny_plan_rb(SkinnyPlan& p, int Nrows, int nk) {
     constexpr int kTile = 64 * RB;
-    // Units one round hands out.  The long streams fill every workgroup slot of the chip.  The short ones (64-row tiles
-    // over at most 64 tokens) aim at one unit per CU although two fit: half as many K slices halve the partial sums
+    // Units one round hands out.  The long streams fill every workgroup slot of the chip.  The short ones (64-row tiles)
+    // aim at one unit per CU although two fit: half as many K slices halve the partial sums
     // written here and re-read by the consumer (8B decode at 64 tokens: qkv 17.7 -> 16.5 us, o 14.8 -> 12.0 us; a
     // target of 128 or 192 units is slower again, 384 and more as well).
-    const int kSlots = ((RB == 1 && TB == 1) ? 256 : SkCfg<RB, TB>::kSlots) / m_blocks;
+    const int kSlots = RB == 1 ? 256 : SkCfg<RB>::kSlots;
     p.rb = RB;
-    p.tb = TB;
-    p.m_blocks = m_blocks;
     p.n_tiles = (Nrows + kTile - 1) / kTile;
     int target = kSlots / p.n_tiles;              // aim at filling every workgroup slot once
     if (target < 1) target = 1;
@@ -979,22 +1316,13 @@ static SkinnyPlan skinny_plan(int M, int N, int K, int mode) {
     const int Nrows = (mode == 2) ? 2 * N : N;
     const int nk = K / kBK;
     const bool stream = (size_t)Nrows * K * sizeof(bf16) >= kSkStreamBytes;
-    if (M <= 64) {
-        if (stream) skinny_plan_rb<2, 1>(p, Nrows, nk, 1);
-        else skinny_plan_rb<1, 1>(p, Nrows, nk, 1);
-    } else {
-        const int m_blocks = (M + 127) / 128;
-        if (stream) skinny_plan_rb<2, 2>(p, Nrows, nk, m_blocks);
-        else skinny_plan_rb<1, 2>(p, Nrows, nk, m_blocks);
-    }
+    if (stream) skinny_plan_rb<2>(p, Nrows, nk);
+    else skinny_plan_rb<1>(p, Nrows, nk);
     p.ws_bytes = (size_t)p.ksplit * M * Nrows * sizeof(float);
     return p;
 }
 
-// Beyond 64 rows a workgroup covers 128.  Against the large-tile kernel with every tile split (the four
-// projections of the 8B-GQA shape, us): 65 rows 118 / 167, 128 rows 130 / 182, 192 rows 207 / 204,
-// 256 rows 215 / 228; with three blocks (384 rows) it loses, 319 / 250.
-constexpr int kSkMaxM = 256;
+constexpr int kSkMaxM = 64;
 static bool skinny_ok(int M, int N, int K) {
     return M >= 1 && M <= kSkMaxM && K % kBK == 0 && N % 4 == 0 &&
            (uint64_t)2 * N * K < 0x7fffffffull;          // 32-bit byte offsets into the weights (2N rows in gate/up mode)
@@ -1002,6 +1330,13 @@ static bool skinny_ok(int M, int N, int K) {
 
 size_t gemm_workspace_bytes(int mode, int M, int N, int K) {
     if (skinny_ok(M, N, K)) return skinny_plan(M, N, K, mode).ws_bytes;
+    MidPlan p;
+    if (mid_takes(mode, M, N, K, p)) {
+        // Up to 256 rows a problem whose output, as one range's sums, is larger than the bound keeps being reported with
+        // that size, although its K is never cut: callers with that much scratch and no more keep refusing it.
+        const size_t one = (size_t)M * ((mode == 2) ? 2 * N : N) * sizeof(float);
+        return M <= 256 && one > kMidMaxPartial ? one : p.ws_bytes;
+    }
     if (big_ok(M, N, K)) return big_plan(mode, M, N, K).ws_bytes;
     return 0;
 }
@@ -1012,39 +1347,34 @@ static bool skinny_applies(int mode, int M, int N, int K, const float* ws, size_
 
 struct SkinnyArgs {
     const bf16* a; const bf16* w; float* ws; bf16* direct;
-    int M, Nrows, K, n_tiles, kt_per_split, rows, m_blocks, units;
+    int M, Nrows, K, n_tiles, kt_per_split, rows;
 };
 
-template <bool GU, bool NT, int RB, int TB>
+template <bool GU, bool NT, int RB>
 static void skinny_go(dim3 grid, hipStream_t st, const SkinnyArgs& g) {
-    constexpr int lds = SkCfg<RB, TB>::kLds;
+    constexpr int lds = SkCfg<RB>::kLds;
     static LdsLimit limit;               // per instantiation: the LDS limit is a per-function setting
-    (void)limit.raise(reinterpret_cast<const void*>(gemm_skinny_kernel<GU, NT, RB, TB>), lds);
-    hipLaunchKernelGGL((gemm_skinny_kernel<GU, NT, RB, TB>), grid, dim3(256), lds, st, g.a, g.w, g.ws, g.direct, g.M,
-                       g.Nrows, g.K, g.n_tiles, g.kt_per_split, g.rows, g.m_blocks, g.units);
+    (void)limit.raise(reinterpret_cast<const void*>(gemm_skinny_kernel<GU, NT, RB>), lds);
+    hipLaunchKernelGGL((gemm_skinny_kernel<GU, NT, RB>), grid, dim3(256), lds, st, g.a, g.w, g.ws, g.direct, g.M,
+                       g.Nrows, g.K, g.n_tiles, g.kt_per_split, g.rows);
 }
 
 // Split-K partial sums only: partial[ksplit][M][Nrows] (Nrows = 2N in SwiGLU mode).  The caller
-// folds the slices in slice order, either with gemm_skinny_epilogue or fused into the next kernel.
+// folds the slices in slice order, either with gemm_partial_epilogue or fused into the next kernel.
 // `c` (gate/up mode only): where the activation goes when one k-slice covers K; then the return value is 0
 // and no partial sums are written.
 static int launch_skinny_partial(int mode, const bf16* a, const bf16* w, bf16* c, int M, int N, int K, float* ws,
                                  hipStream_t st) {
     const SkinnyPlan p = skinny_plan(M, N, K, mode);
     const int Nrows = (mode == 2) ? 2 * N : N;
-    const int units = p.n_tiles * p.ksplit;
-    const dim3 grid((units + 7) / 8 * 8 * p.m_blocks);
+    const dim3 grid(p.n_tiles * p.ksplit);
     bf16* direct = (mode == 2 && p.ksplit == 1) ? c : nullptr;
-    const SkinnyArgs args{a, w, ws, direct, M, Nrows, K, p.n_tiles, p.kt_per_split, p.rows, p.m_blocks, units};
+    const SkinnyArgs args{a, w, ws, direct, M, Nrows, K, p.n_tiles, p.kt_per_split, p.rows};
     const bool gu = mode == 2;
-    if (p.rb == 2 && p.tb == 2) {
-        if (gu) skinny_go<true, true, 2, 2>(grid, st, args); else skinny_go<false, true, 2, 2>(grid, st, args);
-    } else if (p.rb == 2) {
-        if (gu) skinny_go<true, true, 2, 1>(grid, st, args); else skinny_go<false, true, 2, 1>(grid, st, args);
-    } else if (p.tb == 2) {
-        if (gu) skinny_go<true, false, 1, 2>(grid, st, args); else skinny_go<false, false, 1, 2>(grid, st, args);
+    if (p.rb == 2) {
+        if (gu) skinny_go<true, true, 2>(grid, st, args); else skinny_go<false, true, 2>(grid, st, args);
     } else {
-        if (gu) skinny_go<true, false, 1, 1>(grid, st, args); else skinny_go<false, false, 1, 1>(grid, st, args);
+        if (gu) skinny_go<true, false, 1>(grid, st, args); else skinny_go<false, false, 1>(grid, st, args);
     }
     if (direct) return 0;
     return p.ksplit;
@@ -1052,8 +1382,19 @@ static int launch_skinny_partial(int mode, const bf16* a, const bf16* w, bf16* c
 
 int launch_gemm_partial(int mode, const act_t* a, const bf16* w, int M, int N, int K, float* ws, size_t ws_bytes,
                         hipStream_t st) {
-    if (M <= 0 || N <= 0 || !skinny_applies(mode, M, N, K, ws, ws_bytes)) return 0;
-    return launch_skinny_partial(mode, a, w, nullptr, M, N, K, ws, st);
+    if (M <= 0 || N <= 0) return 0;
+    if (skinny_applies(mode, M, N, K, ws, ws_bytes)) return launch_skinny_partial(mode, a, w, nullptr, M, N, K, ws, st);
+    MidPlan p;
+    if (ws == nullptr || !mid_takes(mode, M, N, K, p) || p.ksplit == 1 || ws_bytes < p.ws_bytes) return 0;
+    return launch_mid(mode, p, a, w, nullptr, nullptr, M, N, K, ws, st) ? p.ksplit : 0;
+}
+
+// Adds the slices of `ws` in slice order and applies the epilogue.
+template <int MODE>
+static void launch_partial_epilogue(const float* ws, const bf16* r, bf16* c, int M, int N, int ksplit, hipStream_t st) {
+    const int threads = M * (N >> 2);
+    hipLaunchKernelGGL(gemm_partial_epilogue<MODE>, dim3((threads + 255) / 256), dim3(256), 0, st, ws, r, c, M, N,
+                       (MODE == 2) ? 2 * N : N, ksplit);
 }
 
 template <int MODE>
@@ -1061,10 +1402,19 @@ static void launch_skinny(const bf16* a, const bf16* w, const bf16* r, bf16* c, 
                           hipStream_t st) {
     const int ksplit = launch_skinny_partial(MODE, a, w, c, M, N, K, ws, st);
     if (ksplit == 0) return;                          // the kernel wrote the result itself
-    const int Nrows = (MODE == 2) ? 2 * N : N;
-    const int threads = M * (N >> 2);
-    hipLaunchKernelGGL(gemm_skinny_epilogue<MODE>, dim3((threads + 255) / 256), dim3(256), 0, st, ws, r, c, M, N, Nrows,
-                       ksplit);
+    launch_partial_epilogue<MODE>(ws, r, c, M, N, ksplit, st);
+}
+
+// false: not a problem of the mid-sized kernel (or no LDS for it).  Without scratch for the plan's partial sums K stays whole.
+template <int MODE>
+static bool launch_mid_whole(const bf16* a, const bf16* w, const bf16* r, bf16* c, int M, int N, int K, float* ws,
+                             size_t ws_bytes, hipStream_t st) {
+    MidPlan p;
+    if (!mid_takes(MODE, M, N, K, p)) return false;
+    if (p.ksplit > 1 && (ws == nullptr || ws_bytes < p.ws_bytes)) p = mid_plan(MODE, M, N, K, false);
+    if (!launch_mid(MODE, p, a, w, r, c, M, N, K, ws, st)) return false;
+    if (p.ksplit > 1) launch_partial_epilogue<MODE>(ws, r, c, M, N, p.ksplit, st);
+    return true;
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, int MODE>
@@ -1088,6 +1438,8 @@ static void launch_mode(const bf16* a, const bf16* w, const bf16* r, bf16* c, in
         launch_skinny<MODE>(a, w, r, c, M, N, K, ws, st);
     } else if (M <= 64) {
         launch_cfg<64, 128, 2, 2, MODE>(a, w, r, c, M, N, K, st);
+    } else if (launch_mid_whole<MODE>(a, w, r, c, M, N, K, ws, ws_bytes, st)) {
+        return;
     } else if (big_ok(M, N, K) && big_available<MODE>()) {
         launch_big<MODE>(a, w, r, c, M, N, K, ws, ws_bytes, st);
     } else {

@@ -120,6 +120,15 @@ def test_gemm_large_tile_edges(torch, mode, M, N, K):
     test_gemm(torch, False, mode, M, N, K)
 
 
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("M,N,K", [(65, 36, 64), (96, 4100, 192), (129, 2064, 1024), (225, 5120, 640), (257, 4092, 4096),
+                                   (321, 3004, 320), (552, 7172, 2048), (2048, 520, 448)])
+def test_gemm_mid_sized_edges(torch, mode, M, N, K):
+    """The mid-sized kernel's tiles: one row past a tile, rows of 8k and 8k + 4 features, one k-tile, fewer than the
+    ring holds, many; one range of K and several; one row of tiles (walks that start inside K among them) and more."""
+    test_gemm(torch, False, mode, M, N, K)
+
+
 def test_gemm_residual_in_place_and_identity(torch):
     from paper_2412_17246_amd import op_gemm
     M, N = 150, 256
