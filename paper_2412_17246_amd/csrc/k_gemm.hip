@@ -1074,7 +1074,10 @@ constexpr size_t kSkStreamBytes = (size_t)64 << 20;
 // features (rows N + n0..), so that with a single k-slice the workgroup holds both factors of
 // silu(gate) * up and writes the activation itself (C != nullptr) instead of partial sums.
 // NT: the weight loads carry the non-temporal cache policy.
-template <bool GU, bool NT, int RB>
+// TAIL: K is a multiple of 8 and not of 64.  The last k-tile's pieces past the end re-read the row's last piece and count as
+// zero, both operands, when they are multiplied.  (Such shapes went to the 64x128 kernel before, with a workgroup per 128
+// weight rows and K uncut: 688 -> 256 at one row 10.0 -> 4.8 us.)
+template <bool GU, bool NT, int RB, bool TAIL>
 __global__ __launch_bounds__(256, SkCfg<RB>::kPerCu) void gemm_skinny_kernel(const bf16* __restrict__ X,
                                                                              const bf16* __restrict__ W,
                                                                              float* __restrict__ partial,
@@ -1091,7 +1094,7 @@ __global__ __launch_bounds__(256, SkCfg<RB>::kPerCu) void gemm_skinny_kernel(con
     const int tr = GU ? rows >> 1 : rows;             // real rows per factor (GU) or per tile
     const int n0 = tile_n * tr;
     const int Nh = Nrows >> 1;                        // GU: features per factor
-    const int nk = K / kBK;
+    const int nk = (K + kBK - 1) / kBK;
     const int kt0 = split * kt_per_split;
     const int kt1 = (kt0 + kt_per_split < nk) ? kt0 + kt_per_split : nk;
     const int n = kt1 - kt0;
@@ -1131,13 +1134,20 @@ __global__ __launch_bounds__(256, SkCfg<RB>::kPerCu) void gemm_skinny_kernel(con
         const char* xk = reinterpret_cast<const char*>(X + (size_t)kt * kBK);
         const char* wk = reinterpret_cast<const char*>(W + (size_t)kt * kBK);
         unsigned char* sb = smem_raw + stage * kStage;
+        const int left = TAIL ? K - kt * kBK : kBK;      // columns the tile has; a multiple of 8
+        // bytes by which a lane's piece of LDS row `row` lies behind the row's last one
+        auto back = [&](int row) {
+            const int c = ((lane & 7) ^ swz(row)) * 8;
+            return TAIL && c >= left ? (uint32_t)(c - (left - 8)) * 2u : 0u;
+        };
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-            __builtin_amdgcn_global_load_lds((gptr_t)(xk + x_src[j]), (lptr_t)(sb + (wave_u * 2 + j) * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((gptr_t)(xk + x_src[j] - back((wave * 2 + j) * 8 + (lane >> 3))),
+                                             (lptr_t)(sb + (wave_u * 2 + j) * 1024), 16, 0, 0);
 #pragma unroll
         for (int j = 0; j < 2 * RB; ++j)
-            __builtin_amdgcn_global_load_lds((gptr_t)(wk + w_src[j]), (lptr_t)(sb + kXBytes + (wave_u * 2 * RB + j) * 1024),
-                                             16, 0, NT ? 2 : 0);
+            __builtin_amdgcn_global_load_lds((gptr_t)(wk + w_src[j] - back((wave * 2 * RB + j) * 8 + (lane >> 3))),
+                                             (lptr_t)(sb + kXBytes + (wave_u * 2 * RB + j) * 1024), 16, 0, NT ? 2 : 0);
     };
 
     f32x16 acc[RB];
@@ -1180,10 +1190,13 @@ __global__ __launch_bounds__(256, SkCfg<RB>::kPerCu) void gemm_skinny_kernel(con
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
             const int ko = ((ks * 2 + lk) ^ sw) * 16;
-            const bf16x8 xf = *reinterpret_cast<const bf16x8*>(st + x_off + ko);
+            bf16x8 xf = *reinterpret_cast<const bf16x8*>(st + x_off + ko);
+            const bool past = TAIL && kmap(i) * kBK + (ks * 2 + lk) * 8 >= K;
+            if (past) xf = bf16x8{};
 #pragma unroll
             for (int b = 0; b < RB; ++b) {
-                const bf16x8 wfr = *reinterpret_cast<const bf16x8*>(st + w_off + b * 32 * 128 + ko);
+                bf16x8 wfr = *reinterpret_cast<const bf16x8*>(st + w_off + b * 32 * 128 + ko);
+                if (past) wfr = bf16x8{};
                 acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wfr, xf, acc[b], 0, 0, 0);
             }
         }
@@ -1314,7 +1327,7 @@ static void skinny_plan_rb(SkinnyPlan& p, int Nrows, int nk) {
 static SkinnyPlan skinny_plan(int M, int N, int K, int mode) {
     SkinnyPlan p;
     const int Nrows = (mode == 2) ? 2 * N : N;
-    const int nk = K / kBK;
+    const int nk = (K + kBK - 1) / kBK;
     const bool stream = (size_t)Nrows * K * sizeof(bf16) >= kSkStreamBytes;
     if (stream) skinny_plan_rb<2>(p, Nrows, nk);
     else skinny_plan_rb<1>(p, Nrows, nk);
@@ -1324,7 +1337,9 @@ static SkinnyPlan skinny_plan(int M, int N, int K, int mode) {
 
 constexpr int kSkMaxM = 64;
 static bool skinny_ok(int M, int N, int K) {
-    return M >= 1 && M <= kSkMaxM && K % kBK == 0 && N % 4 == 0 &&
+    return M >= 1 && M <= kSkMaxM && K % 8 == 0 && N % 4 == 0 &&
+           // problems with a K tail needed no scratch before: none whose sums exceed what callers can hold is taken
+           (K % kBK == 0 || (uint64_t)M * 2 * N * sizeof(float) <= kMidMaxPartial) &&
            (uint64_t)2 * N * K < 0x7fffffffull;          // 32-bit byte offsets into the weights (2N rows in gate/up mode)
 }
 
@@ -1350,13 +1365,19 @@ struct SkinnyArgs {
     int M, Nrows, K, n_tiles, kt_per_split, rows;
 };
 
-template <bool GU, bool NT, int RB>
-static void skinny_go(dim3 grid, hipStream_t st, const SkinnyArgs& g) {
+template <bool GU, bool NT, int RB, bool TAIL>
+static void skinny_launch(dim3 grid, hipStream_t st, const SkinnyArgs& g) {
     constexpr int lds = SkCfg<RB>::kLds;
     static LdsLimit limit;               // per instantiation: the LDS limit is a per-function setting
-    (void)limit.raise(reinterpret_cast<const void*>(gemm_skinny_kernel<GU, NT, RB>), lds);
-    hipLaunchKernelGGL((gemm_skinny_kernel<GU, NT, RB>), grid, dim3(256), lds, st, g.a, g.w, g.ws, g.direct, g.M,
+    (void)limit.raise(reinterpret_cast<const void*>(gemm_skinny_kernel<GU, NT, RB, TAIL>), lds);
+    hipLaunchKernelGGL((gemm_skinny_kernel<GU, NT, RB, TAIL>), grid, dim3(256), lds, st, g.a, g.w, g.ws, g.direct, g.M,
                        g.Nrows, g.K, g.n_tiles, g.kt_per_split, g.rows);
+}
+
+template <bool GU, bool NT, int RB>
+static void skinny_go(dim3 grid, hipStream_t st, const SkinnyArgs& g) {
+    if (g.K % kBK) skinny_launch<GU, NT, RB, true>(grid, st, g);
+    else skinny_launch<GU, NT, RB, false>(grid, st, g);
 }
 
 // Split-K partial sums only: partial[ksplit][M][Nrows] (Nrows = 2N in SwiGLU mode).  The caller
