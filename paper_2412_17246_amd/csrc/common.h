@@ -13,6 +13,7 @@ namespace bz {
 typedef __bf16 bf16;
 typedef bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -96,6 +97,29 @@ __device__ __forceinline__ float to_f32(float v) { return v; }
 __device__ __forceinline__ void from_f32(bf16& o, float v) { o = (bf16)v; }
 __device__ __forceinline__ void from_f32(float& o, float v) { o = v; }
 
+// sum over split-K slices, in slice order, of 8 consecutive partial sums of row m.  Loads go out four
+// slices at a time (a slice index past the end re-reads the last slice; its value is not added).
+__device__ __forceinline__ void reduce8(const float* __restrict__ partial, int ksplit, size_t slice_stride,
+                                        size_t off, float (&s)[8]) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s[e] = 0.f;
+    for (int k0 = 0; k0 < ksplit; k0 += 4) {
+        float4 a[4], b[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int k = (k0 + u < ksplit) ? k0 + u : ksplit - 1;
+            a[u] = *reinterpret_cast<const float4*>(partial + k * slice_stride + off);
+            b[u] = *reinterpret_cast<const float4*>(partial + k * slice_stride + off + 4);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (k0 + u < ksplit) {
+                s[0] += a[u].x; s[1] += a[u].y; s[2] += a[u].z; s[3] += a[u].w;
+                s[4] += b[u].x; s[5] += b[u].y; s[6] += b[u].z; s[7] += b[u].w;
+            }
+    }
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
@@ -160,6 +184,15 @@ struct BatchView {
     int n_decode_work;
 };
 
+// The QKV projection of a batch, rows of (Hq + 2 Hkv) * d values: query, key and value heads.  Either the projection's
+// output (`partial` null) or its split-K partial sums partial[ksplit][T][row], which the reader adds in slice order and
+// rounds to the activation type, as the GEMM's own epilogue would have.
+struct QkvSource {
+    act_t* qkv;
+    const float* partial;
+    int ksplit;
+};
+
 constexpr int kPrefillTileQ = 128;   // query rows per prefill-attention workgroup
 constexpr int kDecodeChunk = 256;    // KV positions per decode-attention workgroup
 
@@ -179,15 +212,18 @@ int launch_gemm_partial(int mode, const act_t* a, const bf16* w, int M, int N, i
 // stored; then, unless gain is null, y = rmsnorm(x) * gain exactly as launch_rmsnorm would compute it.
 void launch_reduce_residual_rmsnorm(act_t* x, const float* partial, int ksplit, const bf16* gain, act_t* y, int T,
                                     int H, float eps, hipStream_t st);
-// launch_rope_append on a projection output that is still in split-K partial form
-void launch_rope_append_reduce(act_t* qkv, const float* partial, int ksplit, const float* rope_tab,
-                               const BatchView& bv, const KvView& kv, int Hq, hipStream_t st);
-void launch_rope_append(act_t* qkv, const float* rope_tab, const BatchView& bv, const KvView& kv, int Hq,
-                        hipStream_t st);
-void launch_attn_prefill(const act_t* qkv, act_t* out, const BatchView& bv, const KvView& kv, int Hq,
-                         hipStream_t st);
-void launch_attn_decode(const act_t* qkv, act_t* out, float* partial, const BatchView& bv, const KvView& kv,
-                        int Hq, hipStream_t st_);
+// Rotary embedding (table `rope_tab`: [max_seq_len][d/2] pairs of cos, sin) and the append to the cache are shared out so
+// that the projection is read once and the rotated queries never travel through memory: launch_kv_append takes the keys
+// and values of the sequences with several new tokens, the prefill kernel rotates its queries as it loads them, and the
+// decode kernel does both for its one token per sequence.  (fp32 debug build: launch_kv_append does it all.)
+// launch_kv_append comes first.
+bool kv_append_needed(const BatchView& bv);
+void launch_kv_append(const QkvSource& src, const float* rope_tab, const BatchView& bv, const KvView& kv, int Hq,
+                      hipStream_t st);
+void launch_attn_prefill(const QkvSource& src, const float* rope_tab, act_t* out, const BatchView& bv, const KvView& kv,
+                         int Hq, hipStream_t st);
+void launch_attn_decode(const QkvSource& src, const float* rope_tab, act_t* out, float* partial, const BatchView& bv,
+                        const KvView& kv, int Hq, hipStream_t st);
 void launch_kv_scatter(const act_t* src_k, const act_t* src_v, const KvView& kv, int slot, int pos0, int n,
                        bool to_cache, act_t* dst_k, act_t* dst_v, hipStream_t st);
 // kv_before[s] += 1 for every sequence, then the decode work list is rebuilt for the new lengths

@@ -1069,7 +1069,7 @@ int bz_run_layers(bz_instance* I, int a, int b, const bz_batch* batch, void* hid
         const KvView kvv = kv_view(I, l);
         const int nqkv = sh.nqkv(), qd = sh.Hq * sh.d;
         // Decode-sized batches: the projections leave split-K partial sums in `gws` and the kernel that
-        // consumes the projection folds them (QKV -> rotary/append; O and down -> residual + next norm).
+        // consumes the projection folds them (QKV -> cache append and attention; O and down -> residual + next norm).
         // The stored values are the same bits the unfused kernels produce.
         { ProfScope p(I, BZ_K_RMSNORM, 4.0 * T * sh.H, 2.0 * T * sh.H * e);
           if (pending_down > 0) launch_reduce_residual_rmsnorm(x, gws, pending_down, g1, normed, T, sh.H, I->cfg.rms_eps, st);
@@ -1079,16 +1079,18 @@ int bz_run_layers(bz_instance* I, int a, int b, const bz_batch* batch, void* hid
         { ProfScope p(I, BZ_K_GEMM_QKV, 2.0 * T * nqkv * sh.H, ((double)T * sh.H + (double)T * nqkv) * e + 2.0 * nqkv * sh.H);
           ks_qkv = launch_gemm_partial(0, normed, wqkv, T, nqkv, sh.H, gws, gwsb, st);
           if (ks_qkv == 0) launch_gemm(0, normed, wqkv, nullptr, qkv, T, nqkv, sh.H, gws, gwsb, st); }
-        { ProfScope p(I, BZ_K_ROPE_APPEND, 3.0 * T * (sh.Hq + sh.Hkv) * sh.d, (double)T * (2.0 * sh.Hq + 4.0 * sh.Hkv) * sh.d * e);
-          if (ks_qkv > 0) launch_rope_append_reduce(qkv, gws, ks_qkv, rope, bv, kvv, sh.Hq, st);
-          else launch_rope_append(qkv, rope, bv, kvv, sh.Hq, st); }
+        const QkvSource projected{qkv, ks_qkv > 0 ? gws : nullptr, ks_qkv};
+        if (kv_append_needed(bv)) {
+            ProfScope p(I, BZ_K_ROPE_APPEND, 3.0 * T * sh.Hkv * sh.d, (double)T * 4.0 * sh.Hkv * sh.d * e);
+            launch_kv_append(projected, rope, bv, kvv, sh.Hq, st);
+        }
         if (bv.n_prefill_items > 0) {
             ProfScope p(I, BZ_K_ATTN_PREFILL, 4.0 * sh.Hq * sh.d * batch->prefill_sq, 0.0);
-            launch_attn_prefill(qkv, attn, bv, kvv, sh.Hq, st);
+            launch_attn_prefill(projected, rope, attn, bv, kvv, sh.Hq, st);
         }
         if (bv.n_decode > 0) {
             ProfScope p(I, BZ_K_ATTN_DECODE, 4.0 * sh.Hq * sh.d * decode_kv, decode_kv * 2.0 * sh.Hkv * sh.d * e);
-            launch_attn_decode(qkv, attn, partial, bv, kvv, sh.Hq, st);
+            launch_attn_decode(projected, rope, attn, partial, bv, kvv, sh.Hq, st);
         }
         int ks_o = 0;
         if (by_part) {

@@ -41,9 +41,43 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // cache in exactly the order the MFMAs read it, so a tile is moved global -> LDS by the DMA path
 // (no registers), double-buffered: tile i+1 is in flight while tile i is multiplied.
 // ---------------------------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(256, 2) void attn_prefill_kernel(const bf16* __restrict__ qkv, bf16* __restrict__ out,
-                                                              BatchView bv, KvView kv, int Hq, float scale_log2) {
+// A lane's query fragments qf[ks] hold dims 16 ks + 8 lh + 0..7 of one row, so both halves of a rotation pair (j, j + D/2)
+// are in the same lane: the query is rotated as it is loaded.
+template <int D, bool REDUCE>
+__device__ __forceinline__ void load_rotated_query(const QkvSource& src, size_t at, size_t slice, const float* cs,
+                                                   bf16x8 (&qf)[D / 16], int lh) {
+    constexpr int H = D / 32;                                 // fragments per half of the head
+#pragma unroll
+    for (int ks = 0; ks < H; ++ks) {
+        const int j = ks * 16 + lh * 8;
+        float lo[8], hi[8];
+        if (REDUCE) {
+            reduce8(src.partial, src.ksplit, slice, at + j, lo);
+            reduce8(src.partial, src.ksplit, slice, at + D / 2 + j, hi);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                lo[e] = (float)(bf16)lo[e];
+                hi[e] = (float)(bf16)hi[e];
+            }
+        } else {
+            load8(src.qkv + at + j, lo);
+            load8(src.qkv + at + D / 2 + j, hi);
+        }
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+            const float4 v = *reinterpret_cast<const float4*>(cs + 2 * (j + e));
+            qf[ks][e] = (bf16)(lo[e] * v.x - hi[e] * v.y);
+            qf[ks + H][e] = (bf16)(hi[e] * v.x + lo[e] * v.y);
+            qf[ks][e + 1] = (bf16)(lo[e + 1] * v.z - hi[e + 1] * v.w);
+            qf[ks + H][e + 1] = (bf16)(hi[e + 1] * v.z + lo[e + 1] * v.w);
+        }
+    }
+}
+
+template <int D, bool REDUCE>
+__global__ __launch_bounds__(256, 2) void attn_prefill_kernel(QkvSource qkv, const float* __restrict__ tab,
+                                                              bf16* __restrict__ out, BatchView bv, KvView kv, int Hq,
+                                                              float scale_log2) {
     constexpr int BQ = kPrefillTileQ, BK = 64;
     constexpr int DB = D / 32;           // 32-wide blocks of the head dim
     constexpr int KS = D / 16;           // MFMA k-steps over the head dim
@@ -132,11 +166,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(const bf16* __rest
     issue(0, 0);
 
     bf16x8 qf[KS];
-    {
-        const bf16* qp = qkv + (size_t)(q0 + qic) * nqkv + h * D + lh * 8;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
-    }
+    load_rotated_query<D, REDUCE>(qkv, (size_t)(q0 + qic) * nqkv + h * D, (size_t)bv.T * nqkv, tab + (size_t)qpos * D, qf, lh);
 
     f32x16 o[DB];
 #pragma unroll
@@ -258,22 +288,23 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(const bf16* __rest
     }
 }
 
-template <int D>
-static void launch_prefill_d(const act_t* qkv, act_t* out, const BatchView& bv, const KvView& kv, int Hq,
-                             hipStream_t st) {
+template <int D, bool REDUCE>
+static void launch_prefill_d(const QkvSource& qkv, const float* rope_tab, act_t* out, const BatchView& bv, const KvView& kv,
+                             int Hq, hipStream_t st) {
     constexpr int kLds = 2 * 4 * 32 * D * (int)sizeof(bf16);     // two stages of (K tile + V tile)
     static LdsLimit limit;
-    (void)limit.raise(reinterpret_cast<const void*>(attn_prefill_kernel<D>), kLds);
+    (void)limit.raise(reinterpret_cast<const void*>(attn_prefill_kernel<D, REDUCE>), kLds);
     const float scale_log2 = kLog2e / sqrtf((float)D);
-    hipLaunchKernelGGL(attn_prefill_kernel<D>, dim3(bv.n_prefill_items * Hq), dim3(256), kLds, st, qkv, out, bv, kv, Hq,
-                       scale_log2);
+    hipLaunchKernelGGL((attn_prefill_kernel<D, REDUCE>), dim3(bv.n_prefill_items * Hq), dim3(256), kLds, st, qkv, rope_tab,
+                       out, bv, kv, Hq, scale_log2);
 }
 
-void launch_attn_prefill(const act_t* qkv, act_t* out, const BatchView& bv, const KvView& kv, int Hq,
-                         hipStream_t st) {
+void launch_attn_prefill(const QkvSource& qkv, const float* rope_tab, act_t* out, const BatchView& bv, const KvView& kv,
+                         int Hq, hipStream_t st) {
     if (bv.n_prefill_items <= 0) return;
-    if (kv.d == 128) launch_prefill_d<128>(qkv, out, bv, kv, Hq, st);
-    else launch_prefill_d<64>(qkv, out, bv, kv, Hq, st);
+    const bool sums = qkv.partial != nullptr;
+    if (kv.d == 128) (sums ? launch_prefill_d<128, true> : launch_prefill_d<128, false>)(qkv, rope_tab, out, bv, kv, Hq, st);
+    else (sums ? launch_prefill_d<64, true> : launch_prefill_d<64, false>)(qkv, rope_tab, out, bv, kv, Hq, st);
 }
 
 #else  // BZ_FP32_DEBUG
@@ -320,14 +351,14 @@ __global__ __launch_bounds__(64) void attn_naive_kernel(const float* __restrict_
     }
 }
 
-void launch_attn_prefill(const act_t* qkv, act_t* out, const BatchView& bv, const KvView& kv, int Hq,
+void launch_attn_prefill(const QkvSource& qkv, const float*, act_t* out, const BatchView& bv, const KvView& kv, int Hq,
                          hipStream_t st) {
     if (bv.n_prefill_items <= 0) return;
     const float scale_log2 = kLog2e / sqrtf((float)kv.d);
     // 64 KiB of LDS holds 16384 scores: enough for every supported max_seq_len in the debug build
     static LdsLimit limit;
     (void)limit.raise(reinterpret_cast<const void*>(attn_naive_kernel), 65536);
-    hipLaunchKernelGGL(attn_naive_kernel, dim3(bv.T, Hq), dim3(64), 65536, st, qkv, out, bv, kv, Hq, scale_log2);
+    hipLaunchKernelGGL(attn_naive_kernel, dim3(bv.T, Hq), dim3(64), 65536, st, qkv.qkv, out, bv, kv, Hq, scale_log2);
 }
 #endif
 
@@ -347,14 +378,25 @@ constexpr int kDecodeMaxG = 8;
 //   S^T[pos, g] = K[pos, :] . q[g, :]     q fills G of the 32 columns, the rest are zero;
 //   O^T[j, g]   = V^T[j, pos] . P^T[pos, g]   P^T goes from the score accumulators to the column
 //   operand inside the registers (the V cache is stored in the matching position order).
-template <int D>
-__global__ __launch_bounds__(256, 2) void attn_decode_kernel(const bf16* __restrict__ qkv, float* __restrict__ partial,
+//
+// The new token's rotation and its append to the cache happen here too, in the shadow of the stream: the projection's
+// values are requested before the workgroup's K and V, four pairs per thread, and go through LDS to the waves.  The
+// workgroup whose chunk holds the new position rotates and appends K and V and adds the position as a fifth partial
+// result (score from a plain dot product, probability 1 against its own maximum); everywhere else only cached positions
+// count.  A launch of its own for these few bytes per sequence cost 5 to 7.5 us of a 105 to 370 us decode layer.
+// A sequence with a single chunk gets its output here; the combine kernel leaves it alone.
+template <int D, bool REDUCE>
+__global__ __launch_bounds__(256, 2) void attn_decode_kernel(QkvSource src, const float* __restrict__ tab,
+                                                             float* __restrict__ partial, bf16* __restrict__ out,
                                                              BatchView bv, KvView kv, int Hq, int G, float scale_log2) {
     constexpr int CH = kDecodeChunk;
     constexpr int KS = D / 16, DB = D / 32, BLK = 32 * D;
     __shared__ float wmx[4][kDecodeMaxG];
     __shared__ float wsum[4][kDecodeMaxG];
     __shared__ float osh[4][kDecodeMaxG][D];
+    __shared__ __attribute__((aligned(16))) bf16 qs[kDecodeMaxG][D];       // rotated queries
+    __shared__ __attribute__((aligned(16))) bf16 kn[D], vn[D];             // the new position's key and value
+    __shared__ float sn[kDecodeMaxG];                                      // its scores
 
     // the work list names only chunks that exist, and brings the sequence's slot along: everything else
     // hangs off one more level of loads (see BatchView for the order of workgroups)
@@ -363,80 +405,176 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(const bf16* __restr
     const int s = item.x, slot = item.y, di = item.z;
     const int rest = blockIdx.x - kv.Hkv * item2.x;          // position among this sequence's (kv head, chunk) pairs
     const int kvh = rest / item.w, chunk = rest - kvh * item.w;
-    const int len = bv.kv_before[s] + 1;
+    const int pos = bv.kv_before[s];                         // the new token's position = number of cached ones
     const int c0 = chunk * CH;
-    if (c0 >= len) return;
+    if (c0 > pos) return;
+    const bool newest = pos - c0 < CH;                       // this chunk holds the new position
     const int t = bv.q_start[s];
     const int Hkv = kv.Hkv, cap = kv.slot_cap[slot];
     const size_t head_base = (size_t)kv.slot_off[slot] * Hkv * D + (size_t)kvh * cap * D;
-    const bf16* Kc = kv.k + head_base;
-    const bf16* Vc = kv.v + head_base;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    bf16* Kc = kv.k + head_base;
+    bf16* Vc = kv.v + head_base;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lq = lane & 31, lh = lane >> 5;
-    const bf16* q = qkv + (size_t)t * (Hq + 2 * Hkv) * D + (size_t)kvh * G * D;    // G query heads, contiguous
+
+    // unit = 4 pairs (j, j + D/2) of one of the G query heads or (newest) of the key, or 4 values (newest); threads past
+    // the last unit repeat it and store nothing but the same LDS values
+    constexpr int UPH = D / 8;
+    const int n_rot = (newest ? G + 1 : G) * UPH, n_units = newest ? n_rot + D / 4 : n_rot;
+    const int unit = tid < n_units ? tid : n_units - 1;
+    const bool is_v = unit >= n_rot;
+    const int hh = is_v ? 0 : unit / UPH;
+    const int j0 = (is_v ? unit - n_rot : unit - hh * UPH) * 4;
+    const int nqkv = (Hq + 2 * Hkv) * D;
+    const size_t slice = (size_t)bv.T * nqkv;
+    const size_t at = (size_t)t * nqkv + (is_v ? Hq + Hkv + kvh : hh < G ? kvh * G + hh : Hq + kvh) * D + j0;
+    const int second = is_v ? 0 : D / 2;
+    const float* cs = tab + (size_t)pos * D + (is_v ? 0 : j0 * 2);
+    f32x4 pa[4], pb[4];                                      // REDUCE: up to four slices; else only the first, raw
+    bf16x4 ra, rb;
+    if (REDUCE) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float* p = src.partial + (k < src.ksplit ? k : src.ksplit - 1) * slice + at;
+            pa[k] = *reinterpret_cast<const f32x4*>(p);
+            pb[k] = *reinterpret_cast<const f32x4*>(p + second);
+        }
+    } else {
+        ra = *reinterpret_cast<const bf16x4*>(src.qkv + at);
+        rb = *reinterpret_cast<const bf16x4*>(src.qkv + at + second);
+    }
+    const f32x4 cs0 = *reinterpret_cast<const f32x4*>(cs), cs1 = *reinterpret_cast<const f32x4*>(cs + 4);
+    __builtin_amdgcn_sched_barrier(0);                       // these go out before the stream
 
     const int w0 = c0 + wave * 64;
-    if (w0 < len) {                                          // wave-uniform
-        const int last_blk = (len - 1) >> 5;
-        // a block past the end is replaced by the last valid one (loads stay unconditional and in
-        // bounds); its positions get probability zero
-        size_t boff[2];
+    const bool live = w0 < pos;                              // something cached in this wave's range; wave-uniform
+    // The loads stand outside any branch, or the wait for the projection's values would have to assume that they were not
+    // issued and drain them.  A block past the end is replaced by the last valid one (its positions get probability zero);
+    // a wave without cached positions reads one line per load, of block 0.
+    const int last_blk = live ? (pos - 1) >> 5 : 0;
+    const int lane_k = live ? (lh * 32 + lq) * 8 : 0, lane_v = live ? (lh * D + lq) * 8 : 0;
+    size_t boff[2];
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb) {
-            int kb = (w0 >> 5) + rb;
-            if (kb > last_blk) kb = last_blk;
-            boff[rb] = (size_t)kb * BLK;
+    for (int b = 0; b < 2; ++b) {
+        int kb = (w0 >> 5) + b;
+        if (kb > last_blk) kb = last_blk;
+        boff[b] = (size_t)kb * BLK;
+    }
+    bf16x8 kf[2][KS], vf[2][2][DB];
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            kf[b][ks] = stream_load(reinterpret_cast<const bf16x8*>(Kc + boff[b] + lane_k + ks * 512));
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+                vf[b][tt][db] = stream_load(reinterpret_cast<const bf16x8*>(Vc + boff[b] + lane_v + (2 * tt * D + db * 32) * 8));
+    __builtin_amdgcn_sched_barrier(0);
+    {
+        f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
+        if (REDUCE) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (k < src.ksplit) {
+                    a += pa[k];
+                    b += pb[k];
+                }
+            for (int k = 4; k < src.ksplit; ++k) {
+                a += *reinterpret_cast<const f32x4*>(src.partial + k * slice + at);
+                b += *reinterpret_cast<const f32x4*>(src.partial + k * slice + at + second);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                a[i] = (float)(bf16)a[i];
+                b[i] = (float)(bf16)b[i];
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                a[i] = (float)ra[i];
+                b[i] = (float)rb[i];
+            }
         }
-        bf16x8 kf[2][KS], vf[2][2][DB];
+        if (is_v) {
+            bf16x4 v;
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb)
+            for (int i = 0; i < 4; ++i) v[i] = (bf16)a[i];
+            *reinterpret_cast<bf16x4*>(&vn[j0]) = v;
+            if (tid < n_units) {
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                kf[rb][ks] = stream_load(reinterpret_cast<const bf16x8*>(Kc + boff[rb] + ((ks * 2 + lh) * 32 + lq) * 8));
+                for (int i = 0; i < 4; ++i) Vc[v_elem_offset(pos, j0 + i, D)] = v[i];
+            }
+        } else {
+            bf16x4 lo, hi;
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb)
+            for (int i = 0; i < 4; ++i) {
+                const float c = i < 2 ? cs0[2 * i] : cs1[2 * i - 4], sv = i < 2 ? cs0[2 * i + 1] : cs1[2 * i - 3];
+                lo[i] = (bf16)(a[i] * c - b[i] * sv);
+                hi[i] = (bf16)(b[i] * c + a[i] * sv);
+            }
+            bf16* dst = hh < G ? qs[hh] : kn;
+            *reinterpret_cast<bf16x4*>(dst + j0) = lo;
+            *reinterpret_cast<bf16x4*>(dst + D / 2 + j0) = hi;
+            if (hh == G && tid < n_units) {
+                *reinterpret_cast<bf16x4*>(Kc + k_elem_offset(pos, j0, D)) = lo;
+                *reinterpret_cast<bf16x4*>(Kc + k_elem_offset(pos, D / 2 + j0, D)) = hi;
+            }
+        }
+    }
+    // hand-over through LDS without waiting for the stream (a full barrier would drain it)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    if (newest) {                                            // workgroup-uniform
+        for (int g = wave; g < G; g += 4) {
+            float p = 0.f;
 #pragma unroll
-            for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-                for (int db = 0; db < DB; ++db)
-                    vf[rb][tt][db] =
-                        stream_load(reinterpret_cast<const bf16x8*>(Vc + boff[rb] + ((2 * tt + lh) * D + db * 32 + lq) * 8));
+            for (int i = 0; i < D / kWave; ++i) p = fmaf((float)qs[g][lane * (D / kWave) + i], (float)kn[lane * (D / kWave) + i], p);
+            p = wave_sum(p);
+            if (lane == 0) sn[g] = p * scale_log2;
+        }
+    }
+    if (live) {
         bf16x8 qf[KS];
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            if (lq < G) qf[ks] = *reinterpret_cast<const bf16x8*>(q + lq * D + ks * 16 + lh * 8);
+            if (lq < G) qf[ks] = *reinterpret_cast<const bf16x8*>(&qs[lq][ks * 16 + lh * 8]);
             else
 #pragma unroll
-                for (int e = 0; e < 8; ++e) qf[ks][e] = (bf16)0.f;
+                for (int i = 0; i < 8; ++i) qf[ks][i] = (bf16)0.f;
         }
         f32x16 sacc[2];
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb) {
+        for (int b = 0; b < 2; ++b) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) sacc[rb][r] = 0.f;
+            for (int r = 0; r < 16; ++r) sacc[b][r] = 0.f;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
-                sacc[rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[rb][ks], qf[ks], sacc[rb], 0, 0, 0);
+                sacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[b][ks], qf[ks], sacc[b], 0, 0, 0);
         }
-        // lane (g = lane%32, h = lane/32) holds positions rb*32 + 8*(r/4) + 4h + r%4 of head g
+        // lane (g = lane%32, h = lane/32) holds positions b*32 + 8*(r/4) + 4h + r%4 of head g
         float m = -INFINITY;
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb)
+        for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int pl = rb * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
-                const float sg = (w0 + pl < len) ? sacc[rb][r] * scale_log2 : -INFINITY;
-                sacc[rb][r] = sg;
+                const int pl = b * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
+                const float sg = (w0 + pl < pos) ? sacc[b][r] * scale_log2 : -INFINITY;
+                sacc[b][r] = sg;
                 m = fmaxf(m, sg);
             }
         m = fmaxf(m, __shfl_xor(m, 32, kWave));              // finite: position w0 is valid
         float l = 0.f;
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb)
+        for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const float p = exp2f(sacc[rb][r] - m);
-                sacc[rb][r] = p;
+                const float p = exp2f(sacc[b][r] - m);
+                sacc[b][r] = p;
                 l += p;
             }
         l += __shfl_xor(l, 32, kWave);
@@ -446,15 +584,15 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(const bf16* __restr
 #pragma unroll
             for (int r = 0; r < 16; ++r) oacc[db][r] = 0.f;
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb)
+        for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int tt = 0; tt < 2; ++tt) {
                 bf16x8 pf;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) pf[e] = (bf16)sacc[rb][8 * tt + e];
+                for (int i = 0; i < 8; ++i) pf[i] = (bf16)sacc[b][8 * tt + i];
 #pragma unroll
                 for (int db = 0; db < DB; ++db)
-                    oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[rb][tt][db], pf, oacc[db], 0, 0, 0);
+                    oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[b][tt][db], pf, oacc[db], 0, 0, 0);
             }
         if (lq < G) {
 #pragma unroll
@@ -468,7 +606,7 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(const bf16* __restr
                 wsum[wave][lq] = l;
             }
         }
-    } else {                                                 // nothing cached in this wave's range
+    } else {
         for (int i = lane; i < G * D; i += 64) osh[wave][i / D][i % D] = 0.f;
         if (lane < G) {
             wmx[wave][lane] = -INFINITY;
@@ -476,25 +614,35 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(const bf16* __restr
         }
     }
     __syncthreads();
-    // merge the four waves in wave order
+    // merge the four waves in wave order, then the new position
     const int PS = decode_partial_stride(D);
+    const bool alone = item.w == 1;                          // the sequence's only chunk: the output itself
     for (int i = tid; i < G * D; i += 256) {
         const int g = i / D, dd = i - g * D;
-        const float M = fmaxf(fmaxf(wmx[0][g], wmx[1][g]), fmaxf(wmx[2][g], wmx[3][g]));
-        float acc = 0.f;
+        float M = fmaxf(fmaxf(wmx[0][g], wmx[1][g]), fmaxf(wmx[2][g], wmx[3][g]));
+        if (newest) M = fmaxf(M, sn[g]);
+        float acc = 0.f, L = 0.f;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) acc = fmaf(osh[w][g][dd], exp2f(wmx[w][g] - M), acc);
-        partial[(((size_t)di * Hq + kvh * G + g) * bv.decode_chunks + chunk) * PS + dd] = acc;
-    }
-    if (tid < G) {
-        const int g = tid;
-        const float M = fmaxf(fmaxf(wmx[0][g], wmx[1][g]), fmaxf(wmx[2][g], wmx[3][g]));
-        float L = 0.f;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) L = fmaf(wsum[w][g], exp2f(wmx[w][g] - M), L);
-        float* pp = partial + (((size_t)di * Hq + kvh * G + g) * bv.decode_chunks + chunk) * PS;
-        pp[D] = M;
-        pp[D + 1] = L;
+        for (int w = 0; w < 4; ++w) {
+            const float f = exp2f(wmx[w][g] - M);
+            acc = fmaf(osh[w][g][dd], f, acc);
+            L = fmaf(wsum[w][g], f, L);
+        }
+        if (newest) {
+            const float f = exp2f(sn[g] - M);
+            acc = fmaf((float)vn[dd], f, acc);
+            L += f;
+        }
+        if (alone) {
+            out[(size_t)t * Hq * D + (kvh * G + g) * D + dd] = (bf16)(acc / L);
+        } else {
+            float* pp = partial + (((size_t)di * Hq + kvh * G + g) * bv.decode_chunks + chunk) * PS;
+            pp[dd] = acc;
+            if (dd == 0) {
+                pp[D] = M;
+                pp[D + 1] = L;
+            }
+        }
     }
 }
 
@@ -639,6 +787,9 @@ __global__ __launch_bounds__(D) void attn_combine_kernel(const float* __restrict
     const int s = bv.decode_seqs[di];
     const int len = bv.kv_before[s] + 1;
     const int nch = (len + kDecodeChunk - 1) / kDecodeChunk;
+#ifndef BZ_FP32_DEBUG
+    if (nch == 1) return;                                    // the decode kernel has written the output
+#endif
     const int PS = decode_partial_stride(D);
     const float* base = partial + ((size_t)di * Hq + h) * bv.decode_chunks * PS;
     float M = -INFINITY, num = 0.f, den = 0.f;
@@ -673,29 +824,32 @@ __global__ __launch_bounds__(D) void attn_combine_kernel(const float* __restrict
 }
 
 template <int D>
-static void launch_decode_d(const act_t* qkv, act_t* out, float* partial, const BatchView& bv, const KvView& kv,
-                            int Hq, hipStream_t st) {
+static void launch_decode_d(const QkvSource& qkv, [[maybe_unused]] const float* rope_tab, act_t* out, float* partial,
+                            const BatchView& bv, const KvView& kv, int Hq, hipStream_t st) {
     const float scale_log2 = kLog2e / sqrtf((float)D);
     const dim3 grid(bv.n_decode_work * kv.Hkv);
     const int G = Hq / kv.Hkv;                      // 1, 2, 4 or 8: checked when the instance is created
 #ifndef BZ_FP32_DEBUG
-    hipLaunchKernelGGL(attn_decode_kernel<D>, grid, dim3(256), 0, st, qkv, partial, bv, kv, Hq, G, scale_log2);
+    auto kern = qkv.partial ? attn_decode_kernel<D, true> : attn_decode_kernel<D, false>;
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, qkv, rope_tab, partial, out, bv, kv, Hq, G, scale_log2);
+    if (bv.n_decode_work == bv.n_decode) return;    // one chunk each: nothing to combine
 #else
+    const act_t* q = qkv.qkv;
     switch (G) {
-        case 1: hipLaunchKernelGGL((attn_decode_kernel<D, 1>), grid, dim3(256), 0, st, qkv, partial, bv, kv, Hq, G, scale_log2); break;
-        case 2: hipLaunchKernelGGL((attn_decode_kernel<D, 2>), grid, dim3(256), 0, st, qkv, partial, bv, kv, Hq, G, scale_log2); break;
-        case 4: hipLaunchKernelGGL((attn_decode_kernel<D, 4>), grid, dim3(256), 0, st, qkv, partial, bv, kv, Hq, G, scale_log2); break;
-        default: hipLaunchKernelGGL((attn_decode_kernel<D, 8>), grid, dim3(256), 0, st, qkv, partial, bv, kv, Hq, G, scale_log2); break;
+        case 1: hipLaunchKernelGGL((attn_decode_kernel<D, 1>), grid, dim3(256), 0, st, q, partial, bv, kv, Hq, G, scale_log2); break;
+        case 2: hipLaunchKernelGGL((attn_decode_kernel<D, 2>), grid, dim3(256), 0, st, q, partial, bv, kv, Hq, G, scale_log2); break;
+        case 4: hipLaunchKernelGGL((attn_decode_kernel<D, 4>), grid, dim3(256), 0, st, q, partial, bv, kv, Hq, G, scale_log2); break;
+        default: hipLaunchKernelGGL((attn_decode_kernel<D, 8>), grid, dim3(256), 0, st, q, partial, bv, kv, Hq, G, scale_log2); break;
     }
 #endif
     hipLaunchKernelGGL(attn_combine_kernel<D>, dim3(bv.n_decode, Hq), dim3(D), 0, st, partial, out, bv, Hq);
 }
 
-void launch_attn_decode(const act_t* qkv, act_t* out, float* partial, const BatchView& bv, const KvView& kv,
-                        int Hq, hipStream_t st) {
+void launch_attn_decode(const QkvSource& qkv, const float* rope_tab, act_t* out, float* partial, const BatchView& bv,
+                        const KvView& kv, int Hq, hipStream_t st) {
     if (bv.n_decode <= 0) return;
-    if (kv.d == 128) launch_decode_d<128>(qkv, out, partial, bv, kv, Hq, st);
-    else launch_decode_d<64>(qkv, out, partial, bv, kv, Hq, st);
+    if (kv.d == 128) launch_decode_d<128>(qkv, rope_tab, out, partial, bv, kv, Hq, st);
+    else launch_decode_d<64>(qkv, rope_tab, out, partial, bv, kv, Hq, st);
 }
 
 }  // namespace bz

@@ -1,4 +1,4 @@
-// HBM-bound steps of a decoder layer: RMSNorm, rotary embedding + KV-cache append, KV scatter /
+// HBM-bound steps of a decoder layer: RMSNorm, KV-cache append (keys rotated on the way), KV scatter /
 // gather for cache import/export, and the decode-batch position bump.
 #include "common.h"
 
@@ -8,29 +8,6 @@ namespace bz {
 // RMSNorm: one workgroup per token row.  Sum of squares in fp32 (wave shuffle reduction, then a
 // fixed-order sum over the waves), y = (x * rstd) * gain rounded once to the activation type.
 // ---------------------------------------------------------------------------------------------
-// sum over split-K slices, in slice order, of 8 consecutive partial sums of row m.  Loads go out four
-// slices at a time (a slice index past the end re-reads the last slice; its value is not added).
-__device__ __forceinline__ void reduce8(const float* __restrict__ partial, int ksplit, size_t slice_stride,
-                                        size_t off, float (&s)[8]) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) s[e] = 0.f;
-    for (int k0 = 0; k0 < ksplit; k0 += 4) {
-        float4 a[4], b[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int k = (k0 + u < ksplit) ? k0 + u : ksplit - 1;
-            a[u] = *reinterpret_cast<const float4*>(partial + k * slice_stride + off);
-            b[u] = *reinterpret_cast<const float4*>(partial + k * slice_stride + off + 4);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (k0 + u < ksplit) {
-                s[0] += a[u].x; s[1] += a[u].y; s[2] += a[u].z; s[3] += a[u].w;
-                s[4] += b[u].x; s[5] += b[u].y; s[6] += b[u].z; s[7] += b[u].w;
-            }
-    }
-}
-
 // REDUCE: the row of x is first completed as x + (sum of split-K slices), rounded and stored; the
 // norm then works on the rounded values, so its result is bit-identical to a separate norm kernel.
 // The first kKeep vectors of a thread (rows up to 8 * kKeep * THREADS elements: every supported
@@ -137,174 +114,181 @@ void launch_reduce_residual_rmsnorm(act_t* x, const float* partial, int ksplit, 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Rotary embedding + KV append.  Q is rotated in place inside the packed [T, (Hq+2Hkv)*d]
-// projection output; K is rotated and written to the cache; V is copied to the cache.  Pairs are
-// (j, j + d/2); the cos/sin table is [max_seq_len][d/2][2] floats built on the host in float64.
+// KV append for the sequences with several new tokens: K is rotated and written to the cache, V is copied to it.
+// (Single new tokens are appended by the decode attention kernel.)
 //
-// Workgroups [n_vblocks, n_vblocks + T) handle one token each (rotation, K write).  The V cache
-// keeps 8 positions of one head-dim index in 16 contiguous bytes, so V of a token alone is a
-// scatter of single elements: the token's workgroup does that only for positions whose aligned
-// group of 16 positions is not written completely by this batch (single-token sequences, ragged
-// ends).  Complete groups are written by workgroups [0, n_vblocks): block (prefill item, sub, h)
-// gathers the 8 positions of one piece for every (kv head, j) and stores them as one vector.
+// HBM-bound: the K and V parts of the projection in, the cache out.  A workgroup owns one aligned block of 32 positions
+// (the unit in which the cache is contiguous) of one sequence for `heads_per_wg` kv heads, so a head's block is written as
+// whole cache lines: K as 16-byte pieces, eight consecutive positions of a piece from the eight rows of a wave's load; V
+// as two pieces of 8 positions per thread, gathered from 8 rows.  The rotation's cosines and sines are loaded once per
+// workgroup.  A grid of several heads per workgroup keeps that load small beside the data; small batches take one head per
+// workgroup to fill the chip.
+//
+// Item i of the prefill list (sequence, tile of 128 new rows) covers the blocks first + 4 * tile + 0..3 of its sequence;
+// an unaligned start can make the sequence touch one block more, which the last item's fifth workgroup takes.
 // ---------------------------------------------------------------------------------------------
+#ifndef BZ_FP32_DEBUG
+constexpr int kAppendBlocks = 5;
+
 template <bool REDUCE>
-__global__ __launch_bounds__(256) void rope_append_kernel(act_t* __restrict__ qkv, const float* __restrict__ partial,
-                                                          int ksplit, const float* __restrict__ tab, BatchView bv,
-                                                          KvView kv, int Hq, int n_vblocks, int tsplit) {
+__global__ __launch_bounds__(256) void kv_append_kernel(QkvSource src, const float* __restrict__ tab, BatchView bv,
+                                                        KvView kv, int Hq, int heads_per_wg, int hgroups) {
     const int d = kv.d, Hkv = kv.Hkv, half = d >> 1;
     const int nqkv = (Hq + 2 * Hkv) * d;
-    if ((int)blockIdx.x < n_vblocks) {
-        const int item = blockIdx.x >> 4, sub = (blockIdx.x >> 1) & 7, h = blockIdx.x & 1;
-        const int s = bv.prefill_items[2 * item], qt = bv.prefill_items[2 * item + 1];
-        const int q0 = bv.q_start[s];
-        const int before = bv.kv_before[s];
-        const int end = before + (bv.q_start[s + 1] - q0);
-        const int grp = ((before + 15) >> 4) + qt * 8 + sub;      // aligned group of 16 positions
-        if (grp * 16 + 16 > end) return;
-        const int slot = bv.seq_slot[s];
-        const int cap = kv.slot_cap[slot];
-        const size_t slot_base = (size_t)kv.slot_off[slot] * Hkv * d;
-        const int p0 = grp * 16 + 4 * h;                          // the piece holds p0 + {0..3, 8..11}
-        const act_t* src = qkv + (size_t)(q0 + (p0 - before)) * nqkv + (size_t)(Hq + Hkv) * d;
-        const size_t piece_off = (size_t)(p0 >> 5) * 32 * d + (size_t)(2 * ((p0 >> 4) & 1) + h) * d * 8;
-        for (int u = threadIdx.x; u < Hkv * d; u += blockDim.x) {
-            const int kvh = u / d, j = u - kvh * d;
-            float v[8];
+    const int item = blockIdx.x / (kAppendBlocks * hgroups);
+    const int rest = blockIdx.x - item * (kAppendBlocks * hgroups);
+    const int sub = rest / hgroups, hg = rest - sub * hgroups;
+    const int s = bv.prefill_items[2 * item], qt = bv.prefill_items[2 * item + 1];
+    const int q0 = bv.q_start[s], qlen = bv.q_start[s + 1] - q0;
+    if (sub == kAppendBlocks - 1 && (qt + 1) * kPrefillTileQ < qlen) return;
+    const int before = bv.kv_before[s], end = before + qlen;
+    const int blk = (before >> 5) + qt * 4 + sub;
+    const int p_lo = blk * 32 > before ? blk * 32 : before;
+    const int p_hi = blk * 32 + 32 < end ? blk * 32 + 32 : end;
+    if (p_lo >= p_hi) return;
+    const int slot = bv.seq_slot[s];
+    const size_t head_stride = (size_t)kv.slot_cap[slot] * d;
+    const size_t block_base = (size_t)kv.slot_off[slot] * Hkv * d + (size_t)blk * 32 * d;
+    const size_t slice = (size_t)bv.T * nqkv;
+    const int tid = threadIdx.x;
+    // 256 threads are one head of d = 128 or two of d = 64, in both halves of the kernel
+    const int per_head = 2 * d, hsub = tid / per_head, ht = tid - hsub * per_head, n_par = 256 / per_head;
+    const int h0 = hg * heads_per_wg + hsub;
+    const int h1 = (hg + 1) * heads_per_wg < Hkv ? (hg + 1) * heads_per_wg : Hkv;
+
+    const int uph = d >> 4;                                       // units of 8 pairs (j, j + d/2) per head
+    const int p = ht / uph, unit = ht - p * uph;
+    const int pos = blk * 32 + p;
+    if (pos >= p_lo && pos < p_hi) {
+        const size_t row = (size_t)(q0 + pos - before) * nqkv;
+        const float* cs = tab + (size_t)pos * d + unit * 16;
+        float c8[8], s8[8];
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+            const float4 v = *reinterpret_cast<const float4*>(cs + 2 * e);
+            c8[e] = v.x; s8[e] = v.y; c8[e + 1] = v.z; s8[e + 1] = v.w;
+        }
+        for (int h = h0; h < h1; h += n_par) {
+            const size_t at = row + (size_t)(Hq + h) * d + unit * 8;
+            float lo[8], hi[8], o_lo[8], o_hi[8];
+            if (REDUCE) {
+                reduce8(src.partial, src.ksplit, slice, at, lo);
+                reduce8(src.partial, src.ksplit, slice, at + half, hi);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    lo[e] = (float)(bf16)lo[e];
+                    hi[e] = (float)(bf16)hi[e];
+                }
+            } else {
+                load8(src.qkv + at, lo);
+                load8(src.qkv + at + half, hi);
+            }
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const size_t idx = (size_t)((e & 3) + 8 * (e >> 2)) * nqkv + u;
-                if (REDUCE) {
-                    const size_t off = (size_t)(src - qkv) + idx;
-                    float a = 0.f;
-                    for (int k = 0; k < ksplit; ++k) a += partial[k * ((size_t)bv.T * nqkv) + off];
-                    act_t r;
-                    from_f32(r, a);
-                    v[e] = to_f32(r);
-                } else {
-                    v[e] = to_f32(src[idx]);
+                o_lo[e] = lo[e] * c8[e] - hi[e] * s8[e];
+                o_hi[e] = hi[e] * c8[e] + lo[e] * s8[e];
+            }
+            bf16* dst = kv.k + block_base + (size_t)h * head_stride + p * 8;
+            store8(dst + unit * 256, o_lo);
+            store8(dst + (unit + uph) * 256, o_hi);
+        }
+    }
+
+    const int w = ht / half, j = (ht - w * half) * 2;             // piece of the block, two consecutive head-dim indices
+    const int pbase = blk * 32 + 16 * (w >> 1) + 4 * (w & 1);     // the piece holds pbase + {0..3, 8..11}
+    const bool whole = pbase >= p_lo && pbase + 11 < p_hi;
+    for (int h = h0; h < h1; h += n_par) {
+        const size_t col = (size_t)(Hq + Hkv + h) * d + j;
+        float a[8], b[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            int pe = pbase + (e & 3) + 8 * (e >> 2);
+            pe = pe < p_lo ? p_lo : pe > p_hi - 1 ? p_hi - 1 : pe;            // read in bounds, not stored
+            const size_t at = (size_t)(q0 + pe - before) * nqkv + col;
+            if (REDUCE) {
+                float2 acc = make_float2(0.f, 0.f);
+                for (int k = 0; k < src.ksplit; ++k) {
+                    const float2 v = *reinterpret_cast<const float2*>(src.partial + k * slice + at);
+                    acc.x += v.x;
+                    acc.y += v.y;
+                }
+                a[e] = acc.x;
+                b[e] = acc.y;
+            } else {
+                const bf16x2 v = *reinterpret_cast<const bf16x2*>(src.qkv + at);
+                a[e] = (float)v[0];
+                b[e] = (float)v[1];
+            }
+        }
+        bf16* dst = kv.v + block_base + (size_t)h * head_stride + ((size_t)w * d + j) * 8;
+        if (whole) {
+            store8(dst, a);
+            store8(dst + 8, b);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int pe = pbase + (e & 3) + 8 * (e >> 2);
+                if (pe >= p_lo && pe < p_hi) {
+                    dst[e] = (bf16)a[e];
+                    dst[8 + e] = (bf16)b[e];
                 }
             }
-            store8(kv.v + slot_base + (size_t)kvh * cap * d + piece_off + (size_t)j * 8, v);
         }
-        return;
     }
-    // a token's work is shared by `tsplit` workgroups (small batches: more CUs than tokens)
-    int t = (blockIdx.x - n_vblocks) / tsplit;
-    const int part = (blockIdx.x - n_vblocks) % tsplit;
-    if (tsplit == 1) {
-        // One workgroup per token: workgroups go to the eight XCDs in turn, and a token's K row is 16-byte
-        // pieces that share their 128-byte lines with the 7 neighbouring positions.  Tokens are therefore
-        // dealt out in runs of 8 per XCD (n_vblocks is a multiple of 8, so blockIdx.x & 7 is the XCD), and
-        // the neighbours' pieces meet in one L2 instead of leaving eight partial lines in eight of them.
-        const int xcd = t & 7, seq = t >> 3;
-        t = ((seq >> 3) * 8 + xcd) * 8 + (seq & 7);
-        if (t >= bv.T) return;
-    }
-    const int s = bv.token_seq[t];
-    const int before = bv.kv_before[s];
-    const int pos = before + (t - bv.q_start[s]);
-    const int end = before + (bv.q_start[s + 1] - bv.q_start[s]);
-    const bool v_by_group = (pos & ~15) >= before && (pos & ~15) + 16 <= end;
+}
+
+bool kv_append_needed(const BatchView& bv) { return bv.n_prefill_items > 0; }
+
+void launch_kv_append(const QkvSource& src, const float* rope_tab, const BatchView& bv, const KvView& kv, int Hq,
+                      hipStream_t st) {
+    if (bv.n_prefill_items <= 0) return;
+    const int blocks = bv.n_prefill_items * kAppendBlocks;
+    const int n_par = 128 / kv.d;                      // heads that run side by side in a workgroup
+    int hpw = (int)((int64_t)blocks * kv.Hkv / 4096);  // keep some thousand workgroups
+    hpw = hpw < n_par ? n_par : hpw > 8 ? 8 : hpw;
+    const int hgroups = (kv.Hkv + hpw - 1) / hpw;
+    auto kern = src.partial ? kv_append_kernel<true> : kv_append_kernel<false>;
+    hipLaunchKernelGGL(kern, dim3(blocks * hgroups), dim3(256), 0, st, src, rope_tab, bv, kv, Hq, hpw, hgroups);
+}
+
+#else  // BZ_FP32_DEBUG: one workgroup per token rotates its queries in place, and its keys into the cache, and copies its values
+
+__global__ __launch_bounds__(256) void rope_append_kernel(float* __restrict__ qkv, const float* __restrict__ tab, BatchView bv,
+                                                          KvView kv, int Hq) {
+    const int d = kv.d, Hkv = kv.Hkv, half = d >> 1;
+    const int t = blockIdx.x, s = bv.token_seq[t];
+    const int pos = bv.kv_before[s] + (t - bv.q_start[s]);
     const int slot = bv.seq_slot[s];
-    const int cap = kv.slot_cap[slot];
+    const size_t head_stride = (size_t)kv.slot_cap[slot] * d;
     const size_t slot_base = (size_t)kv.slot_off[slot] * Hkv * d;
-    act_t* row = qkv + (size_t)t * nqkv;
-    const float* cs = tab + (size_t)pos * d;   // [half][2]
-    // REDUCE: the projection output is still split-K partial sums; fold them in slice order and round
-    // to the activation type first, exactly as the separate epilogue kernel would have
-    auto fetch8 = [&](int col, float (&v)[8]) {
-        if (REDUCE) {
-            float s8[8];
-            reduce8(partial, ksplit, (size_t)bv.T * nqkv, (size_t)t * nqkv + col, s8);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                act_t r;
-                from_f32(r, s8[e]);
-                v[e] = to_f32(r);
-            }
+    float* row = qkv + (size_t)t * (Hq + 2 * Hkv) * d;
+    const float* cs = tab + (size_t)pos * d;
+    for (int u = threadIdx.x; u < (Hq + Hkv) * half; u += 256) {
+        const int head = u / half, j = u - head * half;
+        const float lo = row[head * d + j], hi = row[head * d + half + j];
+        const float c = cs[2 * j], sn = cs[2 * j + 1];
+        const float o_lo = lo * c - hi * sn, o_hi = hi * c + lo * sn;
+        if (head < Hq) {
+            row[head * d + j] = o_lo;
+            row[head * d + half + j] = o_hi;
         } else {
-            load8(row + col, v);
-        }
-    };
-    const int units_per_head = half >> 3;      // 8 pairs per unit
-    const int rot_units = (Hq + Hkv) * units_per_head;
-    // V of a token that is stored element by element: first vector requested before the rotation so
-    // that both round trips to memory overlap
-    constexpr int kPass = 2048;
-    const int nv_all = Hkv * d;
-    const int v_per = ((nv_all + tsplit - 1) / tsplit + 7) & ~7;          // this workgroup's share of the V row
-    const int v_lo = part * v_per;
-    const int nv = v_lo >= nv_all ? 0 : (nv_all - v_lo < v_per ? nv_all - v_lo : v_per);
-    const int vcol = (Hq + Hkv) * d + v_lo;
-    float vpre[8];
-    if (!v_by_group && (int)threadIdx.x * 8 < nv) fetch8(vcol + threadIdx.x * 8, vpre);
-    for (int u = part * blockDim.x + threadIdx.x; u < rot_units; u += tsplit * blockDim.x) {
-        {
-            const int head = u / units_per_head;          // 0..Hq-1 query heads, then key heads
-            const int j0 = (u - head * units_per_head) * 8;
-            act_t* hp = row + head * d;
-            float lo[8], hi[8], o_lo[8], o_hi[8];
-            fetch8(head * d + j0, lo);
-            fetch8(head * d + half + j0, hi);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float c = cs[(j0 + e) * 2], sn = cs[(j0 + e) * 2 + 1];
-                o_lo[e] = lo[e] * c - hi[e] * sn;
-                o_hi[e] = hi[e] * c + lo[e] * sn;
-            }
-            if (head < Hq) {
-                store8(hp + j0, o_lo);
-                store8(hp + half + j0, o_hi);
-            } else {
-                const int kvh = head - Hq;
-                act_t* dst = kv.k + slot_base + (size_t)kvh * cap * d;
-                store8(dst + k_piece_offset(pos, j0 >> 3, d), o_lo);
-                store8(dst + k_piece_offset(pos, (half + j0) >> 3, d), o_hi);
-            }
+            float* dst = kv.k + slot_base + (size_t)(head - Hq) * head_stride;
+            dst[k_elem_offset(pos, j, d)] = o_lo;
+            dst[k_elem_offset(pos, half + j, d)] = o_hi;
         }
     }
-    if (!v_by_group) {                                  // workgroup-uniform
-        // single elements: the row is fetched in vectors and handed over through LDS so that consecutive
-        // lanes store consecutive j, i.e. cache addresses 16 bytes apart
-        __shared__ act_t vst[kPass];
-        for (int base = 0; base < nv; base += kPass) {
-            const int cnt = nv - base < kPass ? nv - base : kPass;
-            const int u8 = threadIdx.x * 8;
-            if (u8 < cnt) {
-                if (base > 0) fetch8(vcol + base + u8, vpre);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) from_f32(vst[u8 + e], vpre[e]);
-            }
-            __syncthreads();
-            for (int u = threadIdx.x; u < cnt; u += blockDim.x) {
-                const int kvh = (v_lo + base + u) / d, j = (v_lo + base + u) - kvh * d;
-                kv.v[slot_base + (size_t)kvh * cap * d + v_elem_offset(pos, j, d)] = vst[u];
-            }
-            __syncthreads();
-        }
-    }
+    for (int u = threadIdx.x; u < Hkv * d; u += 256)
+        kv.v[slot_base + (size_t)(u / d) * head_stride + v_elem_offset(pos, u % d, d)] = row[(Hq + Hkv) * d + u];
 }
 
-void launch_rope_append(act_t* qkv, const float* rope_tab, const BatchView& bv, const KvView& kv, int Hq,
-                        hipStream_t st) {
-    if (bv.T <= 0) return;
-    const int nvb = bv.n_prefill_items * 16;
-    const int tsplit = bv.T < 256 ? 4 : 1;
-    const int tblocks = tsplit == 1 ? (bv.T + 63) / 64 * 64 : bv.T * tsplit;      // runs of 8 tokens x 8 XCDs
-    hipLaunchKernelGGL(rope_append_kernel<false>, dim3(nvb + tblocks), dim3(256), 0, st, qkv, nullptr, 0, rope_tab,
-                       bv, kv, Hq, nvb, tsplit);
-}
+bool kv_append_needed(const BatchView& bv) { return bv.T > 0; }
 
-void launch_rope_append_reduce(act_t* qkv, const float* partial, int ksplit, const float* rope_tab,
-                               const BatchView& bv, const KvView& kv, int Hq, hipStream_t st) {
+void launch_kv_append(const QkvSource& src, const float* rope_tab, const BatchView& bv, const KvView& kv, int Hq,
+                      hipStream_t st) {
     if (bv.T <= 0) return;
-    const int nvb = bv.n_prefill_items * 16;
-    const int tsplit = bv.T < 256 ? 4 : 1;
-    const int tblocks = tsplit == 1 ? (bv.T + 63) / 64 * 64 : bv.T * tsplit;
-    hipLaunchKernelGGL(rope_append_kernel<true>, dim3(nvb + tblocks), dim3(256), 0, st, qkv, partial, ksplit,
-                       rope_tab, bv, kv, Hq, nvb, tsplit);
+    hipLaunchKernelGGL(rope_append_kernel, dim3(bv.T), dim3(256), 0, st, src.qkv, rope_tab, bv, kv, Hq);
 }
+#endif
 
 // ---------------------------------------------------------------------------------------------
 // KV scatter/gather between token-major [n, Hkv, d] buffers and the cache layout of one slot.

@@ -252,6 +252,52 @@ def test_mixed_ragged_batch(torch, fp32, shape):
             assert U.rel_err(got[a:b], want[a:b]) <= tol, (i, seqs[i])
 
 
+# Appends at the edges of the cache's blocks of 32, pieces of 16 and chunks of 256 positions: a sequence's first and last
+# position on either side of each, one to four blocks and one more for an unaligned start, single tokens on empty caches,
+# full chunks and the first position of a chunk.
+APPEND_EDGES = [(2, 31), (129, 0), (128, 1), (33, 30), (31, 1), (15, 17), (2, 254), (130, 127), (1, 0), (1, 31), (1, 32),
+                (1, 254), (1, 255), (1, 256), (1, 511), (1, 512)]
+
+
+@pytest.mark.parametrize("few", [False, True], ids=["rows", "partial_sums"])
+@pytest.mark.parametrize("shape", [MIX, MIX64, MHA, G8, H24], ids=lambda s: s.name)
+def test_appended_positions_at_block_edges(torch, shape, few):
+    # the first layer's cache, read back: earlier positions untouched, new ones the oracle's within the bf16 gates (the
+    # rounding of one projection and, for keys, one rotation); `few`: at most 64 rows, the projection comes as partial sums
+    s = W.DecoderShape(shape.name, 1, shape.H, shape.Hq, shape.Hkv, shape.d, shape.F, shape.eps, shape.rope_base, shape.seed)
+    seqs = [(min(n, 5) if few else n, b) for n, b in APPEND_EDGES]
+    T = sum(n for n, _ in seqs)
+    assert (T <= 64) == few
+    inst = U.make_instance(s, max_seqs=len(seqs), max_seq_len=600, max_tokens=T, kv_tokens=len(seqs) * 608)
+    bits = W.layer_weights_bits(s, 0)
+    U.load_all_layers(inst, s)
+    okv = O.OracleKV()
+    for i, (n, before) in enumerate(seqs):
+        inst.kv_reserve(i, n + before)
+        if before:
+            kb, vb = W.kv_prefill_bits(s, 0, i, before)
+            okv.put(0, i, U.f64(kb), U.f64(vb))
+            inst.kv_write(0, i, 0, before, kb, vb)
+    q_start = np.concatenate([[0], np.cumsum([n for n, _ in seqs])])
+    slots, befores = list(range(len(seqs))), [b for _, b in seqs]
+    xbits = W.hidden_bits(s, T, step=7)
+    x = U.to_device(xbits, False)
+    torch.cuda.synchronize()
+    inst.run_layers(0, 1, inst.batch(q_start, slots, befores), x)
+    inst.sync()
+    want = O.run_layers(U.oracle_shape(s), {0: U.oracle_weights(bits)}, 0, 1, U.f64(xbits),
+                        O.OracleBatch(list(q_start), slots, befores), okv)
+    assert U.rel_err(U.from_device(x), want) <= _tol(False)
+    for i, (n, before) in enumerate(seqs):
+        got = [np.zeros((n + before, s.Hkv, s.d), dtype=np.uint16) for _ in range(2)]
+        inst.kv_read(0, i, 0, n + before, *got)
+        for g, o in zip(got, okv.get(0, i, s.Hkv, s.d)):
+            assert np.array_equal(U.f64(g[:before]), o[:before]), (i, seqs[i])
+            assert U.rel_err(U.f64(g[before:]), o[before:]) <= U.BF16_TOL, (i, seqs[i])
+            U.assert_rms(U.f64(g[before:]), o[before:], U.RMS_BF16)
+    inst.close()
+
+
 def _random_case(case):
     """A seeded random decoder shape (head size, heads per group, widths that are multiples of 8 only) and batch."""
     import random
