@@ -171,6 +171,7 @@ struct BatchView {
     const int32_t* token_seq;   // [T] sequence index of each packed row
     const int32_t* prefill_items;  // [n_prefill_items][2] = (seq, q_tile)
     int n_prefill_items;
+    int prefill_keys;              // longest key range of a prefill item
     const int32_t* decode_seqs;    // [n_decode] sequence indices with exactly one new token
     int n_decode;
     int decode_chunks;             // upper bound on ceil((kv_before+1)/kDecodeChunk) over decode seqs

@@ -38,7 +38,7 @@ struct bz_batch {
     int B = 0, T = 0;
     bool all_decode = false;
     std::vector<int32_t> q_start, seq_slot, kv_before;
-    int n_prefill_items = 0, n_decode = 0;
+    int n_prefill_items = 0, prefill_keys = 0, n_decode = 0;
     std::vector<int32_t> decode_seqs;
     double prefill_sq = 0;            // sum over prefill sequences of visible (query, key) pairs
     void* dev = nullptr;              // one allocation holding all device arrays

@@ -148,6 +148,7 @@ BatchView batch_view(const bz_batch* b) {
     v.token_seq = b->d_token_seq;
     v.prefill_items = b->d_items;
     v.n_prefill_items = b->n_prefill_items;
+    v.prefill_keys = b->prefill_keys;
     v.decode_seqs = b->d_decode;
     v.n_decode = b->n_decode;
     int mx = 0, work = 0;
@@ -799,6 +800,7 @@ int describe_batch(const bz_batch_desc* d, bz_batch* b, std::vector<int32_t>& im
     std::stable_sort(its.begin(), its.end(), [](const Item& a, const Item& c) { return a.extent > c.extent; });
     for (const Item& it : its) { items.push_back(it.s); items.push_back(it.qt); }
     b->n_prefill_items = (int)its.size();
+    b->prefill_keys = its.empty() ? 0 : (int)std::min<long long>(its.front().extent, INT32_MAX);
     b->n_decode = (int)b->decode_seqs.size();
 
     // decode work list: one entry per chunk of every decode sequence's cache (the new token included), with

@@ -40,6 +40,11 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // A KV tile is 64 positions = two cache blocks of K and two of V, each block contiguous in the
 // cache in exactly the order the MFMAs read it, so a tile is moved global -> LDS by the DMA path
 // (no registers), double-buffered: tile i+1 is in flight while tile i is multiplied.
+//
+// SETS = 2: a workgroup takes 64 rows, two waves along them and two along the keys: the second pair takes every other KV
+// tile through LDS buffers of its own, and the two parts of a row's result are merged through LDS at the end.  A wave's
+// tiles are a serial chain of 1.4 us each with one wave per SIMD, and a second wave on the SIMD shortens nothing (the
+// vector and the matrix work of all its waves add up), so a grid that leaves CUs idle gains by halving the chains.
 // ---------------------------------------------------------------------------------------------
 // A lane's query fragments qf[ks] hold dims 16 ks + 8 lh + 0..7 of one row, so both halves of a rotation pair (j, j + D/2)
 // are in the same lane: the query is rotated as it is loaded.
@@ -74,18 +79,18 @@ __device__ __forceinline__ void load_rotated_query(const QkvSource& src, size_t 
     }
 }
 
-template <int D, bool REDUCE>
+template <int D, bool REDUCE, int SETS>
 __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(QkvSource qkv, const float* __restrict__ tab,
                                                               bf16* __restrict__ out, BatchView bv, KvView kv, int Hq,
                                                               float scale_log2) {
-    constexpr int BQ = kPrefillTileQ, BK = 64;
+    constexpr int RW = 4 / SETS;         // waves along the rows
+    constexpr int BQ = 32 * RW, BK = 64;
     constexpr int DB = D / 32;           // 32-wide blocks of the head dim
     constexpr int KS = D / 16;           // MFMA k-steps over the head dim
     constexpr int BLK = 32 * D;          // elements per cache block
-    constexpr int NL = D / 32;           // 1 KiB DMA loads per wave per tile, for K and again for V
+    constexpr int NL = D / 32 * SETS;    // 1 KiB DMA loads per wave per tile, for K and again for V
     constexpr int STAGE = 4 * BLK;       // elements per stage: K tile (2 blocks) then V tile (2 blocks)
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    bf16* smem = reinterpret_cast<bf16*>(smem_raw);
 
     // Workgroups go to the eight XCDs in turn.  With a multiple of 8 heads, XCD x takes Hq / 8 consecutive
     // heads; it walks them kv group by kv group, and inside a group query tile by query tile with the group's
@@ -93,10 +98,12 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(QkvSource qkv, con
     // one kv head (of a few sequences) and find them in that XCD's L2.  (Dealt out head by head across the
     // XCDs, every L2 fetched every K and V: 2.6 times the algorithmic traffic, and 11 % (MHA) to 21 % (8
     // query heads per kv head) more time.)
-    int item, h;
+    int item, h, sub;                                        // sub: which BQ rows of the item's
     if ((Hq & 7) == 0) {
         const int xcd = blockIdx.x & 7;
         int seq = blockIdx.x >> 3;
+        sub = seq % SETS;
+        seq /= SETS;
         const int hpx = Hq >> 3, G = Hq / kv.Hkv;
         // A grid that fits the chip's slots in one go (two workgroups per CU, 64 per XCD) lasts as long as its
         // busiest CU.  An XCD's CUs take its workgroups 0..31 first and 32.. as their second one, so CU c holds
@@ -104,7 +111,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(QkvSource qkv, con
         // half is therefore walked backwards: CU c gets the c-th longest and the c-th shortest (one 2000-token
         // sequence: 73 -> 60 us).  Larger grids are handed out as slots free up; longest first is right there.
         const int n_x = bv.n_prefill_items * hpx;
-        if (n_x <= 64 && seq >= 32) seq = 32 + (n_x - 1 - seq);
+        if (SETS == 1 && n_x <= 64 && seq >= 32) seq = 32 + (n_x - 1 - seq);
         // heads of one kv group that sit next to each other on this XCD (1 if groups do not tile its heads)
         const int gl = G >= hpx ? hpx : (hpx % G == 0 ? G : 1);
         const int per_group = bv.n_prefill_items * gl;
@@ -112,12 +119,15 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(QkvSource qkv, con
         item = r / gl;
         h = xcd * hpx + grp * gl + (r - item * gl);
     } else {
-        h = blockIdx.x / bv.n_prefill_items;
-        item = blockIdx.x % bv.n_prefill_items;
+        sub = blockIdx.x % SETS;
+        h = blockIdx.x / (bv.n_prefill_items * SETS);
+        item = blockIdx.x / SETS % bv.n_prefill_items;
     }
-    const int s = bv.prefill_items[2 * item], qt = bv.prefill_items[2 * item + 1];
+    const int s = bv.prefill_items[2 * item];
+    const int qt = bv.prefill_items[2 * item + 1] * SETS + sub;          // in tiles of BQ rows
     const int q0 = bv.q_start[s];
     const int qlen = bv.q_start[s + 1] - q0;
+    if (SETS > 1 && qt * BQ >= qlen) return;
     const int before = bv.kv_before[s];
     const int slot = bv.seq_slot[s];
     const int Hkv = kv.Hkv;
@@ -128,7 +138,10 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(QkvSource qkv, con
     const bf16* Vc = kv.v + head_base;
     const int nqkv = (Hq + 2 * Hkv) * D;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = (tid >> 6) % RW;                        // rows 32 * wave .. of the tile
+    const int set = SETS == 1 ? 0 : __builtin_amdgcn_readfirstlane((tid >> 6) / RW);
+    bf16* smem = reinterpret_cast<bf16*>(smem_raw) + set * (2 * STAGE);
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
     const int lq = lane & 31, lh = lane >> 5;
     const int qi = qt * BQ + wave * 32 + lq;
@@ -163,7 +176,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(QkvSource qkv, con
 #pragma unroll
         for (int q = 0; q < 2 * NL; ++q) issue_one(tile, stage, q);
     };
-    issue(0, 0);
+    issue(set, 0);
 
     bf16x8 qf[KS];
     load_rotated_query<D, REDUCE>(qkv, (size_t)(q0 + qic) * nqkv + h * D, (size_t)bv.T * nqkv, tab + (size_t)qpos * D, qf, lh);
@@ -175,17 +188,19 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(QkvSource qkv, con
         for (int r = 0; r < 16; ++r) o[b][r] = 0.f;
     float m = -INFINITY, l = 0.f;           // running max (already scaled) and sum of this lane's query row
 
-    for (int tile = 0; tile < ntiles; ++tile) {
+    const int rounds = (ntiles + SETS - 1) / SETS;
+    for (int i = 0; i < rounds; ++i) {
+        const int tile = i * SETS + set;                     // one past the last for the second set at times: wholly masked
         const int kbase = tile * BK;
         __builtin_amdgcn_s_waitcnt(0x0070);                  // own pieces of this tile landed, own LDS reads done
         __syncthreads();                                     // everyone's pieces landed; the other stage is free
         // after the last tile the same tile is requested once more into the idle stage: the load schedule
         // then needs no branch between the MFMAs
-        const int nxt = tile + 1 < ntiles ? tile + 1 : tile;
+        const int nxt = i + 1 < rounds ? tile + SETS : tile;
         if (kbase > wave_max_pos) {                          // wave-uniform: tile fully masked for this wave
-            issue(nxt, (tile + 1) & 1);
+            issue(nxt, (i + 1) & 1);
         } else {
-            const bf16* Ks = smem + (tile & 1) * STAGE;
+            const bf16* Ks = smem + (i & 1) * STAGE;
             const bf16* Vs = Ks + 2 * BLK;
             f32x16 sacc[2];
             // Operand fetch runs ahead of the MFMAs by hand: written as "read, multiply" the compiler waits for
@@ -218,7 +233,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(QkvSource qkv, con
                     if (kb == 0) ka[ks] = k_frag(1, ks);
                     else if (ks < 2 * DB) vfr[ks / DB][ks % DB] = v_frag(ks / DB, ks % DB);
                     const int m = kb * KS + ks;
-                    if (m % EVERY == EVERY - 1) issue_one(nxt, (tile + 1) & 1, m / EVERY);
+                    if (m % EVERY == EVERY - 1) issue_one(nxt, (i + 1) & 1, m / EVERY);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -238,8 +253,10 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(QkvSource qkv, con
                 for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[kb][r]);
             mx = fmaxf(m, mx * scale_log2);                  // scale > 0: max commutes with it
             mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+            // a row may have seen no key yet in the second set's tiles
+            const float ref = SETS == 1 || mx > -INFINITY ? mx : 0.f;
             if (__builtin_amdgcn_ballot_w64(mx != m) != 0) { // some row's max moved: rescale (wave-uniform)
-                const float alpha = fast_exp2(m - mx);       // m = -inf on the first tile -> 0
+                const float alpha = fast_exp2(m - ref);      // m = -inf on the first tile -> 0
                 l *= alpha;
 #pragma unroll
                 for (int b = 0; b < DB; ++b)
@@ -252,7 +269,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(QkvSource qkv, con
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const float p = fast_exp2(fmaf(sacc[kb][r], scale_log2, -mx));
+                    const float p = fast_exp2(fmaf(sacc[kb][r], scale_log2, -ref));
                     sacc[kb][r] = p;
                     rs += p;
                 }
@@ -273,6 +290,31 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(QkvSource qkv, con
     }
 
     __builtin_amdgcn_s_waitcnt(0x0F70);                      // no LDS write may be in flight when the workgroup ends
+    if (SETS == 2) {
+        // value r of thread t of a set at ex[TS r + t]
+        constexpr int TS = 64 * RW;
+        float* ex = reinterpret_cast<float*>(smem_raw) + tid % TS;
+        static_assert((DB * 16 + 2) * TS * (int)sizeof(float) <= SETS * 2 * STAGE * (int)sizeof(bf16) || SETS == 1, "merge buffer");
+        __syncthreads();                                     // everyone's loads landed and operands are read
+        if (set == 1) {
+#pragma unroll
+            for (int b = 0; b < DB; ++b)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) ex[(b * 16 + r) * TS] = o[b][r];
+            ex[DB * 16 * TS] = m;
+            ex[(DB * 16 + 1) * TS] = l;
+        }
+        __syncthreads();
+        if (set == 1) return;
+        const float m2 = ex[DB * 16 * TS], l2 = ex[(DB * 16 + 1) * TS];
+        const float M = fmaxf(m, m2);                        // finite: the first set has seen key 0
+        const float f1 = fast_exp2(m - M), f2 = fast_exp2(m2 - M);
+        l = l * f1 + l2 * f2;
+#pragma unroll
+        for (int b = 0; b < DB; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[b][r] = o[b][r] * f1 + ex[(b * 16 + r) * TS] * f2;
+    }
     if (valid) {
         const float inv = 1.0f / l;
         bf16* op = out + (size_t)(q0 + qi) * Hq * D + h * D;
@@ -288,15 +330,29 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(QkvSource qkv, con
     }
 }
 
+template <int D, bool REDUCE, int SETS>
+static void launch_prefill_sets(const QkvSource& qkv, const float* rope_tab, act_t* out, const BatchView& bv, const KvView& kv,
+                                int Hq, hipStream_t st) {
+    constexpr int kLds = SETS * 2 * 4 * 32 * D * (int)sizeof(bf16);     // per set two stages of (K tile + V tile)
+    static LdsLimit limit;
+    if (!limit.raise(reinterpret_cast<const void*>(attn_prefill_kernel<D, REDUCE, SETS>), kLds) && SETS > 1)
+        return launch_prefill_sets<D, REDUCE, 1>(qkv, rope_tab, out, bv, kv, Hq, st);
+    const float scale_log2 = kLog2e / sqrtf((float)D);
+    hipLaunchKernelGGL((attn_prefill_kernel<D, REDUCE, SETS>), dim3(bv.n_prefill_items * Hq * SETS), dim3(256), kLds, st, qkv,
+                       rope_tab, out, bv, kv, Hq, scale_log2);
+}
+
+// 64-row workgroups with two sets of waves while a CU gets one of them at most and the chains are long enough to pay for
+// the merge.  128-row tiles against these, per layer: 4 tiles x 32 heads of 55 KV tiles 78 -> 56 us, 3 x 32 of 3 to 5 KV
+// tiles 12.2 -> 12.5, one tile x 4 heads of one KV tile (d = 64) 7.2 -> 9.7.  (The second set as four more waves on the same
+// CU: 78 -> 71 and 12.2 -> 16.9.)
+constexpr int kLongKeys = 512;
 template <int D, bool REDUCE>
 static void launch_prefill_d(const QkvSource& qkv, const float* rope_tab, act_t* out, const BatchView& bv, const KvView& kv,
                              int Hq, hipStream_t st) {
-    constexpr int kLds = 2 * 4 * 32 * D * (int)sizeof(bf16);     // two stages of (K tile + V tile)
-    static LdsLimit limit;
-    (void)limit.raise(reinterpret_cast<const void*>(attn_prefill_kernel<D, REDUCE>), kLds);
-    const float scale_log2 = kLog2e / sqrtf((float)D);
-    hipLaunchKernelGGL((attn_prefill_kernel<D, REDUCE>), dim3(bv.n_prefill_items * Hq), dim3(256), kLds, st, qkv, rope_tab,
-                       out, bv, kv, Hq, scale_log2);
+    if (bv.n_prefill_items * Hq <= 128 && bv.prefill_keys > kLongKeys)
+        launch_prefill_sets<D, REDUCE, 2>(qkv, rope_tab, out, bv, kv, Hq, st);
+    else launch_prefill_sets<D, REDUCE, 1>(qkv, rope_tab, out, bv, kv, Hq, st);
 }
 
 void launch_attn_prefill(const QkvSource& qkv, const float* rope_tab, act_t* out, const BatchView& bv, const KvView& kv,

@@ -298,6 +298,20 @@ def test_appended_positions_at_block_edges(torch, shape, few):
     inst.close()
 
 
+@pytest.mark.parametrize("rows", [2, 63, 64, 65, 127, 129, 193])
+@pytest.mark.parametrize("shape", [MIX, MIX64, H24], ids=lambda s: s.name)
+def test_few_prefill_tiles_over_long_caches(torch, shape, rows):
+    # grids of few workgroups with long key ranges take the kernel whose waves share a row's keys: rows at the edges of its
+    # 64-row tiles, an even and an odd number of KV tiles of 64, tiles that only part of the rows see, and a prompt without
+    # a cache, whose first rows see nothing of the second set's keys
+    seqs = [(rows, 640), (rows, 705), (65, 449)] if shape.Hq > 8 else [(rows, 640), (rows, 705), (33, 1000), (530, 0)]
+    got, want, q_start = _mixed_case(torch, shape, False, seqs)
+    assert sum((n + 127) // 128 for n, _ in seqs) * shape.Hq <= 128
+    for i in range(len(seqs)):
+        a, b = q_start[i], q_start[i + 1]
+        assert U.rel_err(got[a:b], want[a:b]) <= _tol(False), (i, seqs[i])
+
+
 def _random_case(case):
     """A seeded random decoder shape (head size, heads per group, widths that are multiples of 8 only) and batch."""
     import random
