@@ -491,7 +491,7 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(QkvSource src, cons
     const size_t at = (size_t)t * nqkv + (is_v ? Hq + Hkv + kvh : hh < G ? kvh * G + hh : Hq + kvh) * D + j0;
     const int second = is_v ? 0 : D / 2;
     const float* cs = tab + (size_t)pos * D + (is_v ? 0 : j0 * 2);
-    f32x4 pa[4], pb[4];                                      // REDUCE: up to four slices; else only the first, raw
+    f32x4 pa[4], pb[4];                                      // REDUCE: up to four slices, the rest later
     bf16x4 ra, rb;
     if (REDUCE) {
 #pragma unroll
@@ -523,9 +523,9 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(QkvSource src, cons
     }
     bf16x8 kf[2][KS], vf[2][2][DB];
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
+        for (int b = 0; b < 2; ++b)
             kf[b][ks] = stream_load(reinterpret_cast<const bf16x8*>(Kc + boff[b] + lane_k + ks * 512));
 #pragma unroll
     for (int b = 0; b < 2; ++b)
@@ -600,41 +600,38 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(QkvSource src, cons
         }
     }
     if (live) {
-        bf16x8 qf[KS];
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            if (lq < G) qf[ks] = *reinterpret_cast<const bf16x8*>(&qs[lq][ks * 16 + lh * 8]);
-            else
-#pragma unroll
-                for (int i = 0; i < 8; ++i) qf[ks][i] = (bf16)0.f;
-        }
         f32x16 sacc[2];
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) sacc[b][r] = 0.f;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                sacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[b][ks], qf[ks], sacc[b], 0, 0, 0);
-        }
-        // lane (g = lane%32, h = lane/32) holds positions b*32 + 8*(r/4) + 4h + r%4 of head g
-        float m = -INFINITY;
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int pl = b * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
-                const float sg = (w0 + pl < pos) ? sacc[b][r] * scale_log2 : -INFINITY;
-                sacc[b][r] = sg;
-                m = fmaxf(m, sg);
-            }
-        m = fmaxf(m, __shfl_xor(m, 32, kWave));              // finite: position w0 is valid
+            for (int r = 0; r < 16; ++r) sacc[b][r] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            bf16x8 qf = {};
+            if (lq < G) qf = *reinterpret_cast<const bf16x8*>(&qs[lq][ks * 16 + lh * 8]);
+#pragma unroll
+            for (int b = 0; b < 2; ++b) sacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[b][ks], qf, sacc[b], 0, 0, 0);
+        }
+        // lane (g = lane%32, h = lane/32) holds positions b*32 + 8*(r/4) + 4h + r%4 of head g
+        float m = -INFINITY;
+        if (w0 + 64 > pos) {                                 // wave-uniform: the range ends here
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (w0 + b * 32 + 8 * (r >> 2) + 4 * lh + (r & 3) >= pos) sacc[b][r] = -INFINITY;
+        }
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) m = fmaxf(m, sacc[b][r]);
+        m = fmaxf(m, __shfl_xor(m, 32, kWave)) * scale_log2; // finite: position w0 is valid; scale > 0
         float l = 0.f;
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const float p = exp2f(sacc[b][r] - m);
+                const float p = fast_exp2(fmaf(sacc[b][r], scale_log2, -m));
                 sacc[b][r] = p;
                 l += p;
             }
