@@ -204,7 +204,7 @@ void launch_rmsnorm(const act_t* x, const bf16* gain, act_t* y, int T, int H, fl
 void launch_gemm(int mode, const act_t* a, const bf16* w, const act_t* r, act_t* c, int M, int N, int K,
                  float* ws, size_t ws_bytes, hipStream_t st);
 size_t gemm_workspace_bytes(int mode, int M, int N, int K);
-// Decode-sized problems only: computes the split-K partial sums partial[ksplit][M][Nrows] (Nrows = 2N
+// Problems whose plan cuts K only: computes the split-K partial sums partial[ksplit][M][Nrows] (Nrows = 2N
 // in SwiGLU mode) into `ws` and returns ksplit, leaving the slice-order reduction and the epilogue
 // to the consumer kernel; returns 0 (and does nothing) when the shape does not take that path.
 int launch_gemm_partial(int mode, const act_t* a, const bf16* w, int M, int N, int K, float* ws, size_t ws_bytes,
