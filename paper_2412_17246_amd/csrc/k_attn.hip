@@ -46,6 +46,8 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // tiles are a serial chain of 1.4 us each with one wave per SIMD, and a second wave on the SIMD shortens nothing (the
 // vector and the matrix work of all its waves add up), so a grid that leaves CUs idle gains by halving the chains.
 // ---------------------------------------------------------------------------------------------
+// Largest rise of a row's maximum, in powers of two, that does not move the reference of its exponentials.  Per layer, moved
+// at every rise against 8: 70B, 4 x 2048 rows 370 -> 350 us, 13B mixed batch 288 -> 282.
 constexpr float kLag = 8.f;
 
 // A lane's query fragments qf[ks] hold dims 16 ks + 8 lh + 0..7 of one row, so both halves of a rotation pair (j, j + D/2)

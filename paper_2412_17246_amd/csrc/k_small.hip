@@ -121,8 +121,9 @@ void launch_reduce_residual_rmsnorm(act_t* x, const float* partial, int ksplit, 
 // (the unit in which the cache is contiguous) of one sequence for `heads_per_wg` kv heads, so a head's block is written as
 // whole cache lines: K as 16-byte pieces, eight consecutive positions of a piece from the eight rows of a wave's load; V
 // as two pieces of 8 positions per thread, gathered from 8 rows.  The rotation's cosines and sines are loaded once per
-// workgroup.  A grid of several heads per workgroup keeps that load small beside the data; small batches take one head per
-// workgroup to fill the chip.
+// workgroup.  Before, one workgroup per token rotated queries too and wrote K in 16-byte pieces; that pass against this one
+// (the queries' share went to the prefill kernel): 13B shape, 14 091 rows 226 -> 109 us (5.3 TB/s) and 30 more there, 70B, 8192
+// rows 62 -> 18 and 32, 7B, 4973 rows 64 -> 42 and 11.
 //
 // Item i of the prefill list (sequence, tile of 128 new rows) covers the blocks first + 4 * tile + 0..3 of its sequence;
 // an unaligned start can make the sequence touch one block more, which the last item's fifth workgroup takes.
@@ -244,7 +245,9 @@ void launch_kv_append(const QkvSource& src, const float* rope_tab, const BatchVi
     if (bv.n_prefill_items <= 0) return;
     const int blocks = bv.n_prefill_items * kAppendBlocks;
     const int n_par = 128 / kv.d;                      // heads that run side by side in a workgroup
-    int hpw = (int)((int64_t)blocks * kv.Hkv / 4096);  // keep some thousand workgroups
+    // Several heads per workgroup share the load of cosines and sines, as long as some thousand workgroups remain: 14 091
+    // rows of 40 heads 126 us with one head each, 109 with five; 4973 rows of 32 heads 41.7 and 41.5 either way.
+    int hpw = (int)((int64_t)blocks * kv.Hkv / 4096);
     hpw = hpw < n_par ? n_par : hpw > 8 ? 8 : hpw;
     const int hgroups = (kv.Hkv + hpw - 1) / hpw;
     auto kern = src.partial ? kv_append_kernel<true> : kv_append_kernel<false>;
