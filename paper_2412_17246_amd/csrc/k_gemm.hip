@@ -253,15 +253,20 @@ __device__ __forceinline__ int big_row_feature(int rho) {            // row insi
 // acc += w * x, one 16x16x32 product, accumulating in place.  Written out because the compiler, given 64 accumulators
 // that fill all 256 accumulation registers, takes the form with a separate destination and rotates the accumulators
 // through copies (196 register moves and 97 waits per k-tile).  The compiler still counts the LDS reads behind the
-// operands; what it no longer sees is the time until a result may be read by other instructions: mfma_settle().
+// operands; what it no longer sees is the time until a result may be read by other instructions: mfma16_settle().
 __device__ __forceinline__ void mfma16(f32x4& acc, const bf16x8& w, const bf16x8& x) {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(x));
 }
-// Between the last mfma16 and the first other use of its results (a 4-pass product needs at most 11 wait states).
-__device__ __forceinline__ void mfma_settle() {
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_nop 15");
-    __builtin_amdgcn_sched_barrier(0);
+// The same at the end of a k-tile: behind the last one (left == 1) follow sixteen wait states, of which a 4-pass product
+// needs at most 11 before its result may be read.  They are part of the product's own statement and inside the loop,
+// because nothing else holds the register allocator back: with a separate wait behind the loop it placed its copies of
+// the accumulators between the last product and the wait.
+__device__ __forceinline__ void mfma16_settle(f32x4& acc, const bf16x8& w, const bf16x8& x, int left) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\t"
+                 "s_cmp_lg_u32 %3, 1\n\t"
+                 "s_cbranch_scc1 1\n\t"          // over the next instruction
+                 "s_nop 15"
+                 : "+a"(acc) : "v"(w), "v"(x), "s"(left) : "scc");
 }
 
 // logical tile id -> tile coordinates: groups of 4 tile rows, walked column by column, so that the
@@ -430,13 +435,16 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(const bf16* __restrict
         else wf[buf][q - NB] = *reinterpret_cast<const bf16x8*>(sw_ + wk[ks] + w_blk(q - NB));
     };
     // one k-step: MFMAs from buffer `cur`; fetch k-step `nks` of the tile in slots (sx, sw_) into the
-    // other buffer; request the NCH pieces of one operand of k-tile `ikt` into slot `islot`
-    auto kstep = [&](int cur, const unsigned char* sx, const unsigned char* sw_, int nks, int ikt, int islot, bool iweights) {
+    // other buffer; request the NCH pieces of one operand of k-tile `ikt` into slot `islot`; `left`: k-tiles from this
+    // one on (the second k-step ends them)
+    auto kstep = [&](int cur, const unsigned char* sx, const unsigned char* sw_, int nks, int ikt, int islot, bool iweights,
+                     int left) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int q = 0; q < NMMA; ++q) {
             const int j = q >> 3, i = q & 7;
-            mfma16(acc[j][i], wf[cur][j], xf[cur][i]);
+            if (cur == 1 && q == NMMA - 1) mfma16_settle(acc[j][i], wf[cur][j], xf[cur][i], left);
+            else mfma16(acc[j][i], wf[cur][j], xf[cur][i]);
             if (q % 2 == 0 && q / 2 < NFETCH) fetch_piece(sx, sw_, nks, cur ^ 1, q / 2);
             if (q % 8 == 5) issue_piece(ikt, islot, iweights, q / 8);
             __builtin_amdgcn_sched_barrier(0);
@@ -460,18 +468,17 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(const bf16* __restrict
         const int na = (sa + 2 >= kBigSlots) ? sa + 2 - kBigSlots : sa + 2;      // next tile's slots
         const int nw = (sa + 3 >= kBigSlots) ? sa + 3 - kBigSlots : sa + 3;
         const int fa2 = (sa + 4 >= kBigSlots) ? sa + 4 - kBigSlots : sa + 4;     // where tile i + 2's activations go
-        kstep(0, smem_raw + sa * kBigSlot, smem_raw + sw1 * kBigSlot, 1, kt0 + i + 2, fa2, false);
+        kstep(0, smem_raw + sa * kBigSlot, smem_raw + sw1 * kBigSlot, 1, kt0 + i + 2, fa2, false, n - i);
         // tile i + 1 has landed (only the NCH newest loads, activations of tile i + 2, may be in flight);
         // own LDS reads of tile i are done
         __builtin_amdgcn_s_waitcnt(0x0078);            // vmcnt(8) lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         // tile i + 2's weights into the slot this tile's activations just left
-        kstep(1, smem_raw + na * kBigSlot, smem_raw + nw * kBigSlot, 0, kt0 + i + 2, sa, true);
+        kstep(1, smem_raw + na * kBigSlot, smem_raw + nw * kBigSlot, 0, kt0 + i + 2, sa, true, n - i);
         sa = na;
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);                // no LDS write may be in flight when the workgroup ends
-    mfma_settle();
 
     if (PARTIAL) {
         // partial tile in accumulator order: every (wave, j, i) is 1 KiB of `ws`, four values per lane
