@@ -46,10 +46,6 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // tiles are a serial chain of 1.4 us each with one wave per SIMD, and a second wave on the SIMD shortens nothing (the
 // vector and the matrix work of all its waves add up), so a grid that leaves CUs idle gains by halving the chains.
 // ---------------------------------------------------------------------------------------------
-// Largest rise of a row's maximum, in powers of two, that does not move the reference of its exponentials.  Per layer, moved
-// at every rise against 8: 70B, 4 x 2048 rows 370 -> 350 us, 13B mixed batch 288 -> 282.
-constexpr float kLag = 8.f;
-
 // A lane's query fragments qf[ks] hold dims 16 ks + 8 lh + 0..7 of one row, so both halves of a rotation pair (j, j + D/2)
 // are in the same lane: the query is rotated as it is loaded.
 template <int D, bool REDUCE>
@@ -190,7 +186,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(QkvSource qkv, con
     for (int b = 0; b < DB; ++b)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[b][r] = 0.f;
-    float m = -INFINITY, l = 0.f;           // reference (already scaled) and the lane's half of the sum of its query row
+    float m = -INFINITY, l = 0.f;           // running max (already scaled) and sum of this lane's query row
 
     const int rounds = (ntiles + SETS - 1) / SETS;
     for (int i = 0; i < rounds; ++i) {
@@ -257,13 +253,9 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(QkvSource qkv, con
                 for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[kb][r]);
             mx = fmaxf(m, mx * scale_log2);                  // scale > 0: max commutes with it
             mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
-            // The reference of the exponentials follows a row's maximum only when it has risen by more than kLag (in powers
-            // of two) for some row (wave-uniform): probabilities up to 2^kLag and sums of them are as exact in bf16 and
-            // fp32 as those up to 1, and a rescale costs 66 multiplications per lane, an eighth of a tile's time, where
-            // among 32 rows some maximum rises nearly every tile.
-            if (__builtin_amdgcn_ballot_w64(mx > m + kLag) != 0) {
-                // a row may have seen no key yet in the second set's tiles
-                const float ref = SETS == 1 || mx > -INFINITY ? mx : 0.f;
+            // a row may have seen no key yet in the second set's tiles
+            const float ref = SETS == 1 || mx > -INFINITY ? mx : 0.f;
+            if (__builtin_amdgcn_ballot_w64(mx != m) != 0) { // some row's max moved: rescale (wave-uniform)
                 const float alpha = fast_exp2(m - ref);      // m = -inf on the first tile -> 0
                 l *= alpha;
 #pragma unroll
@@ -272,15 +264,17 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(QkvSource qkv, con
                     for (int r = 0; r < 16; ++r) o[b][r] *= alpha;
                 m = mx;
             }
-            const float ref = SETS == 1 || m > -INFINITY ? m : 0.f;
+            float rs = 0.f;
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const float p = fast_exp2(fmaf(sacc[kb][r], scale_log2, -ref));
                     sacc[kb][r] = p;
-                    l += p;
+                    rs += p;
                 }
+            rs += __shfl_xor(rs, 32, kWave);
+            l += rs;
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 bf16x8 pf;
@@ -296,7 +290,6 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(QkvSource qkv, con
     }
 
     __builtin_amdgcn_s_waitcnt(0x0F70);                      // no LDS write may be in flight when the workgroup ends
-    l += __shfl_xor(l, 32, kWave);
     if (SETS == 2) {
         // value r of thread t of a set at ex[TS r + t]
         constexpr int TS = 64 * RW;

@@ -1,0 +1,118 @@
+"""Prefill attention where scores and values span large ranges, against the CPU oracle: one layer whose queries have one
+large component, on caches whose keys answer it with an offset chosen position by position."""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import decoder as O
+from tests import _util as U
+
+pytestmark = pytest.mark.gpu
+
+# 24 query heads: one sequence makes a grid of at most 128 tiles, six of them a larger one (different kernels over long
+# key ranges)
+STEEP = {d: W.DecoderShape("steep%d" % d, L=1, H=512, Hq=24, Hkv=12, d=d, F=256, rope_base=10000.0, seed=40 + d) for d in (64, 128)}
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return torch
+
+
+def _bits(x):
+    return W.bf16_bits_from_f32(np.asarray(x, dtype=np.float32))
+
+
+def _layer(s):
+    """Seeded weights, but every query head's component of the lowest rotary frequency is 4 times the first (normalised)
+    hidden value, and its rotation partner zero."""
+    bits = dict(W.layer_weights_bits(s, 0))
+    wq = bits["wq"].copy()
+    for h in range(s.Hq):
+        wq[h * s.d + s.d // 2 - 1] = 0
+        wq[h * s.d + s.d - 1] = 0
+        wq[h * s.d + s.d // 2 - 1, 0] = _bits([4.0])[0]
+    bits["wq"] = wq
+    return bits
+
+
+def _hidden(s, T, step):
+    """Hidden values N(0, 1), the first one 4: the large query component is about 15.7."""
+    x = U.f64(W.hidden_bits(s, T, step=step))
+    x[:, 0] = 4.0
+    return _bits(x)
+
+
+def _keys(s, seq, rise, spread):
+    """Keys N(0, spread^2) whose scores carry an offset of about rise[position] powers of two."""
+    rng = np.random.default_rng([s.seed, seq])
+    k = rng.standard_normal((len(rise), s.Hkv, s.d)) * spread
+    k[:, :, s.d // 2 - 1] = (np.asarray(rise) / (15.7 / np.sqrt(s.d) * np.log2(np.e)))[:, None]
+    k[:, :, s.d - 1] = 0.0
+    return _bits(k)
+
+
+def _run(torch, s, rows, caches, xbits):
+    """One layer over sequences of `rows` new tokens each on the given caches ([(key bits, value bits)])."""
+    n = len(caches)
+    room = max(len(k) for k, _ in caches) + rows
+    inst = U.make_instance(s, max_seqs=n, max_seq_len=room, max_tokens=n * rows, kv_tokens=n * (room + 32))
+    inst.load_layer(0, inst.pinned_blob(inst.pack_layer(_layer(s))))
+    for i, (k, v) in enumerate(caches):
+        inst.kv_reserve(i, len(k) + rows)
+        inst.kv_write(0, i, 0, len(k), k, v)
+    x = U.to_device(xbits, False)
+    torch.cuda.synchronize()
+    inst.run_layers(0, 1, inst.batch([rows * i for i in range(n + 1)], list(range(n)), [len(k) for k, _ in caches]), x)
+    inst.sync()
+    got = U.from_device(x)
+    inst.close()
+    return got
+
+
+def _oracle(s, rows, caches, xbits):
+    okv = O.OracleKV()
+    for i, (k, v) in enumerate(caches):
+        okv.put(0, i, U.f64(k), U.f64(v))
+    n = len(caches)
+    return O.run_layers(U.oracle_shape(s), {0: U.oracle_weights(_layer(s))}, 0, 1, U.f64(xbits),
+                        O.OracleBatch([rows * i for i in range(n + 1)], list(range(n)), [len(k) for k, _ in caches]), okv)
+
+
+# rows per sequence and sequences: at most 64 rows in all (the projection comes as partial sums) and more, one key set and two
+GRIDS = [(40, 1), (100, 1), (10, 6), (30, 6)]
+
+
+@pytest.mark.parametrize("rows,seqs", GRIDS)
+@pytest.mark.parametrize("d", [64, 128])
+def test_rows_do_not_depend_on_the_rows_behind_them(torch, d, rows, seqs):
+    """The same prompt's first rows come out the same bits whatever follows them in the batch of the same size.  Maxima rise
+    by about 7 powers of two per 64 keys, by more or by less from row to row."""
+    s = STEEP[d]
+    keys = 704
+    rise = 7.0 * (np.arange(keys) // 64)
+    rng = np.random.default_rng(d)
+    caches = [(_keys(s, i, rise, 0.5), _bits(rng.standard_normal((keys, s.Hkv, s.d)))) for i in range(seqs)]
+    x = _hidden(s, rows * seqs, 1)
+    y = _hidden(s, rows * seqs, 2)
+    keep = rows // 2 - 4
+    head = np.arange(rows * seqs) % rows < keep
+    y[head] = x[head]
+    assert np.array_equal(_run(torch, s, rows, caches, x)[head], _run(torch, s, rows, caches, y)[head])
+
+
+@pytest.mark.parametrize("rows,seqs", GRIDS)
+@pytest.mark.parametrize("d", [64, 128])
+def test_large_values_stay_finite(torch, d, rows, seqs):
+    """Weights relative to the row's own maximum sum up to the number of keys that count at most, here 2^12 - 64, so values
+    of 2^112 stay within fp32, also where all keys but the first 64 score six powers of two above those."""
+    s = STEEP[d]
+    keys = 4096
+    rise = np.where(np.arange(keys) < 64, 0.0, 6.0)
+    caches = [(_keys(s, i, rise, 0.0), _bits(np.full((keys, s.Hkv, s.d), 2.0 ** 112))) for i in range(seqs)]
+    x = _hidden(s, rows * seqs, 1)
+    got = _run(torch, s, rows, caches, x)
+    assert np.isfinite(got).all()
+    assert U.rel_err(got, _oracle(s, rows, caches, x)) <= U.BF16_TOL
