@@ -626,7 +626,8 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(QkvSource src, cons
         for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const float p = fast_exp2(fmaf(sacc[b][r], scale_log2, -m));
+                // not the bare hardware exponential: weights below the normal range count too (0.1 to 0.3 us of 7.2 to 272)
+                const float p = exp2f(fmaf(sacc[b][r], scale_log2, -m));
                 sacc[b][r] = p;
                 l += p;
             }

@@ -45,11 +45,11 @@ def _hidden(s, T, step):
     return _bits(x)
 
 
-def _keys(s, seq, rise, spread):
-    """Keys N(0, spread^2) whose scores carry an offset of about rise[position] powers of two."""
+def _keys(s, seq, rise, spread, q=15.7):
+    """Keys N(0, spread^2) whose scores carry an offset of rise[position] powers of two, for a large query component `q`."""
     rng = np.random.default_rng([s.seed, seq])
     k = rng.standard_normal((len(rise), s.Hkv, s.d)) * spread
-    k[:, :, s.d // 2 - 1] = (np.asarray(rise) / (15.7 / np.sqrt(s.d) * np.log2(np.e)))[:, None]
+    k[:, :, s.d // 2 - 1] = (np.asarray(rise) / (q / np.sqrt(s.d) * np.log2(np.e)))[:, None]
     k[:, :, s.d - 1] = 0.0
     return _bits(k)
 
@@ -116,3 +116,23 @@ def test_large_values_stay_finite(torch, d, rows, seqs):
     got = _run(torch, s, rows, caches, x)
     assert np.isfinite(got).all()
     assert U.rel_err(got, _oracle(s, rows, caches, x)) <= U.BF16_TOL
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_decode_weights_below_the_normal_range_count(torch, d):
+    """Single new tokens: weights 2^-129 of the largest one, which fp32 and bf16 hold as denormals, on values of 2^126, next to
+    a largest one whose value is zero.  The offset comes from a query component of bf16, itself the product of a bf16
+    value and a weight and then rotated: three roundings of 2^-9 on 129 powers of two, a factor of 2^0.76 at most."""
+    s = STEEP[d]
+    keys = 40
+    rise = np.where(np.arange(keys) == 7, 65.0, -64.0)
+    v = np.full((keys, s.Hkv, s.d), 2.0 ** 126)
+    v[7] = 0.0
+    x = _hidden(s, 3, 1)
+    q = 4.0 * O.rmsnorm(U.f64(x), U.f64(_layer(s)["g1"]), s.eps)[:, 0]
+    caches = [(_keys(s, i, rise, 0.0, q[i]), _bits(v)) for i in range(3)]
+    got, want = _run(torch, s, 1, caches, x), _oracle(s, 1, caches, x)
+    plain = _oracle(s, 1, [(k, _bits(np.zeros_like(v))) for k, _ in caches], x)
+    large = np.abs(want - plain) > 0.5 * np.abs(want - plain).max()
+    factor = (got - plain)[large] / (want - plain)[large]
+    assert 2.0 ** -0.8 < factor.min() and factor.max() < 2.0 ** 0.8, (factor.min(), factor.max())
