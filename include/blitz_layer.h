@@ -401,11 +401,11 @@ int bz_op_rmsnorm(const void* x, const void* gain, void* y, int T, int H, float 
  * mode 1: c[M,N] = r[M,N] + a * w^T          (r may alias c)
  * mode 2: w is [2N,K] (gate rows then up rows): c[M,N] = silu(a*wg^T) .* (a*wu^T)
  * `workspace`: device scratch of at least bz_op_gemm_workspace_bytes(mode, M, N, K) bytes, 16-byte
- * aligned.  Problems of up to 256 rows split K over workgroups and keep partial sums there;
- * larger ones whose tile count is below the number of compute units, or leaves a small last
- * round, split those tiles over K and keep partial tiles there.  With NULL or too small a workspace
- * a schedule that needs none is used (same result up to fp32 summation order); bz_run_layers always
- * provides one. */
+ * aligned.  Problems of up to 2048 rows may split K over workgroups and keep partial sums there;
+ * larger ones (and some from 257 rows on) whose tile count is below the number of compute units, or
+ * leaves a small last round, split those tiles over K and keep partial tiles there.  With a smaller
+ * workspace K is cut into fewer ranges, with NULL or one too small for that not at all (same result
+ * up to fp32 summation order).  bz_run_layers uses the instance's own scratch. */
 size_t bz_op_gemm_workspace_bytes(int mode, int M, int N, int K);
 int bz_op_gemm(int mode, const void* a, const void* w, const void* r, void* c, int M, int N, int K, void* workspace,
                size_t workspace_bytes, void* stream);
@@ -416,7 +416,7 @@ int bz_op_gemm(int mode, const void* a, const void* w, const void* r, void* c, i
  * from a static device array of BZ_STATIC_SCRATCH_BYTES that each GPU the library runs on holds until
  * the process ends.  The call allocates and frees nothing.  BZ_ECAPACITY, before any GPU work, if
  * bz_op_gemm_workspace_bytes(mode, M, N, K) exceeds BZ_STATIC_SCRATCH_BYTES (a problem of up to 256
- * rows whose split-K partial sums are larger; every larger problem fits).  All calls on one GPU share
+ * rows whose output in fp32 is larger, gate and up counted both; every larger problem fits).  All calls on one GPU share
  * the one array: calls that overlap in time on the same GPU (two streams, two threads) race; issue
  * them on one stream or order them with events.  Nothing in the array has to be cleared between calls. */
 #define BZ_STATIC_SCRATCH_BYTES (64u << 20)

@@ -199,11 +199,12 @@ constexpr int kDecodeChunk = 256;    // KV positions per decode-attention workgr
 
 // ---- launchers (each enqueues on `st`; shapes are validated by the callers) ------------------
 void launch_rmsnorm(const act_t* x, const bf16* gain, act_t* y, int T, int H, float eps, hipStream_t st);
-// `ws` is fp32 scratch of at least gemm_workspace_bytes(mode, M, N, K) bytes (0 for shapes that need none);
-// without it the decode-sized shapes fall back to a kernel that needs no scratch.
+// `ws` is fp32 scratch, best of at least gemm_workspace_bytes(mode, M, N, K) bytes (0 for shapes that need none).  With less,
+// K is cut into fewer ranges, or a kernel that needs no scratch takes the problem.
 void launch_gemm(int mode, const act_t* a, const bf16* w, const act_t* r, act_t* c, int M, int N, int K,
                  float* ws, size_t ws_bytes, hipStream_t st);
 size_t gemm_workspace_bytes(int mode, int M, int N, int K);
+size_t gemm_instance_bytes(int mode, int M, int N, int K);      // what an instance sets aside for the problem
 // Problems whose plan cuts K only: computes the split-K partial sums partial[ksplit][M][Nrows] (Nrows = 2N
 // in SwiGLU mode) into `ws` and returns ksplit, leaving the slice-order reduction and the epilogue
 // to the consumer kernel; returns 0 (and does nothing) when the shape does not take that path.

@@ -73,6 +73,14 @@ void layout_of(const bz_config* c, bz_layer_layout* o) {
 }
 
 
+// fp32 scratch of a batch of T rows: the largest share of the four projections.  A function of the model and T alone, so that
+// every instance that may run the batch, whatever its largest batch, cuts the projections the same way.
+size_t gemm_scratch(const bz_config* c, int T) {
+    const int nqkv = (c->n_q_heads + 2 * c->n_kv_heads) * c->head_dim, qd = c->n_q_heads * c->head_dim;
+    return std::max({gemm_instance_bytes(0, T, nqkv, c->hidden), gemm_instance_bytes(1, T, c->hidden, qd),
+                     gemm_instance_bytes(2, T, c->ffn, c->hidden), gemm_instance_bytes(1, T, c->hidden, c->ffn)});
+}
+
 void ws_layout(const bz_config* c, WsLayout* w) {
     const size_t T = c->max_tokens, e = sizeof(act_t);
     const size_t nqkv = (size_t)(c->n_q_heads + 2 * c->n_kv_heads) * c->head_dim;
@@ -84,28 +92,15 @@ void ws_layout(const bz_config* c, WsLayout* w) {
     w->act = take(T * c->ffn * e);
     const size_t chunks = (c->max_seq_len + kDecodeChunk - 1) / kDecodeChunk;
     w->partial = take((size_t)c->max_seqs * c->n_q_heads * chunks * decode_partial_stride(c->head_dim) * sizeof(float));
-    {   // fp32 scratch of the GEMMs: the largest need of the four projections over every row count a call may bring.
-        // Up to 64 rows and beyond 2048 it does not fall with the rows (of a 256-row tile).  Between, every tile is a
-        // multiple of 32 rows, so within 32 rows the forms that compete stay the same and a form with fewer ranges of K, whose
-        // cost grows slower with the rows, can only replace one with more: what the first row count takes per row, times the
-        // last row count, bounds them all (asking for each of them would cost 2 ms of instance creation).
-        const int qd = c->n_q_heads * c->head_dim;
+    {   // fp32 scratch of the GEMMs, over every row count a call may bring: up to 256 rows it is linear in the rows for a
+        // given number of 64-row blocks, beyond it depends on the number of 256-row tiles only
         size_t g = 0;
-        auto need = [&](int M, int upto) {
-            for (const size_t t : {gemm_workspace_bytes(0, M, (int)nqkv, c->hidden), gemm_workspace_bytes(1, M, c->hidden, qd),
-                                   gemm_workspace_bytes(2, M, c->ffn, c->hidden), gemm_workspace_bytes(1, M, c->hidden, c->ffn)}) {
-                const size_t all = upto > M ? (t / M + 1) * upto : t;
-                if (all > g) g = all;
-            }
+        auto need = [&](int M) {
+            const size_t t = gemm_scratch(c, M < c->max_tokens ? M : c->max_tokens);
+            if (t > g) g = t;
         };
-        const int most = c->max_tokens;
-        need(most < 64 ? most : 64, 0);
-        for (int M = 65; M <= 2048 && M <= most; M += 32) {
-            const int last = M + 31 < most ? M + 31 : most;
-            need(M, last);
-            need(last, 0);
-        }
-        for (int M = 2304; M < most + 256; M += 256) need(M < most ? M : most, 0);
+        for (int M = 64; M <= 256; M += 64) need(M);
+        for (int M = 512; M < c->max_tokens + 256; M += 256) need(M);
         w->gemm_ws_bytes = g;
         w->gemm_ws = take(g);
     }
@@ -1038,7 +1033,7 @@ int bz_run_layers(bz_instance* I, int a, int b, const bz_batch* batch, void* hid
     act_t* act = reinterpret_cast<act_t*>(I->wsp + I->ws.act);
     float* partial = reinterpret_cast<float*>(I->wsp + I->ws.partial);
     float* gws = reinterpret_cast<float*>(I->wsp + I->ws.gemm_ws);
-    const size_t gwsb = I->ws.gemm_ws_bytes;
+    const size_t gwsb = std::min(gemm_scratch(&I->cfg, T), I->ws.gemm_ws_bytes);
     const float* rope = reinterpret_cast<const float*>(I->wsp + I->ws.rope);
     hipStream_t st = I->compute;
     const double e = sizeof(act_t);

@@ -949,8 +949,7 @@ constexpr MidTile kMidTiles[] = {
 #undef BZ_MID_ENTRY
 };
 constexpr int kMidMinM = 65, kMidMaxM = 2048;
-// Partial sums stay within what every caller's scratch could always hold.
-constexpr size_t kMidMaxPartial = (size_t)64 << 20;
+constexpr size_t kMidMaxPartial = BZ_STATIC_SCRATCH_BYTES;      // partial sums stay within the static scratch
 
 struct MidPlan {
     int tile, m_tiles, n_tiles, kt_per_split, ksplit;
@@ -961,7 +960,8 @@ struct MidPlan {
 // Time model, microseconds, fitted to 900 measurements (9 % rms): a k-tile costs 0.14 + 0.48e-3 (BM + BN) + 1.33e-5 BM BN, a
 // round of 256 workgroups 2.8 more, the whole at least the weights at 4.8 TB/s; a MB of partial sums 0.27 to write and 0.25
 // to read in the kernel that folds it.  Picking by it costs 2 to 4 % against picking the fastest measured form.
-static MidPlan mid_plan(int mode, int M, int N, int K, bool may_split) {
+// `room`: bytes of scratch there are; the best plan within them.
+static MidPlan mid_plan(int mode, int M, int N, int K, size_t room) {
     const int Nrows = (mode == 2) ? 2 * N : N, nk = K / kBK;
     constexpr int kCUs = 256, kMinKt = 4;
     MidPlan best{};
@@ -970,14 +970,14 @@ static MidPlan mid_plan(int mode, int M, int N, int K, bool may_split) {
         const int bm = kMidTiles[t].wt * kMidTiles[t].nbt * 16, bn = (4 / kMidTiles[t].wt) * kMidTiles[t].nbf * 16;
         const int mt = (M + bm - 1) / bm, nt = (Nrows + bn - 1) / bn;
         const float tk = 0.14f + 0.48e-3f * (float)(bm + bn) + 1.33e-5f * (float)(bm * bn);
-        int most = may_split ? kCUs / (mt * nt) : 1;
+        int most = kCUs / (mt * nt);
         if (most > 16) most = 16;
         if (most > nk / kMinKt) most = nk / kMinKt;
         for (int ks = 1; ks == 1 || ks <= most; ++ks) {
             const int per = (nk + ks - 1) / ks;
             if ((nk + per - 1) / per != ks) continue;           // same ranges as a smaller number of them
             const size_t bytes = ks > 1 ? (size_t)ks * M * Nrows * sizeof(float) : 0;
-            if (bytes > kMidMaxPartial) break;
+            if (bytes > kMidMaxPartial || bytes > room) break;
             const int rounds = (mt * nt * ks + kCUs - 1) / kCUs;
             float body = (float)rounds * (float)per * tk;
             const float stream = (float)Nrows * (float)K * 2.0f / 4.8e6f;
@@ -1000,10 +1000,13 @@ static float big_us(int mode, int M, int N, int K) {
 
 // Whether the mid-sized kernel takes the problem: always up to 256 rows (the large tiles never win there), beyond where the
 // models say so.  301 .. 1600 rows of the measured shapes: the choice is within 3 % of the better of the two on average.
-static bool mid_takes(int mode, int M, int N, int K, MidPlan& p) {
+// Which kernel is a matter of the shape alone; `p` is the plan within the scratch there is.
+static bool mid_takes(int mode, int M, int N, int K, size_t room, MidPlan& p) {
     if (M < kMidMinM || M > kMidMaxM || !big_ok(M, N, K)) return false;
-    p = mid_plan(mode, M, N, K, true);
-    return M <= 256 || p.us < big_us(mode, M, N, K);
+    p = mid_plan(mode, M, N, K, kMidMaxPartial);
+    if (M > 256 && p.us >= big_us(mode, M, N, K)) return false;
+    if (p.ws_bytes > room) p = mid_plan(mode, M, N, K, room);
+    return true;
 }
 
 struct MidArgs {
@@ -1353,14 +1356,34 @@ static bool skinny_ok(int M, int N, int K) {
 size_t gemm_workspace_bytes(int mode, int M, int N, int K) {
     if (skinny_ok(M, N, K)) return skinny_plan(M, N, K, mode).ws_bytes;
     MidPlan p;
-    if (mid_takes(mode, M, N, K, p)) {
-        // Up to 256 rows a problem whose output, as one range's sums, is larger than the bound keeps being reported with
-        // that size, although its K is never cut: callers with that much scratch and no more keep refusing it.
+    if (mid_takes(mode, M, N, K, kMidMaxPartial, p)) {
+        // Up to 256 rows a problem whose output, as one range's sums, is larger than the static scratch is reported with
+        // that size, although its K is never cut: the interface promises that such a problem is refused there.
         const size_t one = (size_t)M * ((mode == 2) ? 2 * N : N) * sizeof(float);
         return M <= 256 && one > kMidMaxPartial ? one : p.ws_bytes;
     }
     if (big_ok(M, N, K)) return big_plan(mode, M, N, K).ws_bytes;
     return 0;
+}
+
+// What an instance sets aside for a problem.  It is part of bz_query_sizes, which callers keep workspaces by, so it is not
+// what the plans would like best: partial sums of up to 256 rows over as many ranges of K as tiles of 64 (long streams:
+// 128) weight rows and blocks of 128 rows leave compute units for, and the large tiles' beyond.  run_layers hands the plans
+// of a batch the largest of its four projections' (13B output projection, 200 rows: 7.8 MB of sums, its own share 3.9);
+// of all row counts of five decoder shapes that costs a plan more than 1 % at one (13B down projection around 200 rows, 1.3 %).
+size_t gemm_instance_bytes(int mode, int M, int N, int K) {
+    if (M > 256 || K % kBK) return big_ok(M, N, K) ? big_plan(mode, M, N, K).ws_bytes : 0;
+    if (M <= kSkMaxM) return skinny_ok(M, N, K) ? skinny_plan(M, N, K, mode).ws_bytes : 0;
+    if (!big_ok(M, N, K)) return 0;
+    const int Nrows = (mode == 2) ? 2 * N : N, nk = K / kBK;
+    const int rb = (size_t)Nrows * K * sizeof(bf16) >= kSkStreamBytes ? 2 : 1;
+    const int tiles = (Nrows + 64 * rb - 1) / (64 * rb);
+    int ranges = 256 / ((M + 127) / 128) / tiles;
+    if (ranges < 1) ranges = 1;
+    int per = (nk + ranges - 1) / ranges;
+    const int least = nk < 4 * rb ? nk : 4 * rb;
+    if (per < least) per = least;
+    return (size_t)((nk + per - 1) / per) * M * Nrows * sizeof(float);
 }
 
 static bool skinny_applies(int mode, int M, int N, int K, const float* ws, size_t ws_bytes) {
@@ -1413,7 +1436,7 @@ int launch_gemm_partial(int mode, const act_t* a, const bf16* w, int M, int N, i
     if (M <= 0 || N <= 0) return 0;
     if (skinny_applies(mode, M, N, K, ws, ws_bytes)) return launch_skinny_partial(mode, a, w, nullptr, M, N, K, ws, st);
     MidPlan p;
-    if (ws == nullptr || !mid_takes(mode, M, N, K, p) || p.ksplit == 1 || ws_bytes < p.ws_bytes) return 0;
+    if (ws == nullptr || !mid_takes(mode, M, N, K, ws_bytes, p) || p.ksplit == 1) return 0;
     return launch_mid(mode, p, a, w, nullptr, nullptr, M, N, K, ws, st) ? p.ksplit : 0;
 }
 
@@ -1433,13 +1456,12 @@ static void launch_skinny(const bf16* a, const bf16* w, const bf16* r, bf16* c, 
     launch_partial_epilogue<MODE>(ws, r, c, M, N, ksplit, st);
 }
 
-// false: not a problem of the mid-sized kernel (or no LDS for it).  Without scratch for the plan's partial sums K stays whole.
+// false: not a problem of the mid-sized kernel (or no LDS for it).
 template <int MODE>
 static bool launch_mid_whole(const bf16* a, const bf16* w, const bf16* r, bf16* c, int M, int N, int K, float* ws,
                              size_t ws_bytes, hipStream_t st) {
     MidPlan p;
-    if (!mid_takes(MODE, M, N, K, p)) return false;
-    if (p.ksplit > 1 && (ws == nullptr || ws_bytes < p.ws_bytes)) p = mid_plan(MODE, M, N, K, false);
+    if (!mid_takes(MODE, M, N, K, ws == nullptr ? 0 : ws_bytes, p)) return false;
     if (!launch_mid(MODE, p, a, w, r, c, M, N, K, ws, st)) return false;
     if (p.ksplit > 1) launch_partial_epilogue<MODE>(ws, r, c, M, N, p.ksplit, st);
     return true;
@@ -1513,6 +1535,7 @@ __global__ __launch_bounds__(256) void gemm_naive_kernel(const float* __restrict
 }
 
 size_t gemm_workspace_bytes(int, int, int, int) { return 0; }
+size_t gemm_instance_bytes(int, int, int, int) { return 0; }
 int launch_gemm_partial(int, const act_t*, const bf16*, int, int, int, float*, size_t, hipStream_t) { return 0; }
 
 void launch_gemm(int mode, const act_t* a, const bf16* w, const act_t* r, act_t* c, int M, int N, int K,

@@ -67,6 +67,25 @@ def test_layer_bytes_of_the_five_configured_shapes(lib):
         assert sz.layer_bytes == nbytes
 
 
+def test_workspace_sizes_stay_what_callers_hold():
+    """bz_create refuses a workspace smaller than bz_query_sizes says, and callers keep workspaces across versions of the
+    library: the sizes are pinned (4 sequences of at most 512 positions)."""
+    rows = (1, 64, 150, 256, 552, 2048, 8192)
+    want = {
+        "tiny": (149760, 744192, 1556224, 2556672, 3721728, 9609984, 33792768),
+        "7b": (589824, 12814848, 26619392, 39062016, 102267392, 196479488, 583404032),
+        "8b_gqa": (584192, 12454400, 26200576, 44435968, 99158528, 184945152, 537266688),
+        "13b": (630784, 13339648, 28845056, 48925696, 106867712, 227970048, 713460736),
+        "70b": (868864, 22286848, 51524096, 87560704, 128684544, 294130176, 973607424),
+    }
+    for name, sizes in want.items():
+        for T, nbytes in zip(rows, sizes):
+            cfg = B.make_config(workloads.CONFIGS[name], max_seqs=4, max_seq_len=512, max_tokens=T, kv_tokens=1024)
+            sz = B.bz_sizes()
+            assert B.load_library(False).bz_query_sizes(C.byref(cfg), C.byref(sz)) == 0
+            assert sz.workspace_bytes == nbytes, (name, T)
+
+
 @pytest.mark.parametrize("field,value", [("n_layers", 0), ("hidden", 100), ("head_dim", 96), ("n_kv_heads", 3),
                                          ("ffn", 13), ("max_seqs", 0), ("kv_tokens", 0), ("rms_eps", 0.0),
                                          ("n_q_heads", 48)])
