@@ -410,6 +410,19 @@ size_t bz_op_gemm_workspace_bytes(int mode, int M, int N, int K);
 int bz_op_gemm(int mode, const void* a, const void* w, const void* r, void* c, int M, int N, int K, void* workspace,
                size_t workspace_bytes, void* stream);
 
+/* Which kernel bz_op_gemm takes with that much workspace and how it cuts the problem, for tests; touches no
+ * GPU.  In the fp32 debug build all zero. */
+enum { BZ_GEMM_SMALL = 0, BZ_GEMM_DECODE = 1, BZ_GEMM_MID = 2, BZ_GEMM_LARGE = 3 };
+typedef struct bz_gemm_plan {
+    int kernel;                     /* BZ_GEMM_* */
+    int tile_rows, tile_cols;       /* rows of a, and of w, per tile */
+    int tiles_m, tiles_n;
+    int whole_tiles;                /* BZ_GEMM_LARGE: tiles whose K stays whole */
+    int ranges;                     /* ranges of K (BZ_GEMM_LARGE: of the remaining tiles) */
+    size_t workspace_bytes;         /* what of the workspace is used */
+} bz_gemm_plan;
+int bz_op_gemm_plan(int mode, int M, int N, int K, size_t workspace_bytes, bz_gemm_plan* out);
+
 /* bz_op_gemm for callers that cannot allocate device memory and have no workspace to hand over: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, kernels,
  * schedules and results (bit for bit) as bz_op_gemm called with a sufficient workspace; the scratch comes

@@ -101,6 +101,13 @@ class bz_profile(C.Structure):
                 ("bytes", C.c_double * _NK)]
 
 
+class bz_gemm_plan(C.Structure):
+    _fields_ = [("kernel", C.c_int), ("tile_rows", C.c_int), ("tile_cols", C.c_int), ("tiles_m", C.c_int),
+                ("tiles_n", C.c_int), ("whole_tiles", C.c_int), ("ranges", C.c_int), ("workspace_bytes", C.c_size_t)]
+
+
+BZ_GEMM_SMALL, BZ_GEMM_DECODE, BZ_GEMM_MID, BZ_GEMM_LARGE = 0, 1, 2, 3
+
 # name -> (restype, argtypes); also the list of symbols the header declares
 _P = C.c_void_p
 SIGNATURES = {
@@ -161,6 +168,7 @@ SIGNATURES = {
     "bz_op_rmsnorm": (C.c_int, [_P, _P, _P, C.c_int, C.c_int, C.c_float, _P]),
     "bz_op_gemm_workspace_bytes": (C.c_size_t, [C.c_int, C.c_int, C.c_int, C.c_int]),
     "bz_op_gemm": (C.c_int, [C.c_int, _P, _P, _P, _P, C.c_int, C.c_int, C.c_int, _P, C.c_size_t, _P]),
+    "bz_op_gemm_plan": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_size_t, C.POINTER(bz_gemm_plan)]),
     "bz_op_gemm_static": (C.c_int, [C.c_int, _P, _P, _P, _P, C.c_int, C.c_int, C.c_int, _P]),
 }
 
@@ -590,6 +598,17 @@ def op_rmsnorm(x, gain, y, eps: float, stream=None, fp32_debug: bool = False) ->
 
 def op_gemm_workspace_bytes(mode: int, M: int, N: int, K: int, fp32_debug: bool = False) -> int:
     return int(load_library(fp32_debug).bz_op_gemm_workspace_bytes(mode, M, N, K))
+
+
+def op_gemm_plan(mode: int, M: int, N: int, K: int, workspace_bytes=None, fp32_debug: bool = False) -> bz_gemm_plan:
+    """Kernel and cut of a product; `workspace_bytes` None: with the workspace it would like."""
+    if workspace_bytes is None:
+        workspace_bytes = op_gemm_workspace_bytes(mode, M, N, K, fp32_debug)
+    out = bz_gemm_plan()
+    rc = load_library(fp32_debug).bz_op_gemm_plan(mode, M, N, K, workspace_bytes, C.byref(out))
+    if rc:
+        raise BzError(rc, "bz_op_gemm_plan")
+    return out
 
 
 def op_gemm(mode: int, a, w, r, c, M: int, N: int, K: int, stream=None, fp32_debug: bool = False,

@@ -205,6 +205,7 @@ void launch_gemm(int mode, const act_t* a, const bf16* w, const act_t* r, act_t*
                  float* ws, size_t ws_bytes, hipStream_t st);
 size_t gemm_workspace_bytes(int mode, int M, int N, int K);
 size_t gemm_instance_bytes(int mode, int M, int N, int K);      // what an instance sets aside for the problem
+void gemm_plan(int mode, int M, int N, int K, size_t room, bz_gemm_plan* out);
 // Problems whose plan cuts K only: computes the split-K partial sums partial[ksplit][M][Nrows] (Nrows = 2N
 // in SwiGLU mode) into `ws` and returns ksplit, leaving the slice-order reduction and the epilogue
 // to the consumer kernel; returns 0 (and does nothing) when the shape does not take that path.

@@ -1239,6 +1239,12 @@ size_t bz_op_gemm_workspace_bytes(int mode, int M, int N, int K) {
     return gemm_workspace_bytes(mode, M, N, K);
 }
 
+int bz_op_gemm_plan(int mode, int M, int N, int K, size_t workspace_bytes, bz_gemm_plan* out) {
+    if (!out || mode < 0 || mode > 2 || M < 0 || N < 1 || K < 8 || K % 8) return BZ_EINVAL;
+    gemm_plan(mode, M, N, K, workspace_bytes, out);
+    return BZ_OK;
+}
+
 int bz_op_gemm(int mode, const void* a, const void* w, const void* r, void* c, int M, int N, int K, void* workspace,
                size_t workspace_bytes, void* stream) {
     if (mode < 0 || mode > 2 || !a || !w || !c || (mode == 1 && !r)) return BZ_EINVAL;

@@ -939,10 +939,10 @@ __global__ __launch_bounds__(256, 1) void gemm_mid_kernel(const bf16* __restrict
 }
 
 // Tiles that exist.  Chosen so that over 65 .. 1600 rows of six projection shapes the best of them is within 1 % of the
-// best of 34 measured.
+// best of 34 measured; 320 x 96 is the fastest on none of 596 problems and no longer among them.
 struct MidTile { int wt, nbt, nbf; };
 #define BZ_MID_TILES(X) X(2, 3, 4) X(4, 2, 4) X(4, 2, 6) X(4, 3, 6) X(4, 3, 8) X(2, 5, 4) X(2, 5, 6) X(2, 6, 6) X(2, 7, 6) \
-                        X(2, 5, 8) X(2, 8, 4) X(4, 4, 6) X(4, 5, 6)
+                        X(2, 5, 8) X(2, 8, 4) X(4, 4, 6)
 constexpr MidTile kMidTiles[] = {
 #define BZ_MID_ENTRY(a, b, c) {a, b, c},
     BZ_MID_TILES(BZ_MID_ENTRY)
@@ -957,9 +957,15 @@ struct MidPlan {
     size_t ws_bytes;
 };
 
-// Time model, microseconds, fitted to 900 measurements (9 % rms): a k-tile costs 0.14 + 0.48e-3 (BM + BN) + 1.33e-5 BM BN, a
-// round of 256 workgroups 2.8 more, the whole at least the weights at 4.8 TB/s; a MB of partial sums 0.27 to write and 0.25
-// to read in the kernel that folds it.  Picking by it costs 2 to 4 % against picking the fastest measured form.
+// Time model, microseconds, fitted to 26 000 measurements with cold weights (596 problems of 65 to 1938 rows, all tiles, 1 to 16
+// ranges; 9 % rms).  A k-tile costs 0.043 + 0.00069 BM + 0.00124 BN + 8.8e-6 BM BN; a round 1.35, and 0.066 per MB of activations
+// that the eight XCDs fetch in it; the weights stream at 7.15 TB/s at most, and the two bound the body together (4-norm).
+// Partial sums cost 0.434 per MB and, behind gate/up, 1.8 for the kernel that folds them (elsewhere the next step does).
+// A round is what an XCD's 32 CUs hold: an XCD takes whole units, so 27 units of 9 tiles (243 workgroups) are two rounds,
+// four units being 36 workgroups on three of the XCDs.  Against the kernels of before (65 to 256 rows the decode kernel in
+// blocks of 128, beyond the large tiles) the plans are 20 % faster on average and slower by more than 4 % on 16 of the 596.
+// An earlier model, without rounds per XCD and the cost of many rows sharing few weights, picked plans slower than those
+// kernels on 67 of them (70B down projection at 65 to 128 rows 139 -> 84 us with this one, 13B at 398 rows 109 -> 73).
 // `room`: bytes of scratch there are; the best plan within them.
 static MidPlan mid_plan(int mode, int M, int N, int K, size_t room) {
     const int Nrows = (mode == 2) ? 2 * N : N, nk = K / kBK;
@@ -969,7 +975,7 @@ static MidPlan mid_plan(int mode, int M, int N, int K, size_t room) {
     for (int t = 0; t < (int)(sizeof(kMidTiles) / sizeof(kMidTiles[0])); ++t) {
         const int bm = kMidTiles[t].wt * kMidTiles[t].nbt * 16, bn = (4 / kMidTiles[t].wt) * kMidTiles[t].nbf * 16;
         const int mt = (M + bm - 1) / bm, nt = (Nrows + bn - 1) / bn;
-        const float tk = 0.14f + 0.48e-3f * (float)(bm + bn) + 1.33e-5f * (float)(bm * bn);
+        const float tk = 0.043f + 0.69e-3f * (float)bm + 1.24e-3f * (float)bn + 8.8e-6f * (float)(bm * bn);
         int most = kCUs / (mt * nt);
         if (most > 16) most = 16;
         if (most > nk / kMinKt) most = nk / kMinKt;
@@ -978,33 +984,45 @@ static MidPlan mid_plan(int mode, int M, int N, int K, size_t room) {
             if ((nk + per - 1) / per != ks) continue;           // same ranges as a smaller number of them
             const size_t bytes = ks > 1 ? (size_t)ks * M * Nrows * sizeof(float) : 0;
             if (bytes > kMidMaxPartial || bytes > room) break;
-            const int rounds = (mt * nt * ks + kCUs - 1) / kCUs;
-            float body = (float)rounds * (float)per * tk;
-            const float stream = (float)Nrows * (float)K * 2.0f / 4.8e6f;
-            if (body < stream) body = stream;
-            const float us = 2.1f + body + 2.8f * (float)rounds + 0.52e-6f * (float)bytes;
+            const int rounds = ((nt * ks + 7) / 8 * mt + kCUs / 8 - 1) / (kCUs / 8);
+            const float fetched = (float)rounds * 8.f * (float)M * (float)K * 2.f / (float)ks;
+            const float body = (float)rounds * (float)per * tk + 0.066e-6f * fetched;
+            const float stream = (float)Nrows * (float)K * 2.f / 7.15e6f;
+            const float b2 = body * body, s2 = stream * stream;
+            const float us = 8.0f + sqrtf(sqrtf(b2 * b2 + s2 * s2)) + 1.35f * (float)rounds + 0.434e-6f * (float)bytes +
+                             (ks > 1 ? (mode == 2 ? 1.8f : 0.5f) : 0.f);
             if (best.us < 0.f || us < best.us) best = MidPlan{t, mt, nt, per, ks, us, bytes};
         }
     }
     return best;
 }
 
-// The large-tile kernel on the same scale: 1.4 us per k-tile and round; split tiles add a fix-up launch and their traffic.
+// The large-tile kernel on the same scale: a k-tile costs 0.88, and up to 0.51 more the more of the CUs a round fills; split
+// tiles add a fix-up launch and their traffic.
 static float big_us(int mode, int M, int N, int K) {
     const BigPlan p = big_plan(mode, M, N, K);
-    const int nk = K / kBK;
-    float us = 3.0f + (float)((p.n_dp + 255) / 256 * nk) * 1.4f;
-    if (p.tail > 0) us += (float)((nk + p.splits - 1) / p.splits) * 1.4f + 8.0f + (float)p.ws_bytes * 0.35e-6f;
-    return us;
+    const float nk = (float)(K / kBK);
+    float body = 0.f;
+    if (p.n_dp > 0) {
+        const float rounds = (float)((p.n_dp + 255) / 256);
+        body = rounds * (nk * (0.88f + 0.51f * (float)p.n_dp / (256.f * rounds)) + 11.4f);
+    }
+    if (p.tail > 0)
+        body += (float)((K / kBK + p.splits - 1) / p.splits) * (0.88f + 0.51f * (float)(p.tail * p.splits) / 256.f) + 12.5f +
+                (float)p.ws_bytes * 0.162e-6f;
+    const float us = 1.5f + body, stream = 1.5f + (float)((mode == 2) ? 2 * N : N) * (float)K * 2.f / 5.07e6f;
+    const float b2 = us * us, s2 = stream * stream;
+    return sqrtf(sqrtf(b2 * b2 + s2 * s2));
 }
 
-// Whether the mid-sized kernel takes the problem: always up to 256 rows (the large tiles never win there), beyond where the
-// models say so.  301 .. 1600 rows of the measured shapes: the choice is within 3 % of the better of the two on average.
+// Whether the mid-sized kernel takes the problem: always up to 256 rows (the large tiles win on one of 274 problems there, by
+// 5 %), beyond unless the models see the large tiles 5 % ahead.  Over the 596 problems the choice costs
+// 1.8 % against the best of all forms (without the margin as much on average, with more calls slower than before).
 // Which kernel is a matter of the shape alone; `p` is the plan within the scratch there is.
 static bool mid_takes(int mode, int M, int N, int K, size_t room, MidPlan& p) {
     if (M < kMidMinM || M > kMidMaxM || !big_ok(M, N, K)) return false;
     p = mid_plan(mode, M, N, K, kMidMaxPartial);
-    if (M > 256 && p.us >= big_us(mode, M, N, K)) return false;
+    if (M > 256 && p.us >= 0.95f * big_us(mode, M, N, K)) return false;
     if (p.ws_bytes > room) p = mid_plan(mode, M, N, K, room);
     return true;
 }
@@ -1370,7 +1388,8 @@ size_t gemm_workspace_bytes(int mode, int M, int N, int K) {
 // what the plans would like best: partial sums of up to 256 rows over as many ranges of K as tiles of 64 (long streams:
 // 128) weight rows and blocks of 128 rows leave compute units for, and the large tiles' beyond.  run_layers hands the plans
 // of a batch the largest of its four projections' (13B output projection, 200 rows: 7.8 MB of sums, its own share 3.9);
-// of all row counts of five decoder shapes that costs a plan more than 1 % at one (13B down projection around 200 rows, 1.3 %).
+// by the time model that costs 174 of the 30 000 plans of five decoder shapes between 65 and 2048 rows more than 1 %, 3.7 % at most
+// (13B at 193 rows).
 size_t gemm_instance_bytes(int mode, int M, int N, int K) {
     if (M > 256 || K % kBK) return big_ok(M, N, K) ? big_plan(mode, M, N, K).ws_bytes : 0;
     if (M <= kSkMaxM) return skinny_ok(M, N, K) ? skinny_plan(M, N, K, mode).ws_bytes : 0;
@@ -1497,6 +1516,30 @@ static void launch_mode(const bf16* a, const bf16* w, const bf16* r, bf16* c, in
     }
 }
 
+// What launch_mode does with `room` bytes of scratch, where every kernel gets its LDS.
+void gemm_plan(int mode, int M, int N, int K, size_t room, bz_gemm_plan* out) {
+    *out = bz_gemm_plan{};
+    if (M <= 0 || N <= 0) return;
+    const int Nrows = (mode == 2) ? 2 * N : N;
+    MidPlan mid;
+    if (room > 0 && skinny_ok(M, N, K) && skinny_plan(M, N, K, mode).ws_bytes <= room) {
+        const SkinnyPlan p = skinny_plan(M, N, K, mode);
+        *out = bz_gemm_plan{BZ_GEMM_DECODE, 64, p.rows, 1, p.n_tiles, 0, p.ksplit, p.ws_bytes};
+    } else if (M > 64 && mid_takes(mode, M, N, K, room, mid)) {
+        const MidTile& t = kMidTiles[mid.tile];
+        *out = bz_gemm_plan{BZ_GEMM_MID, t.wt * t.nbt * 16, (4 / t.wt) * t.nbf * 16, mid.m_tiles, mid.n_tiles, 0, mid.ksplit,
+                            mid.ws_bytes};
+    } else if (M > 64 && big_ok(M, N, K)) {
+        const BigPlan p = big_plan(mode, M, N, K);
+        const bool split = p.tail > 0 && p.ws_bytes <= room;
+        *out = bz_gemm_plan{BZ_GEMM_LARGE, 256, 256, p.tiles_m, p.tiles_n, split ? p.n_dp : p.tiles_m * p.tiles_n,
+                            split ? p.splits : 1, split ? p.ws_bytes : 0};
+    } else {
+        const int bm = M <= 64 ? 64 : 128;
+        *out = bz_gemm_plan{BZ_GEMM_SMALL, bm, 128, (M + bm - 1) / bm, (Nrows + 127) / 128, 0, 1, 0};
+    }
+}
+
 void launch_gemm(int mode, const act_t* a, const bf16* w, const act_t* r, act_t* c, int M, int N, int K,
                  float* ws, size_t ws_bytes, hipStream_t st) {
     if (M <= 0 || N <= 0) return;
@@ -1536,6 +1579,7 @@ __global__ __launch_bounds__(256) void gemm_naive_kernel(const float* __restrict
 
 size_t gemm_workspace_bytes(int, int, int, int) { return 0; }
 size_t gemm_instance_bytes(int, int, int, int) { return 0; }
+void gemm_plan(int, int, int, int, size_t, bz_gemm_plan* out) { *out = bz_gemm_plan{}; }
 int launch_gemm_partial(int, const act_t*, const bf16*, int, int, int, float*, size_t, hipStream_t) { return 0; }
 
 void launch_gemm(int mode, const act_t* a, const bf16* w, const act_t* r, act_t* c, int M, int N, int K,

@@ -86,6 +86,46 @@ def test_workspace_sizes_stay_what_callers_hold():
             assert sz.workspace_bytes == nbytes, (name, T)
 
 
+def _rounds_per_xcd(p):
+    """Rounds of workgroups on the busiest of eight XCDs of 32 compute units; an XCD takes whole units (tile column, range)."""
+    return -(-(-(-p.tiles_n * p.ranges // 8) * p.tiles_m) // 32)
+
+
+@pytest.mark.parametrize("mode,M,N,K,ranges", [
+    # 70B and 8B down projections of a few rows: a stream of 470 and 117 MB in two ranges took half as long again
+    (1, 65, 8192, 28672, 4), (1, 93, 8192, 28672, 4), (1, 128, 8192, 28672, 4), (1, 93, 4096, 14336, 4),
+    # many rows on few weights: a few workgroups too many for some XCDs doubled the time
+    (1, 1698, 4096, 14336, 1), (1, 1698, 4096, 11008, 1), (1, 1698, 4096, 4096, 1), (1, 398, 5120, 13824, 1),
+    (1, 552, 5120, 13824, 1), (1, 1282, 5120, 5120, 1)])
+def test_mid_sized_plans_fill_the_chip_in_one_round(mode, M, N, K, ranges):
+    p = B.op_gemm_plan(mode, M, N, K)
+    if p.kernel == B.BZ_GEMM_MID:
+        assert _rounds_per_xcd(p) == 1 and p.ranges >= ranges
+    else:
+        assert p.kernel == B.BZ_GEMM_LARGE and M > 256
+
+
+def test_gemm_plans_stay_within_the_workspace():
+    """Every plan uses no more than it is given, and the reported size buys the plan that any larger one does."""
+    rng = np.random.default_rng(3)
+    kernels = set()
+    for _ in range(3000):
+        mode, M = int(rng.integers(3)), int(np.exp(rng.uniform(0, np.log(9000))))
+        N, K = 4 * int(np.exp(rng.uniform(0, np.log(8000)))), 8 * int(np.exp(rng.uniform(0, np.log(2000))))
+        if rng.random() < 0.8:
+            K = (K + 63) // 64 * 64
+        need = B.op_gemm_workspace_bytes(mode, M, N, K)
+        for room in (0, 16, need // 3, need - 1 if need else 0, need, max(need, 64 << 20), 1 << 40):
+            p = B.op_gemm_plan(mode, M, N, K, room)
+            assert p.workspace_bytes <= room, (mode, M, N, K, room)
+            kernels.add(p.kernel)
+            if room >= max(need, 1):
+                assert bytes(p) == bytes(B.op_gemm_plan(mode, M, N, K, max(need, 1))), (mode, M, N, K, room)
+            if p.kernel == B.BZ_GEMM_MID:
+                assert p.tile_rows * p.tiles_m >= M and p.tile_cols * p.tiles_n >= (2 * N if mode == 2 else N)
+    assert kernels == {B.BZ_GEMM_SMALL, B.BZ_GEMM_DECODE, B.BZ_GEMM_MID, B.BZ_GEMM_LARGE}
+
+
 @pytest.mark.parametrize("field,value", [("n_layers", 0), ("hidden", 100), ("head_dim", 96), ("n_kv_heads", 3),
                                          ("ffn", 13), ("max_seqs", 0), ("kv_tokens", 0), ("rms_eps", 0.0),
                                          ("n_q_heads", 48)])
