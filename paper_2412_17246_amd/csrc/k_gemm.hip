@@ -1371,8 +1371,17 @@ static bool skinny_ok(int M, int N, int K) {
            (uint64_t)2 * N * K < 0x7fffffffull;          // 32-bit byte offsets into the weights (2N rows in gate/up mode)
 }
 
+// Short K tails as single products stay with the 64x128 kernel: the decode kernel needs a second launch for the fold and the
+// epilogue.  Plain epilogue 6.4 -> 8.5 us at K = 8 to 88, 8.1 and 8.6 at 168, 9.8 and 9.8 at 216; with the residual, whose
+// loads grow with the rows in the 64x128 kernel's epilogue, 6.7 -> 9.0 (one row, K = 24), 8.4 and 9.0 (3 rows, 104), 9.9 and
+// 8.9 (12 rows, 40), 16.5 and 9 (45 rows).  Gate/up writes its result itself and is never slower.  (In run_layers
+// the next step folds the sums, so there it is one launch either way: launch_gemm_partial.)
+static bool short_tail(int mode, int M, int K) {
+    return K % kBK != 0 && ((mode == 0 && K < 192) || (mode == 1 && M <= 8 && K < 128));
+}
+
 size_t gemm_workspace_bytes(int mode, int M, int N, int K) {
-    if (skinny_ok(M, N, K)) return skinny_plan(M, N, K, mode).ws_bytes;
+    if (skinny_ok(M, N, K)) return short_tail(mode, M, K) ? 0 : skinny_plan(M, N, K, mode).ws_bytes;
     MidPlan p;
     if (mid_takes(mode, M, N, K, kMidMaxPartial, p)) {
         // Up to 256 rows a problem whose output, as one range's sums, is larger than the static scratch is reported with
@@ -1503,7 +1512,7 @@ static void launch_mode(const bf16* a, const bf16* w, const bf16* r, bf16* c, in
                         size_t ws_bytes, hipStream_t st) {
     // The kernel and its tiling are a function of the problem shape only, so a layer's result never
     // depends on which range of layers a call covers.
-    if (skinny_applies(MODE, M, N, K, ws, ws_bytes)) {
+    if (skinny_applies(MODE, M, N, K, ws, ws_bytes) && !short_tail(MODE, M, K)) {
         launch_skinny<MODE>(a, w, r, c, M, N, K, ws, st);
     } else if (M <= 64) {
         launch_cfg<64, 128, 2, 2, MODE>(a, w, r, c, M, N, K, st);
@@ -1522,7 +1531,7 @@ void gemm_plan(int mode, int M, int N, int K, size_t room, bz_gemm_plan* out) {
     if (M <= 0 || N <= 0) return;
     const int Nrows = (mode == 2) ? 2 * N : N;
     MidPlan mid;
-    if (room > 0 && skinny_ok(M, N, K) && skinny_plan(M, N, K, mode).ws_bytes <= room) {
+    if (room > 0 && skinny_ok(M, N, K) && skinny_plan(M, N, K, mode).ws_bytes <= room && !short_tail(mode, M, K)) {
         const SkinnyPlan p = skinny_plan(M, N, K, mode);
         *out = bz_gemm_plan{BZ_GEMM_DECODE, 64, p.rows, 1, p.n_tiles, 0, p.ksplit, p.ws_bytes};
     } else if (M > 64 && mid_takes(mode, M, N, K, room, mid)) {

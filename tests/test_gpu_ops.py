@@ -130,7 +130,8 @@ def test_gemm_mid_sized_edges(torch, mode, M, N, K):
 
 
 @pytest.mark.parametrize("mode", [0, 1, 2])
-@pytest.mark.parametrize("M,N,K", [(1, 256, 688), (64, 36, 8), (17, 68, 72), (5, 2048, 1016), (33, 9216, 4104)])
+@pytest.mark.parametrize("M,N,K", [(1, 256, 688), (64, 36, 8), (17, 68, 72), (5, 2048, 1016), (33, 9216, 4104),
+                                   (64, 36, 200), (17, 68, 328), (9, 132, 248), (1, 4, 440)])
 def test_gemm_decode_sized_k_tails(torch, mode, M, N, K):
     """The decode kernel where K is no multiple of its 64-wide tiles: a tail of one to seven 8-element pieces, alone, in a
     range of its own and behind others; small matrices and (last) the 128-row tiles of the long streams."""

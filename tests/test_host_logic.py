@@ -105,6 +105,17 @@ def test_mid_sized_plans_fill_the_chip_in_one_round(mode, M, N, K, ranges):
         assert p.kernel == B.BZ_GEMM_LARGE and M > 256
 
 
+@pytest.mark.parametrize("mode,M,N,K,kernel", [
+    (0, 5, 212, 24, B.BZ_GEMM_SMALL), (0, 48, 128, 168, B.BZ_GEMM_SMALL), (0, 11, 2108, 232, B.BZ_GEMM_DECODE),
+    (0, 5, 212, 64, B.BZ_GEMM_DECODE), (1, 8, 80, 24, B.BZ_GEMM_SMALL), (1, 9, 80, 24, B.BZ_GEMM_DECODE),
+    (1, 8, 80, 168, B.BZ_GEMM_DECODE), (2, 5, 116, 8, B.BZ_GEMM_DECODE)])
+def test_short_k_tails_are_one_launch(mode, M, N, K, kernel):
+    """The decode kernel's second launch costs more than it saves where K is short."""
+    assert B.op_gemm_plan(mode, M, N, K, 64 << 20).kernel == kernel
+    if kernel == B.BZ_GEMM_SMALL:
+        assert B.op_gemm_workspace_bytes(mode, M, N, K) == 0
+
+
 def test_gemm_plans_stay_within_the_workspace():
     """Every plan uses no more than it is given, and the reported size buys the plan that any larger one does."""
     rng = np.random.default_rng(3)
