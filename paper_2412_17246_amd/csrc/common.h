@@ -120,6 +120,32 @@ __device__ __forceinline__ void reduce8(const float* __restrict__ partial, int k
     }
 }
 
+// The same for the two halves of a rotation, `half` values apart, whose loads go out together.
+__device__ __forceinline__ void reduce8_pair(const float* __restrict__ partial, int ksplit, size_t slice_stride, size_t off,
+                                             int half, float (&lo)[8], float (&hi)[8]) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) lo[e] = hi[e] = 0.f;
+    for (int k0 = 0; k0 < ksplit; k0 += 4) {
+        float4 v[4][4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float* p = partial + (k0 + u < ksplit ? k0 + u : ksplit - 1) * slice_stride + off;
+            v[u][0] = *reinterpret_cast<const float4*>(p);
+            v[u][1] = *reinterpret_cast<const float4*>(p + 4);
+            v[u][2] = *reinterpret_cast<const float4*>(p + half);
+            v[u][3] = *reinterpret_cast<const float4*>(p + half + 4);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (k0 + u < ksplit) {
+                lo[0] += v[u][0].x; lo[1] += v[u][0].y; lo[2] += v[u][0].z; lo[3] += v[u][0].w;
+                lo[4] += v[u][1].x; lo[5] += v[u][1].y; lo[6] += v[u][1].z; lo[7] += v[u][1].w;
+                hi[0] += v[u][2].x; hi[1] += v[u][2].y; hi[2] += v[u][2].z; hi[3] += v[u][2].w;
+                hi[4] += v[u][3].x; hi[5] += v[u][3].y; hi[6] += v[u][3].z; hi[7] += v[u][3].w;
+            }
+    }
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
@@ -218,8 +244,9 @@ void launch_reduce_residual_rmsnorm(act_t* x, const float* partial, int ksplit, 
 // Rotary embedding (table `rope_tab`: [max_seq_len][d/2] pairs of cos, sin) and the append to the cache are shared out so
 // that the projection is read once and the rotated queries never travel through memory: launch_kv_append takes the keys
 // and values of the sequences with several new tokens, the prefill kernel rotates its queries as it loads them, and the
-// decode kernel does both for its one token per sequence.  (fp32 debug build: launch_kv_append does it all.)
-// launch_kv_append comes first.
+// decode kernel does both for its one token per sequence.  Where the projection is partial sums, launch_kv_append also folds
+// and rotates the queries of those sequences into `qkv`: in the prefill kernel every lane would fold a row of its own, line by
+// line.  (fp32 debug build: launch_kv_append does it all.)  launch_kv_append comes first.
 bool kv_append_needed(const BatchView& bv);
 void launch_kv_append(const QkvSource& src, const float* rope_tab, const BatchView& bv, const KvView& kv, int Hq,
                       hipStream_t st);

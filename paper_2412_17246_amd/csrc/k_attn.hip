@@ -47,27 +47,21 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // vector and the matrix work of all its waves add up), so a grid that leaves CUs idle gains by halving the chains.
 // ---------------------------------------------------------------------------------------------
 // A lane's query fragments qf[ks] hold dims 16 ks + 8 lh + 0..7 of one row, so both halves of a rotation pair (j, j + D/2)
-// are in the same lane: the query is rotated as it is loaded.
-template <int D, bool REDUCE>
-__device__ __forceinline__ void load_rotated_query(const QkvSource& src, size_t at, size_t slice, const float* cs,
-                                                   bf16x8 (&qf)[D / 16], int lh) {
+// are in the same lane: the query is rotated as it is loaded.  ROTATED: it already is (launch_kv_append).
+template <int D, bool ROTATED>
+__device__ __forceinline__ void load_query(const bf16* q, const float* cs, bf16x8 (&qf)[D / 16], int lh) {
     constexpr int H = D / 32;                                 // fragments per half of the head
+    if (ROTATED) {
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(q + ks * 16 + lh * 8);
+        return;
+    }
 #pragma unroll
     for (int ks = 0; ks < H; ++ks) {
         const int j = ks * 16 + lh * 8;
         float lo[8], hi[8];
-        if (REDUCE) {
-            reduce8(src.partial, src.ksplit, slice, at + j, lo);
-            reduce8(src.partial, src.ksplit, slice, at + D / 2 + j, hi);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                lo[e] = (float)(bf16)lo[e];
-                hi[e] = (float)(bf16)hi[e];
-            }
-        } else {
-            load8(src.qkv + at + j, lo);
-            load8(src.qkv + at + D / 2 + j, hi);
-        }
+        load8(q + j, lo);
+        load8(q + D / 2 + j, hi);
 #pragma unroll
         for (int e = 0; e < 8; e += 2) {
             const float4 v = *reinterpret_cast<const float4*>(cs + 2 * (j + e));
@@ -79,8 +73,8 @@ __device__ __forceinline__ void load_rotated_query(const QkvSource& src, size_t 
     }
 }
 
-template <int D, bool REDUCE, int SETS>
-__global__ __launch_bounds__(256, 2) void attn_prefill_kernel(QkvSource qkv, const float* __restrict__ tab,
+template <int D, bool ROTATED, int SETS>
+__global__ __launch_bounds__(256, 2) void attn_prefill_kernel(const bf16* __restrict__ qkv, const float* __restrict__ tab,
                                                               bf16* __restrict__ out, BatchView bv, KvView kv, int Hq,
                                                               float scale_log2) {
     constexpr int RW = 4 / SETS;         // waves along the rows
@@ -179,7 +173,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(QkvSource qkv, con
     issue(set, 0);
 
     bf16x8 qf[KS];
-    load_rotated_query<D, REDUCE>(qkv, (size_t)(q0 + qic) * nqkv + h * D, (size_t)bv.T * nqkv, tab + (size_t)qpos * D, qf, lh);
+    load_query<D, ROTATED>(qkv + (size_t)(q0 + qic) * nqkv + h * D, tab + (size_t)qpos * D, qf, lh);
 
     f32x16 o[DB];
 #pragma unroll
@@ -330,15 +324,15 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(QkvSource qkv, con
     }
 }
 
-template <int D, bool REDUCE, int SETS>
-static void launch_prefill_sets(const QkvSource& qkv, const float* rope_tab, act_t* out, const BatchView& bv, const KvView& kv,
+template <int D, bool ROTATED, int SETS>
+static void launch_prefill_sets(const act_t* qkv, const float* rope_tab, act_t* out, const BatchView& bv, const KvView& kv,
                                 int Hq, hipStream_t st) {
     constexpr int kLds = SETS * 2 * 4 * 32 * D * (int)sizeof(bf16);     // per set two stages of (K tile + V tile)
     static LdsLimit limit;
-    if (!limit.raise(reinterpret_cast<const void*>(attn_prefill_kernel<D, REDUCE, SETS>), kLds) && SETS > 1)
-        return launch_prefill_sets<D, REDUCE, 1>(qkv, rope_tab, out, bv, kv, Hq, st);
+    if (!limit.raise(reinterpret_cast<const void*>(attn_prefill_kernel<D, ROTATED, SETS>), kLds) && SETS > 1)
+        return launch_prefill_sets<D, ROTATED, 1>(qkv, rope_tab, out, bv, kv, Hq, st);
     const float scale_log2 = kLog2e / sqrtf((float)D);
-    hipLaunchKernelGGL((attn_prefill_kernel<D, REDUCE, SETS>), dim3(bv.n_prefill_items * Hq * SETS), dim3(256), kLds, st, qkv,
+    hipLaunchKernelGGL((attn_prefill_kernel<D, ROTATED, SETS>), dim3(bv.n_prefill_items * Hq * SETS), dim3(256), kLds, st, qkv,
                        rope_tab, out, bv, kv, Hq, scale_log2);
 }
 
@@ -347,20 +341,20 @@ static void launch_prefill_sets(const QkvSource& qkv, const float* rope_tab, act
 // tiles 12.2 -> 12.5, one tile x 4 heads of one KV tile (d = 64) 7.2 -> 9.7.  (The second set as four more waves on the same
 // CU: 78 -> 71 and 12.2 -> 16.9.)
 constexpr int kLongKeys = 512;
-template <int D, bool REDUCE>
-static void launch_prefill_d(const QkvSource& qkv, const float* rope_tab, act_t* out, const BatchView& bv, const KvView& kv,
+template <int D, bool ROTATED>
+static void launch_prefill_d(const act_t* qkv, const float* rope_tab, act_t* out, const BatchView& bv, const KvView& kv,
                              int Hq, hipStream_t st) {
     if (bv.n_prefill_items * Hq <= 128 && bv.prefill_keys > kLongKeys)
-        launch_prefill_sets<D, REDUCE, 2>(qkv, rope_tab, out, bv, kv, Hq, st);
-    else launch_prefill_sets<D, REDUCE, 1>(qkv, rope_tab, out, bv, kv, Hq, st);
+        launch_prefill_sets<D, ROTATED, 2>(qkv, rope_tab, out, bv, kv, Hq, st);
+    else launch_prefill_sets<D, ROTATED, 1>(qkv, rope_tab, out, bv, kv, Hq, st);
 }
 
-void launch_attn_prefill(const QkvSource& qkv, const float* rope_tab, act_t* out, const BatchView& bv, const KvView& kv,
+void launch_attn_prefill(const QkvSource& src, const float* rope_tab, act_t* out, const BatchView& bv, const KvView& kv,
                          int Hq, hipStream_t st) {
     if (bv.n_prefill_items <= 0) return;
-    const bool sums = qkv.partial != nullptr;
-    if (kv.d == 128) (sums ? launch_prefill_d<128, true> : launch_prefill_d<128, false>)(qkv, rope_tab, out, bv, kv, Hq, st);
-    else (sums ? launch_prefill_d<64, true> : launch_prefill_d<64, false>)(qkv, rope_tab, out, bv, kv, Hq, st);
+    const bool rotated = src.partial != nullptr;
+    if (kv.d == 128) (rotated ? launch_prefill_d<128, true> : launch_prefill_d<128, false>)(src.qkv, rope_tab, out, bv, kv, Hq, st);
+    else (rotated ? launch_prefill_d<64, true> : launch_prefill_d<64, false>)(src.qkv, rope_tab, out, bv, kv, Hq, st);
 }
 
 #else  // BZ_FP32_DEBUG

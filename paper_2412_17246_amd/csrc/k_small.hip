@@ -125,17 +125,67 @@ void launch_reduce_residual_rmsnorm(act_t* x, const float* partial, int ksplit, 
 // (the queries' share went to the prefill kernel): 13B shape, 14 091 rows 226 -> 109 us (5.3 TB/s) and 30 more there, 70B, 8192
 // rows 62 -> 18 and 32, 7B, 4973 rows 64 -> 42 and 11.
 //
+// Partial sums (few rows): the loads of several slices and rows go out together, and queries are folded and rotated here by
+// workgroups of their own, coalesced.  Folded row by row with one slice's load behind the other, and the queries by every
+// lane of the prefill kernel, the append and the attention took, one kernel after the other, 34.8 us (17 rows, 16 + 2 heads
+// of 128, six slices), 26.4 (129 rows, 16 + 4 of 64) and 31.7 (2 x 20 rows on 500 positions, 70B); now 12.5, 13.2 and 20.5.
+//
 // Item i of the prefill list (sequence, tile of 128 new rows) covers the blocks first + 4 * tile + 0..3 of its sequence;
 // an unaligned start can make the sequence touch one block more, which the last item's fifth workgroup takes.
 // ---------------------------------------------------------------------------------------------
 #ifndef BZ_FP32_DEBUG
 constexpr int kAppendBlocks = 5;
 
+__device__ __forceinline__ void load_cos_sin(const float* cs, float (&c8)[8], float (&s8)[8]) {
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+        const float4 v = *reinterpret_cast<const float4*>(cs + 2 * e);
+        c8[e] = v.x; s8[e] = v.y; c8[e + 1] = v.z; s8[e + 1] = v.w;
+    }
+}
+
+// 8 rotated pairs (j, j + half) of the projection's values from `at` on
+template <bool REDUCE>
+__device__ __forceinline__ void rotated_pair(const QkvSource& src, size_t slice, size_t at, int half, const float (&c8)[8],
+                                             const float (&s8)[8], float (&o_lo)[8], float (&o_hi)[8]) {
+    float lo[8], hi[8];
+    if (REDUCE) {
+        reduce8_pair(src.partial, src.ksplit, slice, at, half, lo, hi);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            lo[e] = (float)(bf16)lo[e];
+            hi[e] = (float)(bf16)hi[e];
+        }
+    } else {
+        load8(src.qkv + at, lo);
+        load8(src.qkv + at + half, hi);
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        o_lo[e] = lo[e] * c8[e] - hi[e] * s8[e];
+        o_hi[e] = hi[e] * c8[e] + lo[e] * s8[e];
+    }
+}
+
+// REDUCE: workgroups from `kv_wgs` on fold and rotate queries, `q_wgs` of them per row.
 template <bool REDUCE>
 __global__ __launch_bounds__(256) void kv_append_kernel(QkvSource src, const float* __restrict__ tab, BatchView bv,
-                                                        KvView kv, int Hq, int heads_per_wg, int hgroups) {
+                                                        KvView kv, int Hq, int heads_per_wg, int hgroups, int kv_wgs, int q_wgs) {
     const int d = kv.d, Hkv = kv.Hkv, half = d >> 1;
     const int nqkv = (Hq + 2 * Hkv) * d;
+    if (REDUCE && (int)blockIdx.x >= kv_wgs) {
+        const int b = blockIdx.x - kv_wgs, t = b / q_wgs, u = (b - t * q_wgs) * 256 + (int)threadIdx.x;
+        const int seq = bv.token_seq[t], first = bv.q_start[seq];
+        if (bv.q_start[seq + 1] - first < 2 || u >= Hq * (d >> 4)) return;
+        const int head = u / (d >> 4), j = (u - head * (d >> 4)) * 8;
+        float c8[8], s8[8], o_lo[8], o_hi[8];
+        load_cos_sin(tab + (size_t)(bv.kv_before[seq] + t - first) * d + 2 * j, c8, s8);
+        const size_t at = (size_t)t * nqkv + head * d + j;
+        rotated_pair<true>(src, (size_t)bv.T * nqkv, at, half, c8, s8, o_lo, o_hi);
+        store8(src.qkv + at, o_lo);
+        store8(src.qkv + at + half, o_hi);
+        return;
+    }
     const int item = blockIdx.x / (kAppendBlocks * hgroups);
     const int rest = blockIdx.x - item * (kAppendBlocks * hgroups);
     const int sub = rest / hgroups, hg = rest - sub * hgroups;
@@ -164,31 +214,11 @@ __global__ __launch_bounds__(256) void kv_append_kernel(QkvSource src, const flo
         const size_t row = (size_t)(q0 + pos - before) * nqkv;
         const float* cs = tab + (size_t)pos * d + unit * 16;
         float c8[8], s8[8];
-#pragma unroll
-        for (int e = 0; e < 8; e += 2) {
-            const float4 v = *reinterpret_cast<const float4*>(cs + 2 * e);
-            c8[e] = v.x; s8[e] = v.y; c8[e + 1] = v.z; s8[e + 1] = v.w;
-        }
+        load_cos_sin(cs, c8, s8);
         for (int h = h0; h < h1; h += n_par) {
             const size_t at = row + (size_t)(Hq + h) * d + unit * 8;
-            float lo[8], hi[8], o_lo[8], o_hi[8];
-            if (REDUCE) {
-                reduce8(src.partial, src.ksplit, slice, at, lo);
-                reduce8(src.partial, src.ksplit, slice, at + half, hi);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    lo[e] = (float)(bf16)lo[e];
-                    hi[e] = (float)(bf16)hi[e];
-                }
-            } else {
-                load8(src.qkv + at, lo);
-                load8(src.qkv + at + half, hi);
-            }
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                o_lo[e] = lo[e] * c8[e] - hi[e] * s8[e];
-                o_hi[e] = hi[e] * c8[e] + lo[e] * s8[e];
-            }
+            float o_lo[8], o_hi[8];
+            rotated_pair<REDUCE>(src, slice, at, half, c8, s8, o_lo, o_hi);
             bf16* dst = kv.k + block_base + (size_t)h * head_stride + p * 8;
             store8(dst + unit * 256, o_lo);
             store8(dst + (unit + uph) * 256, o_hi);
@@ -201,22 +231,39 @@ __global__ __launch_bounds__(256) void kv_append_kernel(QkvSource src, const flo
     for (int h = h0; h < h1; h += n_par) {
         const size_t col = (size_t)(Hq + Hkv + h) * d + j;
         float a[8], b[8];
+        size_t at[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             int pe = pbase + (e & 3) + 8 * (e >> 2);
             pe = pe < p_lo ? p_lo : pe > p_hi - 1 ? p_hi - 1 : pe;            // read in bounds, not stored
-            const size_t at = (size_t)(q0 + pe - before) * nqkv + col;
-            if (REDUCE) {
-                float2 acc = make_float2(0.f, 0.f);
-                for (int k = 0; k < src.ksplit; ++k) {
-                    const float2 v = *reinterpret_cast<const float2*>(src.partial + k * slice + at);
-                    acc.x += v.x;
-                    acc.y += v.y;
+            at[e] = (size_t)(q0 + pe - before) * nqkv + col;
+            a[e] = b[e] = 0.f;
+        }
+        if (REDUCE) {
+            // two slices' loads of all eight rows go out together (row by row, each waited for the one before)
+            for (int k = 0; k < src.ksplit; k += 2) {
+                const float* s0 = src.partial + k * slice;
+                const float* s1 = k + 1 < src.ksplit ? s0 + slice : s0;
+                float2 v[2][8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    v[0][e] = *reinterpret_cast<const float2*>(s0 + at[e]);
+                    v[1][e] = *reinterpret_cast<const float2*>(s1 + at[e]);
                 }
-                a[e] = acc.x;
-                b[e] = acc.y;
-            } else {
-                const bf16x2 v = *reinterpret_cast<const bf16x2*>(src.qkv + at);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    a[e] += v[0][e].x;
+                    b[e] += v[0][e].y;
+                    if (k + 1 < src.ksplit) {
+                        a[e] += v[1][e].x;
+                        b[e] += v[1][e].y;
+                    }
+                }
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const bf16x2 v = *reinterpret_cast<const bf16x2*>(src.qkv + at[e]);
                 a[e] = (float)v[0];
                 b[e] = (float)v[1];
             }
@@ -250,8 +297,13 @@ void launch_kv_append(const QkvSource& src, const float* rope_tab, const BatchVi
     int hpw = (int)((int64_t)blocks * kv.Hkv / 4096);
     hpw = hpw < n_par ? n_par : hpw > 8 ? 8 : hpw;
     const int hgroups = (kv.Hkv + hpw - 1) / hpw;
-    auto kern = src.partial ? kv_append_kernel<true> : kv_append_kernel<false>;
-    hipLaunchKernelGGL(kern, dim3(blocks * hgroups), dim3(256), 0, st, src, rope_tab, bv, kv, Hq, hpw, hgroups);
+    const int kv_wgs = blocks * hgroups, q_wgs = (Hq * (kv.d >> 4) + 255) / 256;
+    if (src.partial)
+        hipLaunchKernelGGL(kv_append_kernel<true>, dim3(kv_wgs + bv.T * q_wgs), dim3(256), 0, st, src, rope_tab, bv, kv, Hq, hpw,
+                           hgroups, kv_wgs, q_wgs);
+    else
+        hipLaunchKernelGGL(kv_append_kernel<false>, dim3(kv_wgs), dim3(256), 0, st, src, rope_tab, bv, kv, Hq, hpw, hgroups,
+                           kv_wgs, q_wgs);
 }
 
 #else  // BZ_FP32_DEBUG: one workgroup per token rotates its queries in place, and its keys into the cache, and copies its values
