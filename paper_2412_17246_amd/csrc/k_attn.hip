@@ -337,10 +337,11 @@ static void launch_prefill_sets(const act_t* qkv, const float* rope_tab, act_t* 
 }
 
 // 64-row workgroups with two sets of waves while a CU gets one of them at most and the chains are long enough to pay for
-// the merge.  128-row tiles against these, per layer: 4 tiles x 32 heads of 55 KV tiles 78 -> 56 us, 3 x 32 of 3 to 5 KV
-// tiles 12.2 -> 12.5, one tile x 4 heads of one KV tile (d = 64) 7.2 -> 9.7.  (The second set as four more waves on the same
-// CU: 78 -> 71 and 12.2 -> 16.9.)
-constexpr int kLongKeys = 512;
+// the merge: from four KV tiles on.  Their time over that of 128-row tiles (seven head counts of both sizes, 20 to 512 rows in one
+// or two sequences): 1.21 at one KV tile, 1.02 at two and three (0.93 to 1.14), 0.91 at four (0.84 to 1.02), 0.93 at five, 0.81 at
+// eight, 0.72 at 16, 0.63 at 56.  (The second set as four more waves on the same CU: 78 -> 71 us instead of 56 at 55 tiles, and
+// 12.2 -> 16.9 at 3 to 5.)
+constexpr int kLongKeys = 192;
 template <int D, bool ROTATED>
 static void launch_prefill_d(const act_t* qkv, const float* rope_tab, act_t* out, const BatchView& bv, const KvView& kv,
                              int Hq, hipStream_t st) {

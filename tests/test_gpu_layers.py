@@ -312,6 +312,18 @@ def test_few_prefill_tiles_over_long_caches(torch, shape, rows):
         assert U.rel_err(got[a:b], want[a:b]) <= _tol(False), (i, seqs[i])
 
 
+@pytest.mark.parametrize("longest", [192, 193, 256, 257, 321])
+@pytest.mark.parametrize("shape", [MIX, MIX64, H24], ids=lambda s: s.name)
+def test_few_prefill_tiles_where_the_two_key_sets_begin(torch, shape, longest):
+    # the longest key range on either side of the line between the two kernels, next to sequences of one and two KV tiles, of
+    # which the second set sees nothing or one tile
+    seqs = [(65, longest - 65), (2, 10), (33, 90), (5, 0)]
+    got, want, q_start = _mixed_case(torch, shape, False, seqs)
+    for i in range(len(seqs)):
+        a, b = q_start[i], q_start[i + 1]
+        assert U.rel_err(got[a:b], want[a:b]) <= _tol(False), (i, seqs[i])
+
+
 def _random_case(case):
     """A seeded random decoder shape (head size, heads per group, widths that are multiples of 8 only) and batch."""
     import random
