@@ -135,7 +135,11 @@ typedef struct bz_stats {
     int32_t  reserved;
 } bz_stats;
 
-/* Kernel classes for bz_profile_read. */
+/* Kernel classes for bz_profile_read.  BZ_K_ROPE_APPEND takes the sequences with several new tokens (their
+ * keys and values; their queries too where the projection is split over K).  Single new tokens are rotated
+ * and appended inside BZ_K_ATTN_DECODE, other queries inside BZ_K_ATTN_PREFILL, and neither class counts that:
+ * a batch of decode steps alone has no BZ_K_ROPE_APPEND launches.  (fp32 debug build: every row, queries
+ * included, in BZ_K_ROPE_APPEND.)  BZ_K_ATTN_DECODE includes the merge of a sequence's chunks. */
 enum {
     BZ_K_RMSNORM = 0, BZ_K_GEMM_QKV, BZ_K_ROPE_APPEND, BZ_K_ATTN_PREFILL, BZ_K_ATTN_DECODE,
     BZ_K_ATTN_COMBINE, BZ_K_GEMM_O, BZ_K_GEMM_GATEUP, BZ_K_GEMM_DOWN, BZ_K_COUNT

@@ -248,6 +248,7 @@ void launch_reduce_residual_rmsnorm(act_t* x, const float* partial, int ksplit, 
 // and rotates the queries of those sequences into `qkv`: in the prefill kernel every lane would fold a row of its own, line by
 // line.  (fp32 debug build: launch_kv_append does it all.)  launch_kv_append comes first.
 bool kv_append_needed(const BatchView& bv);
+int kv_append_skips(const BatchView& bv);       // rows of the batch that the decode kernel appends
 void launch_kv_append(const QkvSource& src, const float* rope_tab, const BatchView& bv, const KvView& kv, int Hq,
                       hipStream_t st);
 void launch_attn_prefill(const QkvSource& src, const float* rope_tab, act_t* out, const BatchView& bv, const KvView& kv,

@@ -1078,7 +1078,9 @@ int bz_run_layers(bz_instance* I, int a, int b, const bz_batch* batch, void* hid
           if (ks_qkv == 0) launch_gemm(0, normed, wqkv, nullptr, qkv, T, nqkv, sh.H, gws, gwsb, st); }
         const QkvSource projected{qkv, ks_qkv > 0 ? gws : nullptr, ks_qkv};
         if (kv_append_needed(bv)) {
-            ProfScope p(I, BZ_K_ROPE_APPEND, 3.0 * T * sh.Hkv * sh.d, (double)T * 4.0 * sh.Hkv * sh.d * e);
+            // keys and values of the rows it takes, and the queries where it rotates them too
+            const double rows = T - kv_append_skips(bv), hq = ks_qkv > 0 || sizeof(act_t) == 4 ? sh.Hq : 0;
+            ProfScope p(I, BZ_K_ROPE_APPEND, 3.0 * rows * (hq + sh.Hkv) * sh.d, rows * (2.0 * hq + 4.0 * sh.Hkv) * sh.d * e);
             launch_kv_append(projected, rope, bv, kvv, sh.Hq, st);
         }
         if (bv.n_prefill_items > 0) {

@@ -286,6 +286,7 @@ __global__ __launch_bounds__(256) void kv_append_kernel(QkvSource src, const flo
 }
 
 bool kv_append_needed(const BatchView& bv) { return bv.n_prefill_items > 0; }
+int kv_append_skips(const BatchView& bv) { return bv.n_decode; }
 
 void launch_kv_append(const QkvSource& src, const float* rope_tab, const BatchView& bv, const KvView& kv, int Hq,
                       hipStream_t st) {
@@ -337,6 +338,7 @@ __global__ __launch_bounds__(256) void rope_append_kernel(float* __restrict__ qk
 }
 
 bool kv_append_needed(const BatchView& bv) { return bv.T > 0; }
+int kv_append_skips(const BatchView&) { return 0; }
 
 void launch_kv_append(const QkvSource& src, const float* rope_tab, const BatchView& bv, const KvView& kv, int Hq,
                       hipStream_t st) {

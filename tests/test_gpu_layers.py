@@ -324,6 +324,30 @@ def test_few_prefill_tiles_where_the_two_key_sets_begin(torch, shape, longest):
         assert U.rel_err(got[a:b], want[a:b]) <= _tol(False), (i, seqs[i])
 
 
+@pytest.mark.parametrize("fp32", [False, True], ids=["bf16", "fp32dbg"])
+def test_profile_books_the_append_over_the_rows_it_takes(torch, fp32):
+    s, e = MIX, 4 if fp32 else 2
+    for seqs in ([(40, 0), (1, 30), (1, 700)], [(300, 5), (1, 9)], [(1, 30), (1, 500)]):
+        T, prompt_rows = sum(n for n, _ in seqs), sum(n for n, _ in seqs if n > 1)
+        inst = U.make_instance(s, max_seqs=3, max_seq_len=800, max_tokens=T, kv_tokens=2048, fp32=fp32)
+        U.load_all_layers(inst, s)
+        for i, (n, before) in enumerate(seqs):
+            inst.kv_reserve(i, n + before)
+        x = U.to_device(W.hidden_bits(s, T), fp32)
+        batch = inst.batch(np.concatenate([[0], np.cumsum([n for n, _ in seqs])]), list(range(len(seqs))), [b for _, b in seqs])
+        torch.cuda.synchronize()
+        inst.profile_enable(True)
+        inst.run_layers(0, s.L, batch, x)
+        inst.sync()
+        got = inst.profile_read()["rope_append"]
+        inst.close()
+        rows = T if fp32 else prompt_rows
+        queries = s.Hq if fp32 or T <= 64 else 0             # up to 64 rows the projection is split over K
+        assert got["launches"] == (s.L if rows else 0)
+        assert got["bytes"] == s.L * rows * (2 * queries + 4 * s.Hkv) * s.d * e
+        assert got["flops"] == s.L * rows * 3 * (queries + s.Hkv) * s.d
+
+
 def _random_case(case):
     """A seeded random decoder shape (head size, heads per group, widths that are multiples of 8 only) and batch."""
     import random
