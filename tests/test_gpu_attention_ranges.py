@@ -136,3 +136,36 @@ def test_decode_weights_below_the_normal_range_count(torch, d):
     large = np.abs(want - plain) > 0.5 * np.abs(want - plain).max()
     factor = (got - plain)[large] / (want - plain)[large]
     assert 2.0 ** -0.8 < factor.min() and factor.max() < 2.0 ** 0.8, (factor.min(), factor.max())
+
+
+def _tile(keys):
+    return np.arange(keys) // 64
+
+
+# offsets of the keys, in powers of two, by KV tile of 64 positions
+RISES = {
+    "rising": lambda k: 12.0 * _tile(k),                                    # every tile moves every row's maximum
+    "falling": lambda k: 12.0 * (_tile(k).max() - _tile(k)),
+    "odd tiles": lambda k: np.where(_tile(k) % 2 == 1, 40.0, 0.0),          # two key sets: the second one's dominate
+    "even tiles": lambda k: np.where(_tile(k) % 2 == 0, 40.0, 0.0),         # and vanish
+    "last key": lambda k: np.where(np.arange(k) == k - 1, 60.0, 0.0),
+    "rising by one": lambda k: 1.0 * _tile(k),                              # the sums of many tiles stay in the result
+}
+
+
+@pytest.mark.parametrize("rows,seqs", GRIDS)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("rise", RISES, ids=lambda r: r.replace(" ", "_"))
+def test_maxima_that_move_from_tile_to_tile(torch, rise, d, rows, seqs):
+    """The sums of earlier keys are rescaled by far from one, by one and by nothing, and two key sets meet with references far
+    apart.  Score differences up to 12 powers of two reach the result (2^-12 is below bf16's half ulp of the sum); they come
+    from a query component of three bf16 roundings, 12 * 3 * 2^-9 = 0.07 powers of two or 5 % of a term of weight 2^-12, and the
+    differences of a rising-by-one row from 11: below the gates everywhere."""
+    s = STEEP[d]
+    keys = 704
+    rng = np.random.default_rng([d, rows])
+    caches = [(_keys(s, i, RISES[rise](keys), 0.5), _bits(rng.standard_normal((keys, s.Hkv, s.d)))) for i in range(seqs)]
+    x = _hidden(s, rows * seqs, 3)
+    got, want = _run(torch, s, rows, caches, x), _oracle(s, rows, caches, x)
+    assert U.rel_err(got, want) <= U.BF16_TOL
+    U.assert_rms(got, want, U.RMS_BF16)

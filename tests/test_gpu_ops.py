@@ -45,17 +45,19 @@ GEMM_SHAPES = [
     # M, N, K: single tile, ragged M, ragged N (not a multiple of 32), K tail (688 = 10*64 + 48)
     (64, 128, 64), (1, 768, 256), (65, 768, 256), (200, 688, 256), (333, 256, 688), (130, 1376, 2048),
     (257, 4096, 512), (31, 48, 72),
-    # large-tile kernel (M > 256, K a multiple of 64): ragged M, N tails, one and many K tiles
+    # 65 .. 2048 rows, K a multiple of 64: ragged M, N tails, one and many K tiles
     (300, 768, 256), (700, 688, 1024), (513, 520, 64), (1030, 1024, 2048), (257, 132, 128),
-    # more than 256 tiles with a small last round (272 / 544 tiles): with a workspace the last tiles are split over K
+    # large-tile kernel, more than 256 tiles with a small last round (272 / 544 tiles): with a workspace the last tiles are
+    # split over K
     (4300, 4092, 1024),
     # decode-sized problems (M <= 64, K a multiple of 64): the split-K kernel when a workspace is given
     (64, 4096, 4096), (33, 688, 1024), (7, 260, 640), (48, 1024, 14336),
-    # 65..128 rows: the same kernel, two 64-row blocks per tile and k-slice (second block ragged)
+    # few rows and long K: several ranges of K, ragged last tile
     (128, 1024, 4096), (97, 688, 1024), (100, 256, 4096), (250, 512, 2048),
-    # a few hundred rows, fewer tiles than CUs: every tile of the large-tile kernel split over K
+    # a few hundred rows, fewer tiles than CUs
     (200, 4096, 2048), (600, 1376, 4096),
-    # decode-sized with a power-of-two row pitch and 32 k-tiles per workgroup: tiles start their walk over K at different places
+    # one row of tiles, a power-of-two row pitch and 32 k-tiles per workgroup: tiles start their walk over K at different
+    # places (and two rows of tiles, which walk in step)
     (40, 7168, 4096), (150, 7168, 4096),
 ]
 
@@ -113,19 +115,65 @@ def test_gemm_random_problems(torch, case):
 
 
 @pytest.mark.parametrize("mode", [0, 1, 2])
-@pytest.mark.parametrize("M,N,K", [(65, 4, 64), (272, 252, 128), (511, 260, 192), (513, 1004, 448), (769, 520, 640)])
-def test_gemm_large_tile_edges(torch, mode, M, N, K):
+@pytest.mark.parametrize("M,N,K,whole,ranges", [
+    (2049, 4, 64, True, 1), (2177, 252, 128, True, 1), (2049, 264, 192, True, 1), (2305, 520, 448, True, 1),
+    (2049, 260, 512, False, 2), (2111, 512, 640, False, 2), (2600, 1004, 1088, False, 2),
+    (2305, 6660, 512, True, 2), (2305, 6656, 576, True, 2)])
+def test_gemm_large_tile_edges(torch, mode, M, N, K, whole, ranges):
     """The large-tile kernel around its 16-row blocks and 256-wide tiles, rows of 8k and 8k + 4 features, one k-tile
-    and a few, whole tiles and split ones."""
+    to many, all tiles whole, all split over K, and whole ones with a split last round."""
+    from paper_2412_17246_amd import op_gemm_plan
+    from paper_2412_17246_amd.binding import BZ_GEMM_LARGE
+    p = op_gemm_plan(mode, M, N, K)
+    assert p.kernel == BZ_GEMM_LARGE and (p.whole_tiles > 0) == whole and min(p.ranges, 2) == ranges
     test_gemm(torch, False, mode, M, N, K)
 
 
 @pytest.mark.parametrize("mode", [0, 1, 2])
 @pytest.mark.parametrize("M,N,K", [(65, 36, 64), (96, 4100, 192), (129, 2064, 1024), (225, 5120, 640), (257, 4092, 4096),
-                                   (321, 3004, 320), (552, 7172, 2048), (2048, 520, 448)])
+                                   (321, 3004, 320), (552, 7172, 2048), (2048, 520, 448), (65, 4, 64), (272, 252, 128),
+                                   (511, 260, 192), (513, 1004, 448), (769, 520, 640)])
 def test_gemm_mid_sized_edges(torch, mode, M, N, K):
     """The mid-sized kernel's tiles: one row past a tile, rows of 8k and 8k + 4 features, one k-tile, fewer than the
     ring holds, many; one range of K and several; one row of tiles (walks that start inside K among them) and more."""
+    from paper_2412_17246_amd import op_gemm_plan
+    from paper_2412_17246_amd.binding import BZ_GEMM_MID
+    assert op_gemm_plan(mode, M, N, K).kernel == BZ_GEMM_MID
+    test_gemm(torch, False, mode, M, N, K)
+
+
+# Every tile of the mid-sized kernel, plain and gated, with one row of tiles where a problem of this size has that, and more:
+# K of one k-tile, and of twice what the tile's ring holds and more.  (rows, weight rows of the tile; mode, M, N, K)
+MID_TILES = [
+    (96, 128, 0, 132, 4180, 1856), (96, 128, 0, 264, 7688, 64), (96, 128, 1, 67, 8300, 1920),
+    (96, 128, 2, 129, 6684, 640), (96, 128, 2, 133, 6228, 64), (128, 64, 0, 148, 1900, 640),
+    (128, 64, 1, 129, 4, 64), (128, 64, 0, 75, 3596, 640), (128, 64, 0, 65, 4, 64), (128, 64, 2, 131, 4, 640),
+    (128, 64, 2, 129, 4, 64), (128, 64, 2, 65, 4, 640), (128, 64, 2, 65, 4, 64), (128, 96, 1, 135, 9016, 640),
+    (128, 96, 0, 129, 8296, 64), (128, 96, 0, 68, 5728, 2112), (128, 96, 2, 137, 4176, 640),
+    (128, 96, 2, 129, 4204, 64), (128, 96, 2, 71, 8364, 640), (128, 96, 2, 67, 8324, 64),
+    (160, 128, 1, 391, 7932, 512), (160, 128, 1, 386, 7740, 64), (160, 128, 2, 221, 6224, 512),
+    (160, 128, 2, 194, 6252, 64), (160, 192, 1, 593, 8424, 384), (160, 192, 0, 779, 6212, 64),
+    (160, 192, 2, 258, 8900, 384), (160, 192, 2, 258, 8540, 64), (160, 256, 0, 910, 9428, 384),
+    (160, 256, 1, 905, 9236, 64), (160, 256, 2, 476, 8284, 384), (160, 256, 2, 449, 8292, 64),
+    (192, 96, 1, 786, 3100, 512), (192, 96, 1, 385, 6236, 64), (192, 96, 0, 132, 8412, 2368),
+    (192, 96, 2, 1082, 1184, 512), (192, 96, 2, 1048, 1156, 64), (192, 96, 2, 131, 8488, 512),
+    (192, 96, 2, 129, 8324, 64), (192, 128, 1, 484, 8452, 512), (192, 128, 1, 962, 4124, 64),
+    (192, 128, 2, 978, 2052, 512), (192, 128, 2, 641, 3164, 64), (192, 192, 0, 1059, 6212, 384),
+    (192, 192, 1, 1057, 6176, 64), (192, 192, 2, 335, 9060, 384), (192, 192, 2, 326, 8268, 64),
+    (224, 192, 1, 770, 9244, 384), (224, 192, 1, 770, 9408, 64), (224, 192, 2, 397, 8252, 384),
+    (224, 192, 2, 397, 8308, 64), (256, 96, 1, 1009, 5160, 384), (256, 96, 0, 388, 10344, 64),
+    (256, 96, 2, 395, 5436, 384), (256, 96, 2, 387, 5644, 64), (256, 96, 2, 196, 8316, 384),
+    (256, 96, 2, 199, 8236, 64), (256, 128, 0, 963, 6188, 384), (256, 128, 0, 646, 9264, 64),
+    (256, 128, 2, 401, 7740, 384), (256, 128, 2, 970, 3076, 64),
+]
+
+
+@pytest.mark.parametrize("rows,cols,mode,M,N,K", MID_TILES)
+def test_gemm_every_mid_sized_tile(torch, rows, cols, mode, M, N, K):
+    from paper_2412_17246_amd import op_gemm_plan
+    from paper_2412_17246_amd.binding import BZ_GEMM_MID
+    p = op_gemm_plan(mode, M, N, K)
+    assert (p.kernel, p.tile_rows, p.tile_cols) == (BZ_GEMM_MID, rows, cols)
     test_gemm(torch, False, mode, M, N, K)
 
 

@@ -14,9 +14,9 @@ from tests import _util as U
 @pytest.mark.parametrize("mode,first,second", [
     # split-K partial sums (decode-sized): 64 rows, then 33 rows of a narrower matrix
     (1, (64, 4096, 4096), (33, 688, 1024)),
-    # partial tiles of the large-tile kernel's split last round, then a few hundred rows with every tile split
+    # partial tiles of the large-tile kernel's split last round, then partial sums of a few hundred rows
     (0, (4300, 4092, 1024), (600, 1376, 4096)),
-    # SwiGLU epilogue behind split-K partial sums (two 64-row blocks), then a schedule that needs no scratch at all
+    # SwiGLU epilogue behind split-K partial sums, then a single range of K, whose kernel writes the result itself
     (2, (128, 1024, 4096), (31, 48, 72)),
 ])
 def test_static_scratch_gemm_equals_workspace_gemm_on_two_calls_in_a_row(fp32, mode, first, second):
@@ -55,13 +55,16 @@ def test_static_scratch_gemm_equals_workspace_gemm_on_two_calls_in_a_row(fp32, m
 
 @pytest.mark.gpu
 def test_static_scratch_gemm_after_the_scratch_was_overwritten():
-    """Stale contents of the static scratch never reach a result: a large split problem fills it, then a
-    smaller one whose partial tiles cover only its first part must still match the workspace call."""
+    """Stale contents of the static scratch never reach a result: a large problem with every tile split over K fills it, then
+    smaller ones whose partial tiles or sums cover only its first part must still match the workspace call."""
     import torch
-    from paper_2412_17246_amd import op_gemm, op_gemm_static, op_gemm_workspace_bytes
+    from paper_2412_17246_amd import op_gemm, op_gemm_plan, op_gemm_static, op_gemm_workspace_bytes
+    from paper_2412_17246_amd.binding import BZ_STATIC_SCRATCH_BYTES
     rng = np.random.default_rng(29)
     outs = []
-    for (M, N, K) in ((2000, 4096, 4096), (300, 768, 256)):
+    used = []
+    for (M, N, K) in ((2100, 3584, 1024), (2100, 512, 1024), (300, 768, 4096), (40, 768, 4096)):
+        used.append(op_gemm_plan(1, M, N, K).workspace_bytes)
         a, _ = U.f64_to_device(rng.standard_normal((M, K)) * 50.0, False)
         w, _ = U.f64_to_device(rng.standard_normal((N, K)), False)
         x, _ = U.f64_to_device(rng.standard_normal((M, N)), False)
@@ -70,6 +73,7 @@ def test_static_scratch_gemm_after_the_scratch_was_overwritten():
         want = x.clone()
         op_gemm(1, a, w, want, want, M, N, K, workspace=ws if nws else None)
         outs.append((M, N, K, a, w, x, want))
+    assert used[0] > 0.98 * BZ_STATIC_SCRATCH_BYTES and all(0 < b < a for a, b in zip(used, used[1:])), used
     for (M, N, K, a, w, x, want) in outs:
         op_gemm_static(1, a, w, x, x, M, N, K)           # residual aliased with the output, as in a layer
     torch.cuda.synchronize()
