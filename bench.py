@@ -51,13 +51,14 @@ PEAK_HBM_GBPS = 8000.0
 MEASURED_TRAFFIC = {
     # gate/up projection of the large-tile kernel: L2-miss traffic summed over the eight XCD L2s (FETCH_SIZE) plus
     # bytes written (WRITE_SIZE); most of the fetches are served by the Infinity Cache, the counters cannot tell
-    ("70b", 8192, "gemm_gateup"): (11.283e9 + 0.470e9, "profiles/gemm_big_kernel_prefill_counters.txt"),
-    ("7b", 6768, "gemm_gateup"): (1.881e9 + 0.149e9 + 0.069e9 + 0.051e9 + 0.051e9 + 0.001e9,
+    ("70b", 8192, "gemm_gateup"): (11.292e9 + 0.470e9, "profiles/gemm_big_kernel_prefill_counters.txt"),
+    ("7b", 6768, "gemm_gateup"): (1.909e9 + 0.148e9 + 0.069e9 + 0.050e9 + 0.050e9 + 0.001e9,
                                   "profiles/gemm_big_kernel_prefill_counters.txt"),
-    ("13b", 11970, "gemm_gateup"): (5.582e9 + 0.331e9, "profiles/gemm_big_kernel_prefill_counters.txt"),
-    # decode attention: split-KV kernel (fetch + partial results written) and the combine's fetch
-    ("8b_gqa", 64, "attn_decode"): (0.5671e9 + 0.0098e9 + 0.0113e9, "profiles/attn_decode_and_skinny_gemm_decode_counters.txt"),
-    ("70b", 32, "attn_decode"): (0.2936e9 + 0.0101e9 + 0.0117e9, "profiles/attn_decode_and_skinny_gemm_decode_counters.txt"),
+    ("13b", 11970, "gemm_gateup"): (5.415e9 + 0.331e9, "profiles/gemm_big_kernel_prefill_counters.txt"),
+    # decode attention: split-KV kernel (cache and projection fetched, partial results and new positions written) and
+    # the combine's fetch
+    ("8b_gqa", 64, "attn_decode"): (0.5793e9 + 0.0111e9 + 0.0114e9, "profiles/attn_decode_and_skinny_gemm_decode_counters.txt"),
+    ("70b", 32, "attn_decode"): (0.3128e9 + 0.0108e9 + 0.0117e9, "profiles/attn_decode_and_skinny_gemm_decode_counters.txt"),
 }
 
 

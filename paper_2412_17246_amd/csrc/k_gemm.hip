@@ -1,12 +1,13 @@
 // Projections of a decoder layer: C[M,N] = A[M,K] * W[N,K]^T with bf16 inputs, fp32 accumulation on
-// the matrix cores (v_mfma_f32_32x32x16_bf16), and three epilogues: plain, + residual, SwiGLU.
+// the matrix cores, and three epilogues: plain, + residual, SwiGLU.
 //
 // Both operands are K-contiguous, so a lane's MFMA operand (8 consecutive k of one row / column)
 // is one 16-byte LDS read.  Four kernels share the work: gemm_big_kernel (prefill-sized problems: 256x256
 // tiles, operands global -> LDS by DMA into a five-slot ring), gemm_mid_kernel (65 to 2048 rows: tiles sized to the
-// batch), gemm_skinny_kernel (up to 64 rows: the weights are streamed once, split over K) and gemm_kernel below (everything else: K tails, odd widths,
-// no workspace), which stages tiles global -> registers -> LDS, double buffered, one barrier per 64-wide
-// K step, LDS rows padded by 16 bytes so that the operand reads of 16 consecutive rows fall in distinct banks.
+// batch), both of 16x16x32 products, gemm_skinny_kernel (up to 64 rows: the weights are streamed once, split over K) and
+// gemm_kernel below (everything else: K tails, odd widths, no workspace), both of 32x32x16 products.  gemm_kernel
+// stages tiles global -> registers -> LDS, double buffered, one barrier per 64-wide K step, LDS rows padded by 16 bytes
+// so that the operand reads of 16 consecutive rows fall in distinct banks.
 #include <type_traits>
 
 #include "common.h"
@@ -617,9 +618,8 @@ static BigPlan big_plan(int mode, int M, int N, int K) {
     p.ws_bytes = 0;
     const int full = tiles / kCUs * kCUs, rest = tiles - full;
     // rest <= kMaxTail: the last round is at most half full (then two ranges of K per tile fit the chip).
-    // full == 0: fewer tiles than CUs altogether (a few hundred rows, or a narrow output); every tile is
-    // split, whatever their number, so that a mid-sized batch still puts the whole chip to streaming the
-    // weights.
+    // full == 0: fewer tiles than CUs altogether; every tile is split, whatever their number, so that the whole chip
+    // streams the weights.
     if (rest > 0 && (rest <= kMaxTail || full == 0)) {
         int sp = kCUs / rest;
         if (sp > kMaxSplits) sp = kMaxSplits;
@@ -686,9 +686,10 @@ static void launch_big(const bf16* a, const bf16* w, const bf16* r, bf16* c, int
 // bytes per ns and CU (13 TB/s over the chip, weights from HBM, activations from L2).  Leaving the MFMAs out changes
 // nothing (7B gate/up at 301 rows: 59.0 -> 59.4 us), and neither do four more waves that do nothing but request; with both
 // operands served by the L2 it takes 44 us.  So tiles are as square as filling the chip allows.
-// Cold weights, against the kernels that took these sizes before, microseconds at 161 / 301 / 552 rows: 7B qkv 44 -> 30 /
-// 62 -> 42 / 80 -> 54, o 19 -> 15 / 34 -> 23 / 43 -> 28, gate/up 84 -> 47 / 83 -> 59 / 111 -> 101, down 36 -> 31 / 50 -> 40 /
-// 81 -> 58; 8B-GQA gate/up 90 -> 56 / 96 -> 72 / 147 -> 120.
+// It is not bound behind the L2s: at 301 rows gate/up fetches 200 MB, 1.10 times its operands.
+// Cold weights, against the kernels that took these sizes before (folds included), microseconds at 161 / 301 / 552 rows: 7B
+// gate/up 91 -> 47 / 94 -> 65 / 121 -> 110, the other three 109 -> 68 / 153 -> 106 / 220 -> 144; 8B-GQA gate/up 99 -> 54 /
+// 103 -> 77 / 162 -> 127, the other three 101 -> 65 / 136 -> 95 / 184 -> 142.
 //
 // A ring of as many whole stages (activations + weights of one 64-wide k-tile) as the CU's LDS holds, filled by
 // direct global->LDS loads.  The barrier of tile i sits between its two k-steps, whose second one runs from
