@@ -136,9 +136,10 @@ typedef struct bz_stats {
 } bz_stats;
 
 /* Kernel classes for bz_profile_read.  BZ_K_ROPE_APPEND takes the sequences with several new tokens (their
- * keys and values; their queries too where the projection is split over K).  Single new tokens are rotated
- * and appended inside BZ_K_ATTN_DECODE, other queries inside BZ_K_ATTN_PREFILL, and neither class counts that:
- * a batch of decode steps alone has no BZ_K_ROPE_APPEND launches.  (fp32 debug build: every row, queries
+ * keys and values; their queries too where the projection is split over K) and, in batches with very many
+ * decode workgroups, the single new tokens.  Otherwise these are rotated and appended inside BZ_K_ATTN_DECODE,
+ * as other queries are inside BZ_K_ATTN_PREFILL, and neither class counts that: a batch of decode steps alone
+ * mostly has no BZ_K_ROPE_APPEND launches.  (fp32 debug build: every row, queries
  * included, in BZ_K_ROPE_APPEND.)  BZ_K_ATTN_DECODE includes the merge of a sequence's chunks. */
 enum {
     BZ_K_RMSNORM = 0, BZ_K_GEMM_QKV, BZ_K_ROPE_APPEND, BZ_K_ATTN_PREFILL, BZ_K_ATTN_DECODE,

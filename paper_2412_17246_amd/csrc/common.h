@@ -244,11 +244,21 @@ void launch_reduce_residual_rmsnorm(act_t* x, const float* partial, int ksplit, 
 // Rotary embedding (table `rope_tab`: [max_seq_len][d/2] pairs of cos, sin) and the append to the cache are shared out so
 // that the projection is read once and the rotated queries never travel through memory: launch_kv_append takes the keys
 // and values of the sequences with several new tokens, the prefill kernel rotates its queries as it loads them, and the
-// decode kernel does both for its one token per sequence.  Where the projection is partial sums, launch_kv_append also folds
+// decode kernel does both for its one token per sequence (below a number of workgroups).  Where the projection is partial sums, launch_kv_append also folds
 // and rotates the queries of those sequences into `qkv`: in the prefill kernel every lane would fold a row of its own, line by
 // line.  (fp32 debug build: launch_kv_append does it all.)  launch_kv_append comes first.
-bool kv_append_needed(const BatchView& bv);
-int kv_append_skips(const BatchView& bv);       // rows of the batch that the decode kernel appends
+bool kv_append_needed(const BatchView& bv, const KvView& kv, int Hq);
+// Whether single new tokens are rotated and appended by launch_kv_append as well.  Inside the decode kernel that costs every
+// workgroup 0.4 us and more of its 9 to 10, a launch of its own 6 to 10 us altogether: on grids of many workgroups it is the
+// cheaper.  Attention with the append, inside against apart, us: one query head per kv head 171.5 / 173.5 (8.8 thousand
+// workgroups), 212 / 209 (10.9), 308 / 301 (15.9), 392 / 386 (20); two 408 / 403 (20); four 367 / 371 (16).  Batches of mostly
+// one chunk per sequence stay inside, where they need no combine (10 thousand workgroups: 169 / 183).
+inline bool decode_append_apart(const BatchView& bv, const KvView& kv, int Hq) {
+    return bv.n_decode_work >= 2 * bv.n_decode && (int64_t)bv.n_decode_work * kv.Hkv > 9600 * (int64_t)(Hq / kv.Hkv);
+}
+// rows whose keys and values, and rows whose queries, launch_kv_append takes
+struct AppendRows { int kv, q; };
+AppendRows kv_append_rows(const QkvSource& src, const BatchView& bv, const KvView& kv, int Hq);
 void launch_kv_append(const QkvSource& src, const float* rope_tab, const BatchView& bv, const KvView& kv, int Hq,
                       hipStream_t st);
 void launch_attn_prefill(const QkvSource& src, const float* rope_tab, act_t* out, const BatchView& bv, const KvView& kv,

@@ -1077,10 +1077,10 @@ int bz_run_layers(bz_instance* I, int a, int b, const bz_batch* batch, void* hid
           ks_qkv = launch_gemm_partial(0, normed, wqkv, T, nqkv, sh.H, gws, gwsb, st);
           if (ks_qkv == 0) launch_gemm(0, normed, wqkv, nullptr, qkv, T, nqkv, sh.H, gws, gwsb, st); }
         const QkvSource projected{qkv, ks_qkv > 0 ? gws : nullptr, ks_qkv};
-        if (kv_append_needed(bv)) {
-            // keys and values of the rows it takes, and the queries where it rotates them too
-            const double rows = T - kv_append_skips(bv), hq = ks_qkv > 0 || sizeof(act_t) == 4 ? sh.Hq : 0;
-            ProfScope p(I, BZ_K_ROPE_APPEND, 3.0 * rows * (hq + sh.Hkv) * sh.d, rows * (2.0 * hq + 4.0 * sh.Hkv) * sh.d * e);
+        if (kv_append_needed(bv, kvv, sh.Hq)) {
+            const AppendRows n = kv_append_rows(projected, bv, kvv, sh.Hq);
+            ProfScope p(I, BZ_K_ROPE_APPEND, 3.0 * sh.d * ((double)n.q * sh.Hq + (double)n.kv * sh.Hkv),
+                        e * sh.d * (2.0 * n.q * sh.Hq + 4.0 * n.kv * sh.Hkv));
             launch_kv_append(projected, rope, bv, kvv, sh.Hq, st);
         }
         if (bv.n_prefill_items > 0) {

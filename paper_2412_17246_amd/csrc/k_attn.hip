@@ -436,12 +436,21 @@ constexpr int kDecodeMaxG = 8;
 // result (score from a plain dot product, probability 1 against its own maximum); everywhere else only cached positions
 // count.  A launch of its own for these few bytes per sequence cost 5 to 7.5 us of a 105 to 370 us decode layer.
 // A sequence with a single chunk gets its output here; the combine kernel leaves it alone.
-template <int D, bool REDUCE>
-__global__ __launch_bounds__(256, 2) void attn_decode_kernel(QkvSource src, const float* __restrict__ tab,
+//
+// SRC: what the new token's values come as: the projection, its partial sums, or rotated and appended already
+// (decode_append_apart).
+// WAVES per SIMD, that is workgroups per CU, set outright: for d = 128 two keep the memory streams in longer runs than three,
+// which the registers would allow where the projection is plain (83 sequences of 40 heads, 402 -> 392 us; 240 of 8 with four
+// query heads each 371 -> 366), except where most caches end within their first chunk (250 sequences of 40 heads 178 -> 170 with
+// three).
+enum { kProjection = 0, kPartialSums = 1, kAppended = 2 };
+template <int D, int SRC, int WAVES>
+__global__ __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) __launch_bounds__(256) void attn_decode_kernel(QkvSource src, const float* __restrict__ tab,
                                                              float* __restrict__ partial, bf16* __restrict__ out,
                                                              BatchView bv, KvView kv, int Hq, int G, float scale_log2) {
     constexpr int CH = kDecodeChunk;
     constexpr int KS = D / 16, DB = D / 32, BLK = 32 * D;
+    constexpr bool REDUCE = SRC == kPartialSums, FUSED = SRC != kAppended;
     __shared__ float wmx[4][kDecodeMaxG];
     __shared__ float wsum[4][kDecodeMaxG];
     __shared__ float osh[4][kDecodeMaxG][D];
@@ -456,10 +465,11 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(QkvSource src, cons
     const int s = item.x, slot = item.y, di = item.z;
     const int rest = blockIdx.x - kv.Hkv * item2.x;          // position among this sequence's (kv head, chunk) pairs
     const int kvh = rest / item.w, chunk = rest - kvh * item.w;
-    const int pos = bv.kv_before[s];                         // the new token's position = number of cached ones
+    const int pos = bv.kv_before[s];                         // the new token's position
+    const int cached = FUSED ? pos : pos + 1;
     const int c0 = chunk * CH;
     if (c0 > pos) return;
-    const bool newest = pos - c0 < CH;                       // this chunk holds the new position
+    const bool newest = FUSED && pos - c0 < CH;              // this chunk holds the new position, which is not cached yet
     const int t = bv.q_start[s];
     const int Hkv = kv.Hkv, cap = kv.slot_cap[slot];
     const size_t head_base = (size_t)kv.slot_off[slot] * Hkv * D + (size_t)kvh * cap * D;
@@ -481,7 +491,7 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(QkvSource src, cons
     const size_t at = (size_t)t * nqkv + (is_v ? Hq + Hkv + kvh : hh < G ? kvh * G + hh : Hq + kvh) * D + j0;
     const int second = is_v ? 0 : D / 2;
     const float* cs = tab + (size_t)pos * D + (is_v ? 0 : j0 * 2);
-    f32x4 pa[4], pb[4];                                      // REDUCE: up to four slices, the rest later
+    f32x4 pa[4], pb[4], cs0, cs1;                            // REDUCE: up to four slices, the rest later
     bf16x4 ra, rb;
     if (REDUCE) {
 #pragma unroll
@@ -490,19 +500,22 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(QkvSource src, cons
             pa[k] = *reinterpret_cast<const f32x4*>(p);
             pb[k] = *reinterpret_cast<const f32x4*>(p + second);
         }
-    } else {
+    } else if (FUSED) {
         ra = *reinterpret_cast<const bf16x4*>(src.qkv + at);
         rb = *reinterpret_cast<const bf16x4*>(src.qkv + at + second);
     }
-    const f32x4 cs0 = *reinterpret_cast<const f32x4*>(cs), cs1 = *reinterpret_cast<const f32x4*>(cs + 4);
+    if (FUSED) {
+        cs0 = *reinterpret_cast<const f32x4*>(cs);
+        cs1 = *reinterpret_cast<const f32x4*>(cs + 4);
+    }
     __builtin_amdgcn_sched_barrier(0);                       // these go out before the stream
 
     const int w0 = c0 + wave * 64;
-    const bool live = w0 < pos;                              // something cached in this wave's range; wave-uniform
+    const bool live = w0 < cached;                           // something cached in this wave's range; wave-uniform
     // The loads stand outside any branch, or the wait for the projection's values would have to assume that they were not
     // issued and drain them.  A block past the end is replaced by the last valid one (its positions get probability zero);
-    // a wave without cached positions reads one line per load, of block 0.
-    const int last_blk = live ? (pos - 1) >> 5 : 0;
+    // a wave without cached positions reads one line per load, of block 0, or (nothing to wait for before) nothing.
+    const int last_blk = live ? (cached - 1) >> 5 : 0;
     const int lane_k = live ? (lh * 32 + lq) * 8 : 0, lane_v = live ? (lh * D + lq) * 8 : 0;
     size_t boff[2];
 #pragma unroll
@@ -512,20 +525,34 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(QkvSource src, cons
         boff[b] = (size_t)kb * BLK;
     }
     bf16x8 kf[2][KS], vf[2][2][DB];
+    if (FUSED || live) {
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+                kf[b][ks] = stream_load(reinterpret_cast<const bf16x8*>(Kc + boff[b] + lane_k + ks * 512));
 #pragma unroll
         for (int b = 0; b < 2; ++b)
-            kf[b][ks] = stream_load(reinterpret_cast<const bf16x8*>(Kc + boff[b] + lane_k + ks * 512));
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+            for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
-        for (int tt = 0; tt < 2; ++tt)
+                for (int db = 0; db < DB; ++db)
+                    vf[b][tt][db] =
+                        stream_load(reinterpret_cast<const bf16x8*>(Vc + boff[b] + lane_v + (2 * tt * D + db * 32) * 8));
+    }
+    bf16x8 qa[KS];
+    if (!FUSED && live) {
+        const bf16* q = src.qkv + (size_t)t * nqkv + kvh * G * D;
 #pragma unroll
-            for (int db = 0; db < DB; ++db)
-                vf[b][tt][db] = stream_load(reinterpret_cast<const bf16x8*>(Vc + boff[b] + lane_v + (2 * tt * D + db * 32) * 8));
+        for (int ks = 0; ks < KS; ++ks) {
+            if (lq < G) qa[ks] = *reinterpret_cast<const bf16x8*>(q + lq * D + ks * 16 + lh * 8);
+            else
+#pragma unroll
+                for (int i = 0; i < 8; ++i) qa[ks][i] = (bf16)0.f;
+        }
+    }
     __builtin_amdgcn_sched_barrier(0);
-    {
+    if (FUSED) {
         f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
         if (REDUCE) {
 #pragma unroll
@@ -576,10 +603,12 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(QkvSource src, cons
             }
         }
     }
-    // hand-over through LDS without waiting for the stream (a full barrier would drain it)
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    if (FUSED) {
+        // hand-over through LDS without waiting for the stream (a full barrier would drain it)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    }
     if (newest) {                                            // workgroup-uniform
         for (int g = wave; g < G; g += 4) {
             float p = 0.f;
@@ -598,18 +627,19 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(QkvSource src, cons
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             bf16x8 qf = {};
-            if (lq < G) qf = *reinterpret_cast<const bf16x8*>(&qs[lq][ks * 16 + lh * 8]);
+            if (!FUSED) qf = qa[ks];
+            else if (lq < G) qf = *reinterpret_cast<const bf16x8*>(&qs[lq][ks * 16 + lh * 8]);
 #pragma unroll
             for (int b = 0; b < 2; ++b) sacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[b][ks], qf, sacc[b], 0, 0, 0);
         }
         // lane (g = lane%32, h = lane/32) holds positions b*32 + 8*(r/4) + 4h + r%4 of head g
         float m = -INFINITY;
-        if (w0 + 64 > pos) {                                 // wave-uniform: the range ends here
+        if (w0 + 64 > cached) {                              // wave-uniform: the range ends here
 #pragma unroll
             for (int b = 0; b < 2; ++b)
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
-                    if (w0 + b * 32 + 8 * (r >> 2) + 4 * lh + (r & 3) >= pos) sacc[b][r] = -INFINITY;
+                    if (w0 + b * 32 + 8 * (r >> 2) + 4 * lh + (r & 3) >= cached) sacc[b][r] = -INFINITY;
         }
 #pragma unroll
         for (int b = 0; b < 2; ++b)
@@ -879,7 +909,12 @@ static void launch_decode_d(const QkvSource& qkv, [[maybe_unused]] const float* 
     const dim3 grid(bv.n_decode_work * kv.Hkv);
     const int G = Hq / kv.Hkv;                      // 1, 2, 4 or 8: checked when the instance is created
 #ifndef BZ_FP32_DEBUG
-    auto kern = qkv.partial ? attn_decode_kernel<D, true> : attn_decode_kernel<D, false>;
+    constexpr int MANY = D == 128 ? 3 : 4;          // what the registers allow
+    constexpr int FEW = D == 128 ? 2 : 4;
+    auto kern = decode_append_apart(bv, kv, Hq)     ? attn_decode_kernel<D, kAppended, FEW>
+                : qkv.partial                       ? attn_decode_kernel<D, kPartialSums, FEW>
+                : bv.n_decode_work < 2 * bv.n_decode ? attn_decode_kernel<D, kProjection, MANY>
+                                                    : attn_decode_kernel<D, kProjection, FEW>;
     hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, qkv, rope_tab, partial, out, bv, kv, Hq, G, scale_log2);
     if (bv.n_decode_work == bv.n_decode) return;    // one chunk each: nothing to combine
 #else

@@ -115,7 +115,7 @@ void launch_reduce_residual_rmsnorm(act_t* x, const float* partial, int ksplit, 
 
 // ---------------------------------------------------------------------------------------------
 // KV append for the sequences with several new tokens: K is rotated and written to the cache, V is copied to it.
-// (Single new tokens are appended by the decode attention kernel.)
+// (Single new tokens are appended by the decode attention kernel, or here row by row: decode_append_apart.)
 //
 // HBM-bound: the K and V parts of the projection in, the cache out.  A workgroup owns one aligned block of 32 positions
 // (the unit in which the cache is contiguous) of one sequence for `heads_per_wg` kv heads, so a head's block is written as
@@ -167,23 +167,59 @@ __device__ __forceinline__ void rotated_pair(const QkvSource& src, size_t slice,
     }
 }
 
-// REDUCE: workgroups from `kv_wgs` on fold and rotate queries, `q_wgs` of them per row.
+// One row's queries (rotated, into the projection's buffer) and, for a single new token, its key and value (to the cache):
+// thread `u` of the row takes 8 rotation pairs, or 8 values.
+template <bool REDUCE>
+__device__ __forceinline__ void append_row(const QkvSource& src, const float* __restrict__ tab, const BatchView& bv,
+                                           const KvView& kv, int Hq, int seq, int t, bool single, int u) {
+    const int d = kv.d, Hkv = kv.Hkv, half = d >> 1, pairs = d >> 4;
+    const int nqkv = (Hq + 2 * Hkv) * d;
+    const size_t row = (size_t)t * nqkv, slice = (size_t)bv.T * nqkv;
+    const int pos = bv.kv_before[seq] + t - bv.q_start[seq];
+    const int rotated = (Hq + (single ? Hkv : 0)) * pairs;
+    if (u < rotated) {
+        const int head = u / pairs, j = (u - head * pairs) * 8;
+        float c8[8], s8[8], o_lo[8], o_hi[8];
+        load_cos_sin(tab + (size_t)pos * d + 2 * j, c8, s8);
+        const size_t at = row + head * d + j;
+        rotated_pair<REDUCE>(src, slice, at, half, c8, s8, o_lo, o_hi);
+        bf16 *lo = src.qkv + at, *hi = lo + half;
+        if (head >= Hq) {
+            const int slot = bv.seq_slot[seq];
+            bf16* k = kv.k + (size_t)kv.slot_off[slot] * Hkv * d + (size_t)(head - Hq) * kv.slot_cap[slot] * d;
+            lo = k + k_piece_offset(pos, j >> 3, d);
+            hi = k + k_piece_offset(pos, (half + j) >> 3, d);
+        }
+        store8(lo, o_lo);
+        store8(hi, o_hi);
+    } else if (single && u < rotated + Hkv * (d >> 3)) {
+        const int head = (u - rotated) / (d >> 3), j = (u - rotated - head * (d >> 3)) * 8;
+        float v[8];
+        const size_t at = row + (Hq + Hkv + head) * d + j;
+        if (REDUCE) reduce8(src.partial, src.ksplit, slice, at, v);
+        else load8(src.qkv + at, v);
+        const int slot = bv.seq_slot[seq];
+        bf16* dst = kv.v + (size_t)kv.slot_off[slot] * Hkv * d + (size_t)head * kv.slot_cap[slot] * d;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) dst[v_elem_offset(pos, j + e, d)] = (bf16)v[e];
+    }
+}
+
+// Workgroups from `kv_wgs` on take rows, `row_wgs` each: with partial sums all rows of the batch, else the decode rows.
+// `singles`: single new tokens are appended here (otherwise their rows are left alone).
 template <bool REDUCE>
 __global__ __launch_bounds__(256) void kv_append_kernel(QkvSource src, const float* __restrict__ tab, BatchView bv,
-                                                        KvView kv, int Hq, int heads_per_wg, int hgroups, int kv_wgs, int q_wgs) {
+                                                        KvView kv, int Hq, int heads_per_wg, int hgroups, int kv_wgs,
+                                                        int row_wgs, int singles) {
     const int d = kv.d, Hkv = kv.Hkv, half = d >> 1;
     const int nqkv = (Hq + 2 * Hkv) * d;
-    if (REDUCE && (int)blockIdx.x >= kv_wgs) {
-        const int b = blockIdx.x - kv_wgs, t = b / q_wgs, u = (b - t * q_wgs) * 256 + (int)threadIdx.x;
-        const int seq = bv.token_seq[t], first = bv.q_start[seq];
-        if (bv.q_start[seq + 1] - first < 2 || u >= Hq * (d >> 4)) return;
-        const int head = u / (d >> 4), j = (u - head * (d >> 4)) * 8;
-        float c8[8], s8[8], o_lo[8], o_hi[8];
-        load_cos_sin(tab + (size_t)(bv.kv_before[seq] + t - first) * d + 2 * j, c8, s8);
-        const size_t at = (size_t)t * nqkv + head * d + j;
-        rotated_pair<true>(src, (size_t)bv.T * nqkv, at, half, c8, s8, o_lo, o_hi);
-        store8(src.qkv + at, o_lo);
-        store8(src.qkv + at + half, o_hi);
+    if ((int)blockIdx.x >= kv_wgs) {
+        const int b = blockIdx.x - kv_wgs, r = b / row_wgs;
+        const int seq = REDUCE ? bv.token_seq[r] : bv.decode_seqs[r];
+        const int t = REDUCE ? r : bv.q_start[seq];
+        const bool single = bv.q_start[seq + 1] - bv.q_start[seq] == 1;
+        if (single && !singles) return;
+        append_row<REDUCE>(src, tab, bv, kv, Hq, seq, t, single, (b - r * row_wgs) * 256 + (int)threadIdx.x);
         return;
     }
     const int item = blockIdx.x / (kAppendBlocks * hgroups);
@@ -285,12 +321,17 @@ __global__ __launch_bounds__(256) void kv_append_kernel(QkvSource src, const flo
     }
 }
 
-bool kv_append_needed(const BatchView& bv) { return bv.n_prefill_items > 0; }
-int kv_append_skips(const BatchView& bv) { return bv.n_decode; }
+bool kv_append_needed(const BatchView& bv, const KvView& kv, int Hq) {
+    return bv.n_prefill_items > 0 || (bv.n_decode > 0 && decode_append_apart(bv, kv, Hq));
+}
+AppendRows kv_append_rows(const QkvSource& src, const BatchView& bv, const KvView& kv, int Hq) {
+    const int prompts = bv.T - bv.n_decode, singles = decode_append_apart(bv, kv, Hq) ? bv.n_decode : 0;
+    return AppendRows{prompts + singles, (src.partial ? prompts : 0) + singles};
+}
 
 void launch_kv_append(const QkvSource& src, const float* rope_tab, const BatchView& bv, const KvView& kv, int Hq,
                       hipStream_t st) {
-    if (bv.n_prefill_items <= 0) return;
+    if (!kv_append_needed(bv, kv, Hq)) return;
     const int blocks = bv.n_prefill_items * kAppendBlocks;
     const int n_par = 128 / kv.d;                      // heads that run side by side in a workgroup
     // Several heads per workgroup share the load of cosines and sines, as long as some thousand workgroups remain: 14 091
@@ -298,13 +339,14 @@ void launch_kv_append(const QkvSource& src, const float* rope_tab, const BatchVi
     int hpw = (int)((int64_t)blocks * kv.Hkv / 4096);
     hpw = hpw < n_par ? n_par : hpw > 8 ? 8 : hpw;
     const int hgroups = (kv.Hkv + hpw - 1) / hpw;
-    const int kv_wgs = blocks * hgroups, q_wgs = (Hq * (kv.d >> 4) + 255) / 256;
-    if (src.partial)
-        hipLaunchKernelGGL(kv_append_kernel<true>, dim3(kv_wgs + bv.T * q_wgs), dim3(256), 0, st, src, rope_tab, bv, kv, Hq, hpw,
-                           hgroups, kv_wgs, q_wgs);
-    else
-        hipLaunchKernelGGL(kv_append_kernel<false>, dim3(kv_wgs), dim3(256), 0, st, src, rope_tab, bv, kv, Hq, hpw, hgroups,
-                           kv_wgs, q_wgs);
+    const bool singles = bv.n_decode > 0 && decode_append_apart(bv, kv, Hq);
+    // threads per row: rotation pairs by eights, and a single new token's values by eights
+    const int units = (Hq + (singles ? kv.Hkv : 0)) * (kv.d >> 4) + (singles ? kv.Hkv * (kv.d >> 3) : 0);
+    const int kv_wgs = blocks * hgroups, row_wgs = (units + 255) / 256;
+    const int rows = src.partial ? bv.T : singles ? bv.n_decode : 0;
+    auto kern = src.partial ? kv_append_kernel<true> : kv_append_kernel<false>;
+    hipLaunchKernelGGL(kern, dim3(kv_wgs + rows * row_wgs), dim3(256), 0, st, src, rope_tab, bv, kv, Hq, hpw, hgroups, kv_wgs,
+                       row_wgs, (int)singles);
 }
 
 #else  // BZ_FP32_DEBUG: one workgroup per token rotates its queries in place, and its keys into the cache, and copies its values
@@ -337,8 +379,8 @@ __global__ __launch_bounds__(256) void rope_append_kernel(float* __restrict__ qk
         kv.v[slot_base + (size_t)(u / d) * head_stride + v_elem_offset(pos, u % d, d)] = row[(Hq + Hkv) * d + u];
 }
 
-bool kv_append_needed(const BatchView& bv) { return bv.T > 0; }
-int kv_append_skips(const BatchView&) { return 0; }
+bool kv_append_needed(const BatchView& bv, const KvView&, int) { return bv.T > 0; }
+AppendRows kv_append_rows(const QkvSource&, const BatchView& bv, const KvView&, int) { return AppendRows{bv.T, bv.T}; }
 
 void launch_kv_append(const QkvSource& src, const float* rope_tab, const BatchView& bv, const KvView& kv, int Hq,
                       hipStream_t st) {

@@ -138,6 +138,75 @@ def test_decode_weights_below_the_normal_range_count(torch, d):
     assert 2.0 ** -0.8 < factor.min() and factor.max() < 2.0 ** 0.8, (factor.min(), factor.max())
 
 
+@pytest.mark.parametrize("d,prompt,single", [(64, 0, 60), (128, 0, 60), (64, 4, 60), (128, 40, 80), (64, 0, 130)])
+def test_many_decode_workgroups(torch, d, prompt, single):
+    """Above 9600 workgroups per query head of a kv head the single new tokens are appended by a launch of its own.  The same batch in
+    two halves takes the other kernel: same cache, bit for bit where the projection's plan is the same (up to 64 rows), and the
+    same output within the gates; four sequences against the oracle."""
+    s = W.DecoderShape("wide%d" % d, L=1, H=512, Hq=40, Hkv=40, d=d, F=256, rope_base=10000.0, seed=90 + d)
+    rng = np.random.default_rng([d, single])
+    edges = [1023, 1024, 1055, 1056, 1279, 1280, 1281]
+    before = (edges + rng.integers(1030, 1400, single - len(edges)).tolist()) if single <= 64 else \
+             (edges + rng.integers(513, 800, single - len(edges)).tolist())
+    news = [1] * single + ([prompt] if prompt else [])
+    befores = before + ([700] if prompt else [])
+    assert sum(b // 256 + 1 for b in before) * 40 > 9600 > sum(b // 256 + 1 for b in before[:(single + 1) // 2]) * 40
+    n, T = len(news), sum(news)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d)
+    caches = [[torch.randn(b * s.Hkv * s.d, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2)] for b in befores]
+    start = np.concatenate([[0], np.cumsum(news)]).astype(int)
+    xbits = W.hidden_bits(s, T, step=5, scale=1.0 / 16)
+    bits = W.layer_weights_bits(s, 0)
+
+    def run(parts):
+        inst = U.make_instance(s, max_seqs=n, max_seq_len=max(befores) + 64, max_tokens=T, kv_tokens=sum(befores) + 96 * n)
+        inst.load_layer(0, inst.pinned_blob(inst.pack_layer(bits)))
+        for i, (k, v) in enumerate(caches):
+            inst.kv_reserve(i, befores[i] + news[i])
+            inst.kv_write(0, i, 0, befores[i], k, v)
+        out = np.zeros((T, s.H))
+        for ids in parts:
+            q = np.concatenate([[0], np.cumsum([news[i] for i in ids])])
+            rows = np.concatenate([np.arange(start[i], start[i + 1]) for i in ids])
+            x = U.to_device(xbits[rows], False)
+            torch.cuda.synchronize()
+            inst.run_layers(0, 1, inst.batch(q, list(ids), [befores[i] for i in ids]), x)
+            inst.sync()
+            out[rows] = U.from_device(x)
+        new = []
+        for i in range(n):
+            kv = [np.zeros((news[i], s.Hkv, s.d), dtype=np.uint16) for _ in range(2)]
+            inst.kv_read(0, i, befores[i], news[i], *kv)
+            new.append(kv)
+        inst.close()
+        return out, new
+
+    half = (single + 1) // 2
+    got, kv = run([range(n)])
+    want, kv_want = run([range(half), range(half, n)])
+    assert U.rel_err(got, want) <= U.BF16_TOL
+    U.assert_rms(got, want, U.RMS_BF16)
+    for a, b in zip(kv, kv_want):
+        for x, y in zip(a, b):
+            if T <= 64:
+                assert np.array_equal(x, y)
+            else:
+                assert U.rel_err(U.f64(x), U.f64(y)) <= U.BF16_TOL
+    okv, ids = O.OracleKV(), [1, 3, 5, n - 1]
+    for j, i in enumerate(ids):
+        k, v = (t.view(torch.int16).cpu().numpy().view(np.uint16).reshape(befores[i], s.Hkv, s.d) for t in caches[i])
+        okv.put(0, j, U.f64(k), U.f64(v))
+    rows = np.concatenate([np.arange(start[i], start[i + 1]) for i in ids])
+    want = O.run_layers(U.oracle_shape(s), {0: U.oracle_weights(bits)}, 0, 1, U.f64(xbits[rows]),
+                        O.OracleBatch(list(np.concatenate([[0], np.cumsum([news[i] for i in ids])])), [0, 1, 2, 3], [befores[i] for i in ids]), okv)
+    assert U.rel_err(got[rows], want) <= U.BF16_TOL
+    U.assert_rms(got[rows], want, U.RMS_BF16)
+    for j, i in enumerate(ids):
+        for g, o in zip(kv[i], okv.get(0, j, s.Hkv, s.d)):
+            assert U.rel_err(U.f64(g), o[befores[i]:]) <= U.BF16_TOL
+
+
 def _tile(keys):
     return np.arange(keys) // 64
 
