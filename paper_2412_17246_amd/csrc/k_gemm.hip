@@ -1511,8 +1511,8 @@ static void launch_cfg(const bf16* a, const bf16* w, const bf16* r, bf16* c, int
 template <int MODE>
 static void launch_mode(const bf16* a, const bf16* w, const bf16* r, bf16* c, int M, int N, int K, float* ws,
                         size_t ws_bytes, hipStream_t st) {
-    // The kernel and its tiling are a function of the problem shape only, so a layer's result never
-    // depends on which range of layers a call covers.
+    // The kernel and its tiling are a function of the problem's shape and the scratch, and that in run_layers one of the model
+    // and the rows: a layer's result never depends on which range of layers a call covers, or on the instance.
     if (skinny_applies(MODE, M, N, K, ws, ws_bytes) && !short_tail(MODE, M, K)) {
         launch_skinny<MODE>(a, w, r, c, M, N, K, ws, st);
     } else if (M <= 64) {
