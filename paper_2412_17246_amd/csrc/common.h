@@ -157,6 +157,12 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
+// silu(z) = z / (1 + exp(-z)) with the hardware's exponential and reciprocal (about 1 ulp each; every
+// use rounds the product to bf16 afterwards).  An IEEE division costs ten instructions per element in the
+// epilogue of the gate/up projection, which has 128 of them per lane and tile.  One definition for every
+// kernel that applies SwiGLU, so that they agree bit for bit.
+__device__ __forceinline__ float silu_fast(float z) { return z * __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
+
 // Device-side view of the KV cache of one layer.  K part then V part; inside a part, slot s
 // starts at element slot_off[s] * Hkv * d and holds Hkv heads of slot_cap[s] positions each
 // (slot_cap is a multiple of 32).  Both K and V of one head are stored in blocks of 32 positions,
@@ -263,8 +269,17 @@ void launch_kv_append(const QkvSource& src, const float* rope_tab, const BatchVi
                       hipStream_t st);
 void launch_attn_prefill(const QkvSource& src, const float* rope_tab, act_t* out, const BatchView& bv, const KvView& kv,
                          int Hq, hipStream_t st);
+// combine: false where the caller combines the chunks itself (few_combines); then a single chunk leaves partial results, too
 void launch_attn_decode(const QkvSource& src, const float* rope_tab, act_t* out, float* partial, const BatchView& bv,
-                        const KvView& kv, int Hq, hipStream_t st);
+                        const KvView& kv, int Hq, bool combine, hipStream_t st);
+// Few rows: the projections with everything around them in one launch each.  mode 0: c = rmsnorm(x) * gain * w^T; 1: c = r +
+// x * w^T (r may be c); 2: c = silu(gate) * up of rmsnorm(x) * gain.
+bool few_rows(int M, int H, int qd, int F);
+void launch_few(int mode, const act_t* x, const bf16* gain, float eps, const bf16* w, const act_t* r, act_t* c, int M, int N,
+                int K, hipStream_t st);
+// The output projection of single new tokens whose attention left partial results (no combine launch then): x += combined * w^T.
+bool few_combines(const BatchView& bv, int qd);
+void launch_few_out(const float* partial, const BatchView& bv, const KvView& kv, const bf16* w, act_t* x, int H, int qd, hipStream_t st);
 void launch_kv_scatter(const act_t* src_k, const act_t* src_v, const KvView& kv, int slot, int pos0, int n,
                        bool to_cache, act_t* dst_k, act_t* dst_v, hipStream_t st);
 // kv_before[s] += 1 for every sequence, then the decode work list is rebuilt for the new lengths

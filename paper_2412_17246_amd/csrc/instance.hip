@@ -1040,6 +1040,8 @@ int bz_run_layers(bz_instance* I, int a, int b, const bz_batch* batch, void* hid
     double decode_kv = 0;
     for (int s : batch->decode_seqs) decode_kv += (double)(batch->kv_before[s] + 1);
 
+    // Few rows: the norms, the residual and SwiGLU are part of the projections' launches.
+    const bool few = few_rows(T, sh.H, sh.Hq * sh.d, sh.F), combine_later = few && few_combines(bv, sh.Hq * sh.d);
     int pending_down = 0;        // split-K slices of the previous layer's down projection still to be folded into x
     for (int l = a; l < b; ++l) {
         // A layer still on its way is waited for as a whole, except the last one of the range: there each
@@ -1068,14 +1070,16 @@ int bz_run_layers(bz_instance* I, int a, int b, const bz_batch* batch, void* hid
         // Decode-sized batches: the projections leave split-K partial sums in `gws` and the kernel that
         // consumes the projection folds them (QKV -> cache append and attention; O and down -> residual + next norm).
         // The stored values are the same bits the unfused kernels produce.
-        { ProfScope p(I, BZ_K_RMSNORM, 4.0 * T * sh.H, 2.0 * T * sh.H * e);
+        if (!few) {
+          ProfScope p(I, BZ_K_RMSNORM, 4.0 * T * sh.H, 2.0 * T * sh.H * e);
           if (pending_down > 0) launch_reduce_residual_rmsnorm(x, gws, pending_down, g1, normed, T, sh.H, I->cfg.rms_eps, st);
           else launch_rmsnorm(x, g1, normed, T, sh.H, I->cfg.rms_eps, st);
           pending_down = 0; }
         int ks_qkv = 0;
         { ProfScope p(I, BZ_K_GEMM_QKV, 2.0 * T * nqkv * sh.H, ((double)T * sh.H + (double)T * nqkv) * e + 2.0 * nqkv * sh.H);
-          ks_qkv = launch_gemm_partial(0, normed, wqkv, T, nqkv, sh.H, gws, gwsb, st);
-          if (ks_qkv == 0) launch_gemm(0, normed, wqkv, nullptr, qkv, T, nqkv, sh.H, gws, gwsb, st); }
+          if (few) launch_few(0, x, g1, I->cfg.rms_eps, wqkv, nullptr, qkv, T, nqkv, sh.H, st);
+          else ks_qkv = launch_gemm_partial(0, normed, wqkv, T, nqkv, sh.H, gws, gwsb, st);
+          if (!few && ks_qkv == 0) launch_gemm(0, normed, wqkv, nullptr, qkv, T, nqkv, sh.H, gws, gwsb, st); }
         const QkvSource projected{qkv, ks_qkv > 0 ? gws : nullptr, ks_qkv};
         if (kv_append_needed(bv, kvv, sh.Hq)) {
             const AppendRows n = kv_append_rows(projected, bv, kvv, sh.Hq);
@@ -1089,7 +1093,7 @@ int bz_run_layers(bz_instance* I, int a, int b, const bz_batch* batch, void* hid
         }
         if (bv.n_decode > 0) {
             ProfScope p(I, BZ_K_ATTN_DECODE, 4.0 * sh.Hq * sh.d * decode_kv, decode_kv * 2.0 * sh.Hkv * sh.d * e);
-            launch_attn_decode(projected, rope, attn, partial, bv, kvv, sh.Hq, st);
+            launch_attn_decode(projected, rope, attn, partial, bv, kvv, sh.Hq, !combine_later, st);
         }
         int ks_o = 0;
         if (by_part) {
@@ -1097,9 +1101,12 @@ int bz_run_layers(bz_instance* I, int a, int b, const bz_batch* batch, void* hid
             if (two) HIP_TRY(hipStreamWaitEvent(st, I->ev_part2[4 * l + 1], 0));
         }
         { ProfScope p(I, BZ_K_GEMM_O, 2.0 * T * sh.H * qd, (2.0 * T * sh.H + (double)T * qd) * e + 2.0 * sh.H * qd);
-          ks_o = launch_gemm_partial(1, attn, wo, T, sh.H, qd, gws, gwsb, st);
-          if (ks_o == 0) launch_gemm(1, attn, wo, x, x, T, sh.H, qd, gws, gwsb, st); }
-        { ProfScope p(I, BZ_K_RMSNORM, 4.0 * T * sh.H, 2.0 * T * sh.H * e);
+          if (combine_later) launch_few_out(partial, bv, kvv, wo, x, sh.H, qd, st);
+          else if (few) launch_few(1, attn, nullptr, 0.f, wo, x, x, T, sh.H, qd, st);
+          else ks_o = launch_gemm_partial(1, attn, wo, T, sh.H, qd, gws, gwsb, st);
+          if (!few && ks_o == 0) launch_gemm(1, attn, wo, x, x, T, sh.H, qd, gws, gwsb, st); }
+        if (!few) {
+          ProfScope p(I, BZ_K_RMSNORM, 4.0 * T * sh.H, 2.0 * T * sh.H * e);
           if (ks_o > 0) launch_reduce_residual_rmsnorm(x, gws, ks_o, g2, normed, T, sh.H, I->cfg.rms_eps, st);
           else launch_rmsnorm(x, g2, normed, T, sh.H, I->cfg.rms_eps, st); }
         if (by_part) {
@@ -1107,11 +1114,13 @@ int bz_run_layers(bz_instance* I, int a, int b, const bz_batch* batch, void* hid
             if (two) HIP_TRY(hipStreamWaitEvent(st, I->ev_part2[4 * l + 2], 0));
         }
         { ProfScope p(I, BZ_K_GEMM_GATEUP, 4.0 * T * sh.F * sh.H, ((double)T * sh.H + (double)T * sh.F) * e + 4.0 * sh.F * sh.H);
-          launch_gemm(2, normed, wgu, nullptr, act, T, sh.F, sh.H, gws, gwsb, st); }
+          if (few) launch_few(2, x, g2, I->cfg.rms_eps, wgu, nullptr, act, T, sh.F, sh.H, st);
+          else launch_gemm(2, normed, wgu, nullptr, act, T, sh.F, sh.H, gws, gwsb, st); }
         if (by_part) HIP_TRY(hipStreamWaitEvent(st, I->ev[l], 0));
         { ProfScope p(I, BZ_K_GEMM_DOWN, 2.0 * T * sh.H * sh.F, (2.0 * T * sh.H + (double)T * sh.F) * e + 2.0 * sh.H * sh.F);
-          pending_down = launch_gemm_partial(1, act, wd, T, sh.H, sh.F, gws, gwsb, st);
-          if (pending_down == 0) launch_gemm(1, act, wd, x, x, T, sh.H, sh.F, gws, gwsb, st); }
+          if (few) launch_few(1, act, nullptr, 0.f, wd, x, x, T, sh.H, sh.F, st);
+          else pending_down = launch_gemm_partial(1, act, wd, T, sh.H, sh.F, gws, gwsb, st);
+          if (!few && pending_down == 0) launch_gemm(1, act, wd, x, x, T, sh.H, sh.F, gws, gwsb, st); }
         HIP_TRY(hipGetLastError());
     }
     if (pending_down > 0) {      // last layer of the range: finish the residual stream without a norm

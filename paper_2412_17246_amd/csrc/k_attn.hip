@@ -447,7 +447,8 @@ enum { kProjection = 0, kPartialSums = 1, kAppended = 2 };
 template <int D, int SRC, int WAVES>
 __global__ __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) __launch_bounds__(256) void attn_decode_kernel(QkvSource src, const float* __restrict__ tab,
                                                              float* __restrict__ partial, bf16* __restrict__ out,
-                                                             BatchView bv, KvView kv, int Hq, int G, float scale_log2) {
+                                                             BatchView bv, KvView kv, int Hq, int G, float scale_log2,
+                                                             int combine) {
     constexpr int CH = kDecodeChunk;
     constexpr int KS = D / 16, DB = D / 32, BLK = 32 * D;
     constexpr bool REDUCE = SRC == kPartialSums, FUSED = SRC != kAppended;
@@ -695,7 +696,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) __launch_bounds__(
     __syncthreads();
     // merge the four waves in wave order, then the new position
     const int PS = decode_partial_stride(D);
-    const bool alone = item.w == 1;                          // the sequence's only chunk: the output itself
+    const bool alone = item.w == 1 && combine;               // the sequence's only chunk: the output itself
     for (int i = tid; i < G * D; i += 256) {
         const int g = i / D, dd = i - g * D;
         float M = fmaxf(fmaxf(wmx[0][g], wmx[1][g]), fmaxf(wmx[2][g], wmx[3][g]));
@@ -904,7 +905,7 @@ __global__ __launch_bounds__(D) void attn_combine_kernel(const float* __restrict
 
 template <int D>
 static void launch_decode_d(const QkvSource& qkv, [[maybe_unused]] const float* rope_tab, act_t* out, float* partial,
-                            const BatchView& bv, const KvView& kv, int Hq, hipStream_t st) {
+                            const BatchView& bv, const KvView& kv, int Hq, bool combine, hipStream_t st) {
     const float scale_log2 = kLog2e / sqrtf((float)D);
     const dim3 grid(bv.n_decode_work * kv.Hkv);
     const int G = Hq / kv.Hkv;                      // 1, 2, 4 or 8: checked when the instance is created
@@ -915,7 +916,7 @@ static void launch_decode_d(const QkvSource& qkv, [[maybe_unused]] const float* 
                 : qkv.partial                       ? attn_decode_kernel<D, kPartialSums, FEW>
                 : bv.n_decode_work < 2 * bv.n_decode ? attn_decode_kernel<D, kProjection, MANY>
                                                     : attn_decode_kernel<D, kProjection, FEW>;
-    hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, qkv, rope_tab, partial, out, bv, kv, Hq, G, scale_log2);
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, qkv, rope_tab, partial, out, bv, kv, Hq, G, scale_log2, (int)combine);
     if (bv.n_decode_work == bv.n_decode) return;    // one chunk each: nothing to combine
 #else
     const act_t* q = qkv.qkv;
@@ -926,14 +927,14 @@ static void launch_decode_d(const QkvSource& qkv, [[maybe_unused]] const float* 
         default: hipLaunchKernelGGL((attn_decode_kernel<D, 8>), grid, dim3(256), 0, st, q, partial, bv, kv, Hq, G, scale_log2); break;
     }
 #endif
-    hipLaunchKernelGGL(attn_combine_kernel<D>, dim3(bv.n_decode, Hq), dim3(D), 0, st, partial, out, bv, Hq);
+    if (combine) hipLaunchKernelGGL(attn_combine_kernel<D>, dim3(bv.n_decode, Hq), dim3(D), 0, st, partial, out, bv, Hq);
 }
 
 void launch_attn_decode(const QkvSource& qkv, const float* rope_tab, act_t* out, float* partial, const BatchView& bv,
-                        const KvView& kv, int Hq, hipStream_t st) {
+                        const KvView& kv, int Hq, bool combine, hipStream_t st) {
     if (bv.n_decode <= 0) return;
-    if (kv.d == 128) launch_decode_d<128>(qkv, rope_tab, out, partial, bv, kv, Hq, st);
-    else launch_decode_d<64>(qkv, rope_tab, out, partial, bv, kv, Hq, st);
+    if (kv.d == 128) launch_decode_d<128>(qkv, rope_tab, out, partial, bv, kv, Hq, combine, st);
+    else launch_decode_d<64>(qkv, rope_tab, out, partial, bv, kv, Hq, combine, st);
 }
 
 }  // namespace bz

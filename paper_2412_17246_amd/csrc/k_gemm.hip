@@ -14,12 +14,6 @@
 
 namespace bz {
 
-// silu(z) = z / (1 + exp(-z)) with the hardware's exponential and reciprocal (about 1 ulp each; every
-// use rounds the product to bf16 afterwards).  An IEEE division costs ten instructions per element in the
-// epilogue of the gate/up projection, which has 128 of them per lane and tile.  One definition for every
-// kernel that applies SwiGLU, so that they agree bit for bit.
-__device__ __forceinline__ float silu_fast(float z) { return z * __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
-
 #ifndef BZ_FP32_DEBUG
 
 constexpr int kBK = 64;            // K step per LDS stage
