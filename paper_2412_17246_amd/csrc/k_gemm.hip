@@ -836,11 +836,13 @@ __global__ __launch_bounds__(256, 1) void gemm_mid_kernel(const bf16* __restrict
     using Yes = std::true_type;
     using No = std::false_type;
 
-    // With one row of tiles the walk over K starts tile_n / n_tiles of the way in when the row pitch is a power of two, as
-    // in the decode kernel below and for its reason (161 rows: 7B gate/up 47.4 -> 44.7 us, 8B-GQA 55.7 -> 51.7).  With several, the
-    // workgroups that share a weight tile and those that share activations do better in step (552 rows: 8B-GQA qkv 34.5 in
-    // step, 40.8 shifted).
-    const int rot = (m_tiles == 1 && (K & (K - 1)) == 0 && n >= 32) ? (int)(((long long)tile_n * n) / n_tiles) : 0;
+    // The walk over K does not start at the first k-tile everywhere, or the whole chip would read one column of all weight rows
+    // at a time, which crowds onto few memory channels.  With one row of tiles it starts tile_n / n_tiles of the way in when the
+    // row pitch is a power of two, as in the decode kernel below (161 rows: 7B gate/up 47.4 -> 44.7 us, 8B-GQA 55.7 -> 51.7).
+    // With several, the workgroups that share a weight tile and those that share activations do better in step (552 rows: 8B-GQA
+    // qkv 34.5 in step, 40.8 shifted each by itself), so each XCD, where the sharing is, has one start (301 rows: four layers of the
+    // 7B shape 795 -> 763 us, of 8B-GQA 815 -> 787; other pitches and row counts unchanged; two starts per XCD the same).
+    const int rot = n < 32 ? 0 : m_tiles > 1 ? xcd * n / 8 : (K & (K - 1)) == 0 ? (int)(((long long)tile_n * n) / n_tiles) : 0;
     auto koff_of = [&](int j) { const int r = j + rot; return (kt0 + (r >= n ? r - n : r)) * (kBK * 2); };
     const int first = n < S ? n : S;
 #pragma unroll

@@ -142,6 +142,17 @@ def test_gemm_mid_sized_edges(torch, mode, M, N, K):
     test_gemm(torch, False, mode, M, N, K)
 
 
+@pytest.mark.parametrize("mode,M,N,K", [(0, 300, 8300, 1984), (0, 300, 8300, 2048), (1, 300, 8300, 2112), (2, 420, 8300, 2496)])
+def test_gemm_mid_sized_walks(torch, mode, M, N, K):
+    """Several rows of tiles over one range of 31 k-tiles (every walk from its start), and of 32, 33 and 39 (an XCD's start of its
+    own, the walk wrapping around)."""
+    from paper_2412_17246_amd import op_gemm_plan
+    from paper_2412_17246_amd.binding import BZ_GEMM_MID
+    p = op_gemm_plan(mode, M, N, K)
+    assert p.kernel == BZ_GEMM_MID and p.tiles_m > 1 and p.ranges == 1
+    test_gemm(torch, False, mode, M, N, K)
+
+
 # Every tile of the mid-sized kernel, plain and gated, with one row of tiles where a problem of this size has that, and more:
 # K of one k-tile, and of twice what the tile's ring holds and more.  (rows, weight rows of the tile; mode, M, N, K)
 MID_TILES = [
