@@ -438,7 +438,9 @@ constexpr int kDecodeMaxG = 8;
 // A sequence with a single chunk gets its output here; the combine kernel leaves it alone.
 //
 // SRC: what the new token's values come as: the projection, its partial sums, or rotated and appended already
-// (decode_append_apart).
+// (decode_append_apart).  In the last case the queries, too, are requested before the stream and go through LDS: requested behind
+// it by every wave, they held the score product back until all of K and V had arrived (7B shape, 161 sequences 273 -> 264 us,
+// 13B, 83 sequences 300 -> 294).
 // WAVES per SIMD, that is workgroups per CU, set outright: for d = 128 two keep the memory streams in longer runs than three,
 // which the registers would allow where the projection is plain (83 sequences of 40 heads, 402 -> 392 us; 240 of 8 with four
 // query heads each 371 -> 366), except where most caches end within their first chunk (250 sequences of 40 heads 178 -> 170 with
@@ -505,9 +507,13 @@ __global__ __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) __launch_bounds__(
         ra = *reinterpret_cast<const bf16x4*>(src.qkv + at);
         rb = *reinterpret_cast<const bf16x4*>(src.qkv + at + second);
     }
+    bf16x8 qr;                                               // kAppended: 8 values of the G * D, at most 128 threads' worth
     if (FUSED) {
         cs0 = *reinterpret_cast<const f32x4*>(cs);
         cs1 = *reinterpret_cast<const f32x4*>(cs + 4);
+    } else {
+        const int i = tid < G * (D / 8) ? tid : G * (D / 8) - 1;
+        qr = *reinterpret_cast<const bf16x8*>(src.qkv + (size_t)t * nqkv + kvh * G * D + i * 8);
     }
     __builtin_amdgcn_sched_barrier(0);                       // these go out before the stream
 
@@ -540,17 +546,6 @@ __global__ __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) __launch_bounds__(
                 for (int db = 0; db < DB; ++db)
                     vf[b][tt][db] =
                         stream_load(reinterpret_cast<const bf16x8*>(Vc + boff[b] + lane_v + (2 * tt * D + db * 32) * 8));
-    }
-    bf16x8 qa[KS];
-    if (!FUSED && live) {
-        const bf16* q = src.qkv + (size_t)t * nqkv + kvh * G * D;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            if (lq < G) qa[ks] = *reinterpret_cast<const bf16x8*>(q + lq * D + ks * 16 + lh * 8);
-            else
-#pragma unroll
-                for (int i = 0; i < 8; ++i) qa[ks][i] = (bf16)0.f;
-        }
     }
     __builtin_amdgcn_sched_barrier(0);
     if (FUSED) {
@@ -604,7 +599,8 @@ __global__ __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) __launch_bounds__(
             }
         }
     }
-    if (FUSED) {
+    if (!FUSED && tid < G * (D / 8)) *reinterpret_cast<bf16x8*>(&qs[0][0] + tid * 8) = qr;
+    {
         // hand-over through LDS without waiting for the stream (a full barrier would drain it)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
         __builtin_amdgcn_s_barrier();
@@ -628,8 +624,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) __launch_bounds__(
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             bf16x8 qf = {};
-            if (!FUSED) qf = qa[ks];
-            else if (lq < G) qf = *reinterpret_cast<const bf16x8*>(&qs[lq][ks * 16 + lh * 8]);
+            if (lq < G) qf = *reinterpret_cast<const bf16x8*>(&qs[lq][ks * 16 + lh * 8]);
 #pragma unroll
             for (int b = 0; b < 2; ++b) sacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[b][ks], qf, sacc[b], 0, 0, 0);
         }
