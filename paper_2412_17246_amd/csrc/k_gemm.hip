@@ -1075,20 +1075,24 @@ static bool launch_mid(int mode, const MidPlan& p, const bf16* x, const bf16* w,
 //
 // RB = 1: 64-row tiles, four 16 KiB stages, two workgroups per CU: short streams (small matrices),
 // where many small workgroups start and finish faster.
-// RB = 2: 128-row tiles, five 24 KiB stages, one workgroup per CU: long streams.  Every tile re-reads
+// RB = 2: 128-row tiles, one workgroup per CU: long streams.  Every tile re-reads
 // the activations from L2, which costs about a tenth of the time at 64 rows; twice the rows halve
-// that, and the deeper ring keeps 64 KiB of weights in flight per CU instead of 48.  Measured against
-// RB = 1 on the decode shapes (64 rows): 8B-GQA down projection 31.4 -> 28.0 us, gate/up unchanged;
-// 70B qkv 40.9 -> 37.1, o 36.1 -> 37.8, gate/up 185 -> 168, down 96.5 -> 78.5 us.  (Three stages and
-// two workgroups per CU win on some of these shapes and lose on others.)
-// ---------------------------------------------------------------------------------------------
-template <int RB> struct SkCfg {
-    static constexpr int kXBytes = 64 * kBK * (int)sizeof(bf16);              // activations of a stage: 8 KiB
+// that.  Measured against RB = 1 on the decode shapes (64 rows, five stages): 8B-GQA down projection 31.4 -> 28.0 us, gate/up
+// unchanged; 70B qkv 40.9 -> 37.1, o 36.1 -> 37.8, gate/up 185 -> 168, down 96.5 -> 78.5 us.
+//
+// TB: 32-row blocks of the activations in a stage; with one (up to 32 rows) the four waves share out the weight rows alone.
+// ST: stages.  A stage of 64 activation rows costs as many loads whether they are real or not, and behind 32 real ones
+// half of them; four stages are better than five or seven, in either form.  Us at 32 rows: 70B gate/up 161 -> 148, down 77.2 ->
+// 75.3, qkv 32.0 -> 30.2, o 26.8 -> 25.5; at 20 rows: 13B 47.7 -> 45.4, 28.8 -> 27.5 (qkv), 25.9 -> 24.6 (down); at 12: 7B 34.4 ->
+// 29.6 (with the tiles as many as CUs, below), 19.2 -> 17.7, 18.7 -> 17.6; at 24: 8B-GQA 37.1 -> 36.4, 20.6 -> 20.4.  Above 32 rows four
+// stages instead of five: 13B (48) 49.9 -> 49.5, 30.9 -> 30.4, 27.2 -> 26.7, 7B gate/up (64) 36.8 -> 35.5.  Where there are more
+// tiles than CUs three, which leave room for two workgroups: 70B gate/up (64) 172 -> 161; elsewhere they lose (13B 52.5, 31.1, 27.6).
+template <int RB, int TB = 2, int ST = RB == 1 ? 4 : 5> struct SkCfg {
+    static constexpr int kXBytes = 32 * TB * kBK * (int)sizeof(bf16);         // activations of a stage: 4 KiB * TB
     static constexpr int kStage = kXBytes + 64 * RB * kBK * (int)sizeof(bf16);  // + weights 8 KiB * RB
-    static constexpr int kStages = RB == 1 ? 4 : 5;
+    static constexpr int kStages = ST;
     static constexpr int kLds = kStage * kStages;
     static constexpr int kPerCu = kLds * 2 <= 160 * 1024 ? 2 : 1;
-    static constexpr int kSlots = 256 * kPerCu;                               // workgroups the chip holds at a time
 };
 // Weight matrices from this size on count as long streams: RB = 2, and loads with the non-temporal cache
 // policy (read once per step; streamed that way a long read runs faster - gate/up of the 8B shape -6 % -
@@ -1102,15 +1106,17 @@ constexpr size_t kSkStreamBytes = (size_t)64 << 20;
 // TAIL: K is a multiple of 8 and not of 64.  The last k-tile's pieces past the end re-read the row's last piece and count as
 // zero, both operands, when they are multiplied.  (Such shapes went to the 64x128 kernel before, with a workgroup per 128
 // weight rows and K uncut: 688 -> 256 at one row 10.0 -> 4.8 us.)
-template <bool GU, bool NT, int RB, bool TAIL>
-__global__ __launch_bounds__(256, SkCfg<RB>::kPerCu) void gemm_skinny_kernel(const bf16* __restrict__ X,
+template <bool GU, bool NT, int RB, int TB, int ST, bool TAIL>
+__global__ __launch_bounds__(256, (SkCfg<RB, TB, ST>::kPerCu)) void gemm_skinny_kernel(const bf16* __restrict__ X,
                                                                              const bf16* __restrict__ W,
                                                                              float* __restrict__ partial,
                                                                              bf16* __restrict__ C, int M, int Nrows, int K,
                                                                              int n_tiles, int kt_per_split, int rows) {
-    using Cfg = SkCfg<RB>;
+    using Cfg = SkCfg<RB, TB, ST>;
     constexpr int kStage = Cfg::kStage, kStages = Cfg::kStages, kXBytes = Cfg::kXBytes;
-    constexpr int LPS = 2 + 2 * RB;                   // loads per wave and stage
+    constexpr int LPS = TB + 2 * RB;                  // loads per wave and stage
+    constexpr int NB = TB == 2 ? RB : RB / 2;         // 32-row blocks of a wave
+    static_assert(NB >= 1, "TB = 1: the four waves share out the weight rows alone");
     constexpr int HALF = 32 * RB;                     // rows per wave along the features (GU: rows per factor)
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
     const int tile_n = blockIdx.x % n_tiles, split = blockIdx.x / n_tiles;
@@ -1125,16 +1131,17 @@ __global__ __launch_bounds__(256, SkCfg<RB>::kPerCu) void gemm_skinny_kernel(con
     const int n = kt1 - kt0;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wf = wave >> 1, wt = wave & 1;          // feature half, token half
+    const int wf = wave >> 1, wt = TB == 2 ? wave & 1 : 0;          // feature half, token half
+    const int b0 = TB == 2 ? 0 : (wave & 1) * NB;                   // first block of the half's RB
     const int lrow = lane & 31, lk = lane >> 5;
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
 
-    // loader: 1 KiB chunks of 8 rows; the first 8 chunks of a stage hold the activation rows, the
-    // 8 * RB after them the weight rows; this wave fills 2 of the former and 2 * RB of the latter
-    uint32_t x_src[2], w_src[2 * RB];
+    // loader: 1 KiB chunks of 8 rows; the first 4 * TB chunks of a stage hold the activation rows, the
+    // 8 * RB after them the weight rows; this wave fills TB of the former and 2 * RB of the latter
+    uint32_t x_src[TB], w_src[2 * RB];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int row = (wave * 2 + j) * 8 + (lane >> 3);
+    for (int j = 0; j < TB; ++j) {
+        const int row = (wave * TB + j) * 8 + (lane >> 3);
         int xr = row;
         if (xr > M - 1) xr = M - 1;
         x_src[j] = ((uint32_t)xr * (uint32_t)K + ((lane & 7) ^ swz(row)) * 8) * 2u;
@@ -1166,23 +1173,23 @@ __global__ __launch_bounds__(256, SkCfg<RB>::kPerCu) void gemm_skinny_kernel(con
             return TAIL && c >= left ? (uint32_t)(c - (left - 8)) * 2u : 0u;
         };
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-            __builtin_amdgcn_global_load_lds((gptr_t)(xk + x_src[j] - back((wave * 2 + j) * 8 + (lane >> 3))),
-                                             (lptr_t)(sb + (wave_u * 2 + j) * 1024), 16, 0, 0);
+        for (int j = 0; j < TB; ++j)
+            __builtin_amdgcn_global_load_lds((gptr_t)(xk + x_src[j] - back((wave * TB + j) * 8 + (lane >> 3))),
+                                             (lptr_t)(sb + (wave_u * TB + j) * 1024), 16, 0, 0);
 #pragma unroll
         for (int j = 0; j < 2 * RB; ++j)
             __builtin_amdgcn_global_load_lds((gptr_t)(wk + w_src[j] - back((wave * 2 * RB + j) * 8 + (lane >> 3))),
                                              (lptr_t)(sb + kXBytes + (wave_u * 2 * RB + j) * 1024), 16, 0, NT ? 2 : 0);
     };
 
-    f32x16 acc[RB];
+    f32x16 acc[NB];
 #pragma unroll
-    for (int b = 0; b < RB; ++b)
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
     const int sw = swz(lrow);
     const int x_off = (wt * 32 + lrow) * 128;
-    const int w_off = kXBytes + (wf * HALF + lrow) * 128;
+    const int w_off = kXBytes + (wf * HALF + b0 * 32 + lrow) * 128;
 
     // Every workgroup would walk its k-tiles in the same order at about the same pace, so that at any moment the
     // whole chip reads the same 128-byte column of thousands of weight rows; when the row pitch is a power of two
@@ -1201,8 +1208,7 @@ __global__ __launch_bounds__(256, SkCfg<RB>::kPerCu) void gemm_skinny_kernel(con
     for (int i = 0; i < n; ++i) {
         // tile i must have landed; the tiles requested after it (LPS loads each) may still be in flight
         const int later = (n - 1 - i < kStages - 2) ? n - 1 - i : kStages - 2;
-        if (later >= 4) __builtin_amdgcn_s_waitcnt(lds_wait(4 * LPS));
-        else if (later == 3) __builtin_amdgcn_s_waitcnt(lds_wait(3 * LPS));
+        if (later >= 3) __builtin_amdgcn_s_waitcnt(lds_wait(3 * LPS));
         else if (later == 2) __builtin_amdgcn_s_waitcnt(lds_wait(2 * LPS));
         else if (later == 1) __builtin_amdgcn_s_waitcnt(lds_wait(LPS));
         else __builtin_amdgcn_s_waitcnt(lds_wait(0));
@@ -1219,7 +1225,7 @@ __global__ __launch_bounds__(256, SkCfg<RB>::kPerCu) void gemm_skinny_kernel(con
             const bool past = TAIL && kmap(i) * kBK + (ks * 2 + lk) * 8 >= K;
             if (past) xf = bf16x8{};
 #pragma unroll
-            for (int b = 0; b < RB; ++b) {
+            for (int b = 0; b < NB; ++b) {
                 bf16x8 wfr = *reinterpret_cast<const bf16x8*>(st + w_off + b * 32 * 128 + ko);
                 if (past) wfr = bf16x8{};
                 acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wfr, xf, acc[b], 0, 0, 0);
@@ -1236,24 +1242,24 @@ __global__ __launch_bounds__(256, SkCfg<RB>::kPerCu) void gemm_skinny_kernel(con
         __syncthreads();
         if (wf == 1) {
 #pragma unroll
-            for (int b = 0; b < RB; ++b)
+            for (int b = 0; b < NB; ++b)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) ex[((wt * RB + b) * 16 + r) * 64 + lane] = acc[b][r];
+                for (int r = 0; r < 16; ++r) ex[((wt * RB + b0 + b) * 16 + r) * 64 + lane] = acc[b][r];
         }
         __syncthreads();
         if (wf == 0 && m < M) {
 #pragma unroll
-            for (int b = 0; b < RB; ++b)
+            for (int b = 0; b < NB; ++b)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    const int lf = b * 32 + 8 * g + 4 * lk;
+                    const int lf = (b0 + b) * 32 + 8 * g + 4 * lk;
                     const int nn = n0 + lf;
                     if (lf < tr && nn < Nh) {
                         bf16x4 w4;
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             const float o = acc[b][4 * g + e];
-                            const float u = ex[((wt * RB + b) * 16 + 4 * g + e) * 64 + lane];
+                            const float u = ex[((wt * RB + b0 + b) * 16 + 4 * g + e) * 64 + lane];
                             w4[e] = (bf16)(silu_fast(o) * u);
                         }
                         *reinterpret_cast<bf16x4*>(C + (size_t)m * Nh + nn) = w4;
@@ -1265,10 +1271,10 @@ __global__ __launch_bounds__(256, SkCfg<RB>::kPerCu) void gemm_skinny_kernel(con
     if (m >= M) return;
     float* prow = partial + ((size_t)split * M + m) * Nrows;           // partial[split][m][n]
 #pragma unroll
-    for (int b = 0; b < RB; ++b)
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-            const int lf = (GU ? 0 : wf * HALF) + b * 32 + 8 * g + 4 * lk;      // feature inside the tile (GU: the factor)
+            const int lf = (GU ? 0 : wf * HALF) + (b0 + b) * 32 + 8 * g + 4 * lk;      // feature inside the tile (GU: the factor)
             const int f = n0 + lf;
             const int nn = GU ? wf * Nh + f : f;
             if (lf < tr && f < (GU ? Nh : Nrows))
@@ -1323,7 +1329,7 @@ static void skinny_plan_rb(SkinnyPlan& p, int Nrows, int nk) {
     // aim at one unit per CU although two fit: half as many K slices halve the partial sums
     // written here and re-read by the consumer (8B decode at 64 tokens: qkv 17.7 -> 16.5 us, o 14.8 -> 12.0 us; a
     // target of 128 or 192 units is slower again, 384 and more as well).
-    const int kSlots = RB == 1 ? 256 : SkCfg<RB>::kSlots;
+    constexpr int kSlots = 256;
     p.rb = RB;
     p.n_tiles = (Nrows + kTile - 1) / kTile;
     int target = kSlots / p.n_tiles;              // aim at filling every workgroup slot once
@@ -1333,16 +1339,16 @@ static void skinny_plan_rb(SkinnyPlan& p, int Nrows, int nk) {
     if (p.kt_per_split < min_kt) p.kt_per_split = min_kt;
     p.ksplit = (nk + p.kt_per_split - 1) / p.kt_per_split;
     // A grid a little short of a multiple of the slots leaves some of them idle for the whole kernel (448
-    // workgroups on 512 slots: an eighth of the chip).  Narrower tiles (down to three quarters of the rows,
-    // in steps of 8) bring the count up to the multiple; narrower than that, the activations would be
-    // re-read by too many tiles.
+    // workgroups on 512 slots: an eighth of the chip).  Narrower tiles (down to half of the rows, in steps of 8)
+    // bring the count up to the multiple; narrower than that, the activations would be re-read by too many tiles.
+    // (88 of 128 rows: 7B gate/up 172 -> 251 workgroups, 30.8 -> 29.6 us at 12 rows, 39.2 -> 37.5 at 64.)
     p.rows = kTile;
     const int total = p.n_tiles * p.ksplit;
     const int rounds = (total + kSlots - 1) / kSlots;
     const int want_tiles = rounds * kSlots / p.ksplit;
     if (want_tiles > p.n_tiles) {
         const int r = ((Nrows + want_tiles - 1) / want_tiles + 7) / 8 * 8;
-        if (r >= kTile * 3 / 4 && r < kTile) {
+        if (r >= kTile / 2 && r < kTile) {
             p.rows = r;
             p.n_tiles = (Nrows + r - 1) / r;
         }
@@ -1420,19 +1426,26 @@ struct SkinnyArgs {
     int M, Nrows, K, n_tiles, kt_per_split, rows;
 };
 
-template <bool GU, bool NT, int RB, bool TAIL>
+template <bool GU, bool NT, int RB, int TB, int ST, bool TAIL>
 static void skinny_launch(dim3 grid, hipStream_t st, const SkinnyArgs& g) {
-    constexpr int lds = SkCfg<RB>::kLds;
+    constexpr int lds = SkCfg<RB, TB, ST>::kLds;
     static LdsLimit limit;               // per instantiation: the LDS limit is a per-function setting
-    (void)limit.raise(reinterpret_cast<const void*>(gemm_skinny_kernel<GU, NT, RB, TAIL>), lds);
-    hipLaunchKernelGGL((gemm_skinny_kernel<GU, NT, RB, TAIL>), grid, dim3(256), lds, st, g.a, g.w, g.ws, g.direct, g.M,
+    (void)limit.raise(reinterpret_cast<const void*>(gemm_skinny_kernel<GU, NT, RB, TB, ST, TAIL>), lds);
+    hipLaunchKernelGGL((gemm_skinny_kernel<GU, NT, RB, TB, ST, TAIL>), grid, dim3(256), lds, st, g.a, g.w, g.ws, g.direct, g.M,
                        g.Nrows, g.K, g.n_tiles, g.kt_per_split, g.rows);
 }
 
-template <bool GU, bool NT, int RB>
+template <bool GU, bool NT, int RB, int TB, int ST>
 static void skinny_go(dim3 grid, hipStream_t st, const SkinnyArgs& g) {
-    if (g.K % kBK) skinny_launch<GU, NT, RB, true>(grid, st, g);
-    else skinny_launch<GU, NT, RB, false>(grid, st, g);
+    if (g.K % kBK) skinny_launch<GU, NT, RB, TB, ST, true>(grid, st, g);
+    else skinny_launch<GU, NT, RB, TB, ST, false>(grid, st, g);
+}
+
+template <bool GU>
+static void skinny_stream(dim3 grid, hipStream_t st, const SkinnyArgs& g) {
+    if (g.M <= 32) skinny_go<GU, true, 2, 1, 4>(grid, st, g);
+    else if (grid.x > 256) skinny_go<GU, true, 2, 2, 3>(grid, st, g);
+    else skinny_go<GU, true, 2, 2, 4>(grid, st, g);
 }
 
 // Split-K partial sums only: partial[ksplit][M][Nrows] (Nrows = 2N in SwiGLU mode).  The caller
@@ -1448,9 +1461,9 @@ static int launch_skinny_partial(int mode, const bf16* a, const bf16* w, bf16* c
     const SkinnyArgs args{a, w, ws, direct, M, Nrows, K, p.n_tiles, p.kt_per_split, p.rows};
     const bool gu = mode == 2;
     if (p.rb == 2) {
-        if (gu) skinny_go<true, true, 2>(grid, st, args); else skinny_go<false, true, 2>(grid, st, args);
+        if (gu) skinny_stream<true>(grid, st, args); else skinny_stream<false>(grid, st, args);
     } else {
-        if (gu) skinny_go<true, false, 1>(grid, st, args); else skinny_go<false, false, 1>(grid, st, args);
+        if (gu) skinny_go<true, false, 1, 2, 4>(grid, st, args); else skinny_go<false, false, 1, 2, 4>(grid, st, args);
     }
     if (direct) return 0;
     return p.ksplit;

@@ -142,6 +142,34 @@ def test_gemm_mid_sized_edges(torch, mode, M, N, K):
     test_gemm(torch, False, mode, M, N, K)
 
 
+@pytest.mark.parametrize("mode,N,K,narrow", [(0, 8204, 4104, False), (1, 4100, 8256, False), (2, 5000, 4160, False), (1, 33000, 1024, True),
+                                            (2, 16648, 1032, True), (2, 11004, 1536, True)])
+def test_gemm_long_streams_of_few_and_many_rows(torch, mode, N, K, narrow):
+    """Decode-sized products of 64 MiB of weights and more: up to 32 rows the activations take half of the stage, with more tiles
+    than CUs it has fewer stages, and tiles narrow down to fill the chip; with and without a K tail.  A row's bits do not depend
+    on the other rows."""
+    from paper_2412_17246_amd import op_gemm, op_gemm_plan, op_gemm_workspace_bytes
+    from paper_2412_17246_amd.binding import BZ_GEMM_DECODE
+    rng = np.random.default_rng([12, mode, N, K])
+    a, ar = U.f64_to_device(rng.standard_normal((64, K)), False)
+    w, wr = U.f64_to_device(rng.standard_normal((2 * N if mode == 2 else N, K)) * (2.0 / np.sqrt(K)), False)
+    r, rr = U.f64_to_device(rng.standard_normal((64, N)), False)
+    assert w.numel() * 2 >= 64 << 20
+    want = O.linear(ar, wr) if mode == 0 else rr + O.linear(ar, wr) if mode == 1 else O.swiglu(ar, wr[:N], wr[N:])
+    whole = None
+    for M in (64, 33, 32, 31, 5):
+        p = op_gemm_plan(mode, M, N, K)
+        assert p.kernel == BZ_GEMM_DECODE and (p.tile_cols < 96) == narrow
+        ws = torch.empty(op_gemm_workspace_bytes(mode, M, N, K), dtype=torch.uint8, device="cuda")
+        c = torch.zeros_like(r[:M])
+        op_gemm(mode, a[:M], w, r[:M] if mode == 1 else None, c, M, N, K, workspace=ws)
+        got = U.from_device(c)
+        assert U.rel_err(got, want[:M]) <= U.BF16_TOL
+        U.assert_rms(got, want[:M], U.RMS_BF16_OP)
+        whole = c if whole is None else whole
+        assert torch.equal(c.view(torch.int16), whole[:M].view(torch.int16)), M
+
+
 @pytest.mark.parametrize("mode,M,N,K", [(0, 300, 8300, 1984), (0, 300, 8300, 2048), (1, 300, 8300, 2112), (2, 420, 8300, 2496)])
 def test_gemm_mid_sized_walks(torch, mode, M, N, K):
     """Several rows of tiles over one range of 31 k-tiles (every walk from its start), and of 32, 33 and 39 (an XCD's start of its
