@@ -5,16 +5,18 @@
 //
 // Bound: the weights, read once.  One workgroup per CU takes a run of weight rows; its 8 waves share out K, each streaming its
 // part of 16 to 32 rows per step, one cache line per row, through a ring of its own in LDS, with no barrier but one per tile:
-// that keeps about 128 KiB in flight per CU.  Tried before: the weights straight into registers in the matrix instruction's
+// that keeps 32 to 96 KiB in flight per CU.  Tried before: the weights straight into registers in the matrix instruction's
 // operand order (16 rows of 64 bytes per load): 8B-GQA gate/up 48 us against 38.6, a lane's neighbours being in other lines.
 // The norm hides behind the first weights: its rows are requested first, and it runs while the ring fills.
 //
-// Measured (one row, 8B-GQA / 7B / 13B / 70B, us): QKV with the norm 11.4 / 18.6 / 27 / 29, output projection with the combine
-// 10.5 / 10.8 / 15 / 30, gate/up with the norm 38.8 (6.1 TB/s) / 32 / 47 / 146 (6.4 TB/s), down 20 / 16.8 / 24.9 / 74.  As
-// separate kernels at 8B-GQA: norms 4.2 each, QKV 9.8 to 12, output projection 7.6, combine 4.5, gate/up 38, down 20.  Four
-// layers of one step each, before and after: 8B-GQA one row 401 -> 363, four 405 -> 380; two layers: 70B one row 613 -> 592, four
-// 620 -> 617, 13B 279 -> 263 and 303 -> 299, 7B 210 -> 192 and 227 -> 214.  At 8 rows the rows' part of the norm, done by every
-// workgroup, outweighs the launches saved (8B-GQA 418 -> 423).
+// Measured (one row, 8B-GQA / 7B / 13B / 70B, us): QKV with the norm 10.6 / 18 / 27 / 28.5, output projection with the combine
+// 8.9 / 10 / 14 / 29.6, gate/up with the norm 37.7 (6.2 TB/s) / 31 / 46 / 145 (6.5 TB/s), down 19.6 / 16.5 / 24.4 / 73.5.  As
+// separate kernels at 8B-GQA: norms 4.2 each, QKV 9.8 to 12, output projection 7.6, combine 4.5, gate/up 38, down 20.  One layer,
+// before and after: 8B-GQA one row 101 -> 88, four 101 -> 94; 70B one 307 -> 296, four 310 -> 308; 13B one 139 -> 130, three
+// 148 -> 143; 7B one 105 -> 93.  Beyond four rows the rows' part of the norm, done by every workgroup, outweighs the launches
+// saved on some shapes (8B-GQA five 105 -> 103, eight 110.5 -> 110; 7B 112 -> 114 and 125 -> 128).
+#include <type_traits>
+
 #include "common.h"
 
 namespace bz {
@@ -49,6 +51,23 @@ template <int SRC, int NR> struct FewCfg {
 
 __device__ __forceinline__ int few_swz(int row) { return (row & 7) ^ ((row >> 3) & 1); }
 __device__ __forceinline__ constexpr int few_vmcnt(int n) { return ((n >> 4) << 14) | 0x0f70 | (n & 15); }
+
+// Sum over the wave, in lane 63: shifts inside rows of 16 lanes, then broadcasts of the rows' last lanes.  The norm is a chain of
+// dependent steps here, and a shuffle is a trip through LDS (the smallest session 511 -> 498 us).
+__device__ __forceinline__ float last_lane_sum(float v) {
+    auto moved = [](float x, auto ctrl, auto rows) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value,
+                                                                     decltype(rows)::value, 0xf, false));
+    };
+    using All = std::integral_constant<int, 0xf>;
+    v += moved(v, std::integral_constant<int, 0x111>(), All());                                  // row_shr:1, 2, 4, 8
+    v += moved(v, std::integral_constant<int, 0x112>(), All());
+    v += moved(v, std::integral_constant<int, 0x114>(), All());
+    v += moved(v, std::integral_constant<int, 0x118>(), All());
+    v += moved(v, std::integral_constant<int, 0x142>(), std::integral_constant<int, 0xa>());     // row_bcast:15
+    v += moved(v, std::integral_constant<int, 0x143>(), std::integral_constant<int, 0xc>());     // row_bcast:31
+    return v;
+}
 
 struct FewArgs {
     const bf16* x;           // rows; kNorm: the residual stream
@@ -196,8 +215,8 @@ __global__ __launch_bounds__(kFewThreads, 2) void gemm_few_kernel(const FewArgs 
             float ss = 0.f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) ss = fmaf((float)xv[q][e], (float)xv[q][e], ss);
-            ss = wave_sum(tid + (wide ? (q & 1) * kFewThreads : 0) < nvec ? ss : 0.f);
-            if (lane == 0) ssq[q * NW + wave] = ss;
+            ss = last_lane_sum(tid + (wide ? (q & 1) * kFewThreads : 0) < nvec ? ss : 0.f);
+            if (lane == 63) ssq[q * NW + wave] = ss;
         }
         lds_barrier();
 #pragma unroll
@@ -335,19 +354,22 @@ static void launch_few_d(const FewArgs& a, hipStream_t st) {
     hipLaunchKernelGGL(kern, dim3((a.units + a.per_wg - 1) / a.per_wg), dim3(kFewThreads), lds, st, a);
 }
 
-template <int EPI, int NR, int D2, int D4>
+// Steps in flight: as few as keep the stream going, because what is requested first holds back the norm or the combine, whose
+// own values are requested before but unpacked after it: with rings of about 128 KiB (8 steps of 16 rows, 5 of 24, 4 of 32) four
+// decode steps of the 8B-GQA shape take 1454 us, with 4, 3 and 2 1406, with these 1402, with 2 everywhere 1414.
+template <int EPI, int NR, int D>
 static void launch_few_norm(const FewArgs& a, hipStream_t st) {
     const int vectors = a.M * few_vectors(a.K);
-    if (vectors > 4) launch_few_d<kNorm, EPI, NR, D4, 8>(a, st);
-    else if (vectors > 2) launch_few_d<kNorm, EPI, NR, D4, 4>(a, st);
-    else launch_few_d<kNorm, EPI, NR, D2, 2>(a, st);
+    if (vectors > 4) launch_few_d<kNorm, EPI, NR, D, 8>(a, st);
+    else if (vectors > 2) launch_few_d<kNorm, EPI, NR, D, 4>(a, st);
+    else launch_few_d<kNorm, EPI, NR, D, 2>(a, st);
 }
 
-template <int NR, int D1, int D2>
+template <int NR, int D>
 static void launch_few_combine(const FewArgs& a, hipStream_t st) {
-    if (a.M == 2) launch_few_d<kCombine, 1, NR, D2, 8, 2>(a, st);
-    else if (a.chunks <= 8) launch_few_d<kCombine, 1, NR, D1, 8, 1>(a, st);
-    else launch_few_d<kCombine, 1, NR, D1, 16, 1>(a, st);
+    if (a.M == 2) launch_few_d<kCombine, 1, NR, D, 8, 2>(a, st);
+    else if (a.chunks <= 8) launch_few_d<kCombine, 1, NR, D, 8, 1>(a, st);
+    else launch_few_d<kCombine, 1, NR, D, 16, 1>(a, st);
 }
 
 // Weight rows per workgroup (one per CU), in groups of 4, and the row groups of 8 of a tile: as many as they are, up to four;
@@ -368,9 +390,9 @@ bool few_combines(const BatchView& bv, int qd) {
 void launch_few_out(const float* partial, const BatchView& bv, const KvView& kv, const bf16* w, act_t* x, int H, int qd, hipStream_t st) {
     FewArgs a{nullptr, nullptr, 0.f, w, x, x, bv.T, H, qd, 0, 0, partial, bv.kv_before, kv.d, bv.decode_chunks};
     switch (few_cut(a)) {
-        case 2: launch_few_combine<2, 8, 6>(a, st); break;
-        case 3: launch_few_combine<3, 5, 4>(a, st); break;
-        default: launch_few_combine<4, 4, 3>(a, st);
+        case 2: launch_few_combine<2, 3>(a, st); break;
+        case 3: launch_few_combine<3, 2>(a, st); break;
+        default: launch_few_combine<4, 2>(a, st);
     }
 }
 
@@ -380,18 +402,17 @@ void launch_few(int mode, const act_t* x, const bf16* gain, float eps, const bf1
     const int nr = few_cut(a);
     const bool small = K <= 1024 && nr == 2;
     if (mode == 2) {
-        if (small) launch_few_norm<2, 2, 2, 2>(a, st);
-        else launch_few_norm<2, 2, 8, 5>(a, st);
+        if (small) launch_few_norm<2, 2, 2>(a, st);
+        else launch_few_norm<2, 2, 3>(a, st);
     } else if (mode == 0) {
-        if (small) launch_few_norm<0, 2, 2, 2>(a, st);
-        else if (nr == 2) launch_few_norm<0, 2, 8, 5>(a, st);
-        else if (nr == 3) launch_few_norm<0, 3, 5, 3>(a, st);
-        else launch_few_norm<0, 4, 4, 2>(a, st);
+        if (small) launch_few_norm<0, 2, 2>(a, st);
+        else if (nr == 2) launch_few_norm<0, 2, 3>(a, st);
+        else if (nr == 3) launch_few_norm<0, 3, 3>(a, st);
+        else launch_few_norm<0, 4, 2>(a, st);
     } else {
-        if (small) launch_few_d<kRows, 1, 2, 2>(a, st);
-        else if (nr == 2) launch_few_d<kRows, 1, 2, 6>(a, st);
-        else if (nr == 3) launch_few_d<kRows, 1, 3, 4>(a, st);
-        else launch_few_d<kRows, 1, 4, 3>(a, st);
+        if (nr == 2) launch_few_d<kRows, 1, 2, 2>(a, st);
+        else if (nr == 3) launch_few_d<kRows, 1, 3, 3>(a, st);
+        else launch_few_d<kRows, 1, 4, 2>(a, st);
     }
 }
 
