@@ -140,7 +140,9 @@ typedef struct bz_stats {
  * decode workgroups, the single new tokens.  Otherwise these are rotated and appended inside BZ_K_ATTN_DECODE,
  * as other queries are inside BZ_K_ATTN_PREFILL, and neither class counts that: a batch of decode steps alone
  * mostly has no BZ_K_ROPE_APPEND launches.  (fp32 debug build: every row, queries
- * included, in BZ_K_ROPE_APPEND.)  BZ_K_ATTN_DECODE includes the merge of a sequence's chunks. */
+ * included, in BZ_K_ROPE_APPEND.)  BZ_K_ATTN_DECODE includes the merge of a sequence's chunks.  Batches of one to four rows
+ * have no BZ_K_RMSNORM launches: the norms are part of BZ_K_GEMM_QKV and BZ_K_GEMM_GATEUP, and in batches of one or two decode
+ * rows the merge is part of BZ_K_GEMM_O. */
 enum {
     BZ_K_RMSNORM = 0, BZ_K_GEMM_QKV, BZ_K_ROPE_APPEND, BZ_K_ATTN_PREFILL, BZ_K_ATTN_DECODE,
     BZ_K_ATTN_COMBINE, BZ_K_GEMM_O, BZ_K_GEMM_GATEUP, BZ_K_GEMM_DOWN, BZ_K_COUNT
