@@ -840,9 +840,10 @@ __global__ __launch_bounds__(256, 1) void gemm_mid_kernel(const bf16* __restrict
     // at a time, which crowds onto few memory channels.  With one row of tiles it starts tile_n / n_tiles of the way in when the
     // row pitch is a power of two, as in the decode kernel below (161 rows: 7B gate/up 47.4 -> 44.7 us, 8B-GQA 55.7 -> 51.7).
     // With several, the workgroups that share a weight tile and those that share activations do better in step (552 rows: 8B-GQA
-    // qkv 34.5 in step, 40.8 shifted each by itself), so each XCD, where the sharing is, has one start (301 rows: four layers of the
-    // 7B shape 795 -> 763 us, of 8B-GQA 815 -> 787; other pitches and row counts unchanged; two starts per XCD the same).
-    const int rot = n < 32 ? 0 : m_tiles > 1 ? xcd * n / 8 : (K & (K - 1)) == 0 ? (int)(((long long)tile_n * n) / n_tiles) : 0;
+    // qkv 34.5 in step, 40.8 shifted each by itself), so with two or three each XCD, where the sharing is, has one start (three layers of
+    // the 7B shape, 301 rows 605 -> 586 us, 250 rows 549 -> 542, two of 70B, 250 rows 1008 -> 1002; two starts per XCD the same); with
+    // more, all are in step (shifted by XCD, 13B 700 rows 991 -> 995, 8B-GQA 1200 rows 1548 -> 1553).
+    const int rot = n < 32 || m_tiles > 3 ? 0 : m_tiles > 1 ? xcd * n / 8 : (K & (K - 1)) == 0 ? (int)(((long long)tile_n * n) / n_tiles) : 0;
     auto koff_of = [&](int j) { const int r = j + rot; return (kt0 + (r >= n ? r - n : r)) * (kBK * 2); };
     const int first = n < S ? n : S;
 #pragma unroll

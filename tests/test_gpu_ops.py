@@ -170,10 +170,11 @@ def test_gemm_long_streams_of_few_and_many_rows(torch, mode, N, K, narrow):
         assert torch.equal(c.view(torch.int16), whole[:M].view(torch.int16)), M
 
 
-@pytest.mark.parametrize("mode,M,N,K", [(0, 300, 8300, 1984), (0, 300, 8300, 2048), (1, 300, 8300, 2112), (2, 420, 8300, 2496)])
+@pytest.mark.parametrize("mode,M,N,K", [(0, 300, 8300, 1984), (0, 300, 8300, 2048), (1, 300, 8300, 2112), (2, 420, 8300, 2496),
+                                        (0, 700, 4100, 2112)])
 def test_gemm_mid_sized_walks(torch, mode, M, N, K):
-    """Several rows of tiles over one range of 31 k-tiles (every walk from its start), and of 32, 33 and 39 (an XCD's start of its
-    own, the walk wrapping around)."""
+    """Two rows of tiles over one range of 31 k-tiles (every walk from its start), and of 32, 33 and 39 (an XCD's start of its
+    own, the walk wrapping around); four rows of tiles (in step again)."""
     from paper_2412_17246_amd import op_gemm_plan
     from paper_2412_17246_amd.binding import BZ_GEMM_MID
     p = op_gemm_plan(mode, M, N, K)
