@@ -440,7 +440,8 @@ constexpr int kDecodeMaxG = 8;
 // SRC: what the new token's values come as: the projection, its partial sums, or rotated and appended already
 // (decode_append_apart).  In the last case the queries, too, are requested before the stream and go through LDS: requested behind
 // it by every wave, they held the score product back until all of K and V had arrived (7B shape, 161 sequences 273 -> 264 us,
-// 13B, 83 sequences 300 -> 294).
+// 13B, 83 sequences 300 -> 295; 150 of the 7B shape on long caches 469 -> 466, 161 caches that all end with a chunk 211 -> 214).  By
+// every wave into registers, its products starting as K arrives: 264, 301, 473, 222.
 // WAVES per SIMD, that is workgroups per CU, set outright: for d = 128 two keep the memory streams in longer runs than three,
 // which the registers would allow where the projection is plain (83 sequences of 40 heads, 402 -> 392 us; 240 of 8 with four
 // query heads each 371 -> 366), except where most caches end within their first chunk (250 sequences of 40 heads 178 -> 170 with
