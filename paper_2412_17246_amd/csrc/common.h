@@ -273,8 +273,7 @@ void launch_attn_prefill(const QkvSource& src, const float* rope_tab, act_t* out
 void launch_attn_decode(const QkvSource& src, const float* rope_tab, act_t* out, float* partial, const BatchView& bv,
                         const KvView& kv, int Hq, bool combine, hipStream_t st);
 // Few rows: the projections with everything around them in one launch each.  mode 0: c = rmsnorm(x) * gain * w^T; 1: c = r +
-// x * w^T (r may be c); 2: c = silu(gate) * up of rmsnorm(x) * gain.
-bool few_rows(int M, int H, int qd, int F);
+// x * w^T (r may be c); 2: c = silu(gate) * up of rmsnorm(x) * gain.  For the batches that few_rows names.
 void launch_few(int mode, const act_t* x, const bf16* gain, float eps, const bf16* w, const act_t* r, act_t* c, int M, int N,
                 int K, hipStream_t st);
 // The output projection of single new tokens whose attention left partial results (no combine launch then): x += combined * w^T.

@@ -9,6 +9,7 @@
 #include <string>
 #include <vector>
 
+#include "few_rows.h"
 #include "instance.h"
 
 using namespace bz;
@@ -1041,7 +1042,7 @@ int bz_run_layers(bz_instance* I, int a, int b, const bz_batch* batch, void* hid
     for (int s : batch->decode_seqs) decode_kv += (double)(batch->kv_before[s] + 1);
 
     // Few rows: the norms, the residual and SwiGLU are part of the projections' launches.
-    const bool few = few_rows(T, sh.H, sh.Hq * sh.d, sh.F), combine_later = few && few_combines(bv, sh.Hq * sh.d);
+    const bool few = few_rows(T, sh.H, sh.Hq * sh.d, sh.nqkv(), sh.F), combine_later = few && few_combines(bv, sh.Hq * sh.d);
     int pending_down = 0;        // split-K slices of the previous layer's down projection still to be folded into x
     for (int l = a; l < b; ++l) {
         // A layer still on its way is waited for as a whole, except the last one of the range: there each

@@ -18,6 +18,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "few_rows.h"
 
 namespace bz {
 
@@ -27,9 +28,8 @@ typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kFewWaves = 8, kFewThreads = kFewWaves * kWave;
+constexpr int kFewWaves = kFewThreads / kWave;
 constexpr int kFewK = 64;                    // columns of a step: one cache line of a weight row
-constexpr int kFewRows = 4;                  // most rows of a batch
 constexpr int kFewPad = 64;                  // bytes between the rows in LDS, so that their reads of one step spread over the banks
 constexpr int kFewLds = 160 * 1024;
 
@@ -337,13 +337,6 @@ __global__ __launch_bounds__(kFewThreads, 2) void gemm_few_kernel(const FewArgs 
     __builtin_amdgcn_s_waitcnt(few_vmcnt(0));                         // no LDS write may be in flight when the workgroup ends
 }
 
-static int few_vectors(int H) { return (H / 8 + kFewThreads - 1) / kFewThreads; }       // per thread and row
-
-bool few_rows(int M, int H, int qd, int F) {
-    return M >= 1 && M <= kFewRows && few_vectors(H) <= 2 && M * few_vectors(H) <= 8 && H % 8 == 0 && F % 8 == 0 && qd % 8 == 0 &&
-           (uint64_t)2 * F * H < 0x7fffffffull;
-}
-
 template <int SRC, int EPI, int NR, int D, int SLOTS = 1, int TOK = 1>
 static void launch_few_d(const FewArgs& a, hipStream_t st) {
     const int lds = FewCfg<SRC, NR>::ring_at(a.M, a.K) + kFewWaves * D * FewCfg<SRC, NR>::kSlot;
@@ -418,7 +411,6 @@ void launch_few(int mode, const act_t* x, const bf16* gain, float eps, const bf1
 
 #else
 
-bool few_rows(int, int, int, int) { return false; }
 bool few_combines(const BatchView&, int) { return false; }
 void launch_few_out(const float*, const BatchView&, const KvView&, const bf16*, act_t*, int, int, hipStream_t) {}
 void launch_few(int, const act_t*, const bf16*, float, const bf16*, const act_t*, act_t*, int, int, int, hipStream_t) {}

@@ -326,6 +326,49 @@ def test_one_to_four_rows(torch, shape, seqs):
             assert U.rel_err(got[a:b], want[a:b]) <= _tol(False), (i, seqs[i])
 
 
+@pytest.mark.parametrize("rows", [1, 4])
+def test_one_to_four_rows_on_projections_past_4_gib(torch, rows):
+    """A model whose QKV matrix is larger than 32-bit byte offsets reach (4.4 GB): new sequences, whose attention is their own
+    value, against the layer in fp32."""
+    H, Hq, Hkv, d, F = 8192, 1056, 528, 128, 264
+    s = W.DecoderShape("wide", L=1, H=H, Hq=Hq, Hkv=Hkv, d=d, F=F, seed=66)
+    inst = U.make_instance(s, max_seqs=rows, max_seq_len=32, max_tokens=rows, kv_tokens=32 * rows)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(66)
+    blob = torch.empty(inst.layer_bytes // 2, dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.02, generator=gen)
+    lay = inst.layout
+    for at in (lay.g1 // 2, lay.g2 // 2):
+        blob[at:at + H].add_(1.0)
+    torch.cuda.synchronize()
+    inst.load_layer_from_device(0, blob.view(torch.uint8))
+    inst.wait_layer(0)
+    inst.drop_sources()
+    for i in range(rows):
+        inst.kv_reserve(i, 32)
+    x = torch.randn(rows, H, generator=gen, device="cuda").to(torch.bfloat16)
+    given = x.float()
+    torch.cuda.synchronize()
+    inst.run_layers(0, 1, inst.batch(list(range(rows + 1)), list(range(rows)), [0] * rows), x)
+    inst.sync()
+    got = U.from_device(x)
+    inst.close()
+
+    def part(at, n):
+        return blob[at // 2:at // 2 + n].float()
+
+    def norm(v, at):
+        return v * torch.rsqrt((v * v).mean(1, keepdim=True) + s.eps) * part(at, H)
+
+    value = norm(given, lay.g1) @ part(lay.wv, Hkv * d * H).view(Hkv * d, H).t()
+    attn = value.view(rows, Hkv, 1, d).expand(rows, Hkv, Hq // Hkv, d).reshape(rows, Hq * d)
+    mid = given + attn @ part(lay.wo, H * Hq * d).view(H, Hq * d).t()
+    n = norm(mid, lay.g2)
+    act = torch.nn.functional.silu(n @ part(lay.wg, F * H).view(F, H).t()) * (n @ part(lay.wu, F * H).view(F, H).t())
+    want = (mid + act @ part(lay.wd, H * F).view(H, F).t()).double().cpu().numpy()
+    assert U.rel_err(got, want) <= U.BF16_TOL
+    U.assert_rms(got, want, U.RMS_BF16_FULLSIZE)
+
+
 @pytest.mark.parametrize("rows", [2, 63, 64, 65, 127, 129, 193])
 @pytest.mark.parametrize("shape", [MIX, MIX64, H24], ids=lambda s: s.name)
 def test_few_prefill_tiles_over_long_caches(torch, shape, rows):

@@ -409,3 +409,33 @@ def test_headers_compile_as_c_and_the_library_serves_a_plain_c_program(tmp_path,
     assert res.returncode == 0, res.stderr
     run = subprocess.run([exe], capture_output=True, text=True, timeout=60)
     assert run.returncode == 0 and "all checks passed" in run.stdout, run.stdout + run.stderr
+
+
+def test_few_rows_take_matrices_that_32_bit_offsets_reach(tmp_path):
+    """The kernels for one to four rows address a matrix with 32-bit byte offsets: each of the four has to fit, at the limit
+    and past it, whichever is the largest."""
+    import shutil
+    import subprocess
+    if shutil.which("g++") is None:
+        pytest.skip("no g++")
+    cases = []                                     # M, H, qd, nqkv, F, expected
+    for name in ("tiny", "7b", "8b_gqa", "13b", "70b"):
+        s = workloads.CONFIGS[name]
+        cases += [(M, s.H, s.Hq * s.d, (s.Hq + 2 * s.Hkv) * s.d, s.F, 1 <= M <= 4) for M in (0, 1, 4, 5)]
+    H = 8192
+    cases += [(1, H, 1024 * 128, 3 * 1024 * 128, 8192, False),         # QKV 6.4 GB
+              (1, H, 4096, (1 << 18) - 8, 264, True), (1, H, 4096, 1 << 18, 264, False),
+              (1, H, (1 << 18) - 8, 64, 264, True), (1, H, 1 << 18, 64, 264, False),
+              (1, H, 4096, 6144, (1 << 17) - 8, True), (1, H, 4096, 6144, 1 << 17, False),
+              (1, H + 8, 4096, 6144, 8192, False), (1, 4100, 4096, 6144, 8192, False), (1, H, 4096, 6144, 8196, False),
+              (1, 8, 1 << 27, 1 << 28, 8, False), (1, 8, 1 << 29, 3 << 29, 8, False)]
+    src = tmp_path / "few.cpp"
+    src.write_text('#include <stdio.h>\n#include "few_rows.h"\nint main() { int a[5]; while (scanf("%d %d %d %d %d", a, a + 1, a + 2, '
+                   'a + 3, a + 4) == 5) printf("%d\\n", (int)bz::few_rows(a[0], a[1], a[2], a[3], a[4])); }\n')
+    exe = str(tmp_path / "few")
+    for flags, on in (([], True), (["-DBZ_FP32_DEBUG"], False)):
+        subprocess.run(["g++", "-std=c++17", "-Wall", "-Wextra", "-Werror", "-I", os.path.join(ROOT, "paper_2412_17246_amd", "csrc"),
+                        str(src), "-o", exe] + flags, check=True)
+        given = "\n".join(" ".join(str(v) for v in c[:5]) for c in cases)
+        got = subprocess.run([exe], input=given, capture_output=True, text=True, timeout=60, check=True).stdout.split()
+        assert [bool(int(g)) for g in got] == [on and c[5] for c in cases]
