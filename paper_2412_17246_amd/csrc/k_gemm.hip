@@ -1339,10 +1339,12 @@ static void skinny_plan_rb(SkinnyPlan& p, int Nrows, int nk) {
     const int min_kt = nk < 4 * RB ? nk : 4 * RB; // keep the ring worth filling
     if (p.kt_per_split < min_kt) p.kt_per_split = min_kt;
     p.ksplit = (nk + p.kt_per_split - 1) / p.kt_per_split;
-    // A grid a little short of a multiple of the slots leaves some of them idle for the whole kernel (448
-    // workgroups on 512 slots: an eighth of the chip).  Narrower tiles (down to half of the rows, in steps of 8)
-    // bring the count up to the multiple; narrower than that, the activations would be re-read by too many tiles.
-    // (88 of 128 rows: 7B gate/up 172 -> 251 workgroups, 30.8 -> 29.6 us at 12 rows, 39.2 -> 37.5 at 64.)
+    // A grid a little short of a multiple of the units leaves some CUs idle for the whole kernel, or for its last round.
+    // Narrower tiles (down to half of the rows, in steps of 8) bring the count up to the multiple; narrower than that, the
+    // activations would be re-read by too many tiles.  (88 of 128 rows: 7B gate/up 172 -> 251 workgroups, 30.8 -> 29.6 us at
+    // 12 rows, 39.2 -> 37.5 at 64.)  Half against three quarters of the rows, cold weights, time ratios of products whose plan
+    // that changes: long streams (26) 0.77 at 8 rows, 0.79 at 32, 0.87 at 64.  Short streams in several rounds (16) 0.95, 0.94, 0.91, 0.91
+    // at 5, 16, 40 and 64 rows; in a single round (44) 1.003, 1.002, 0.984, 0.955 there, the worst 1.02 at 5 rows (8704 x 3072).
     p.rows = kTile;
     const int total = p.n_tiles * p.ksplit;
     const int rounds = (total + kSlots - 1) / kSlots;

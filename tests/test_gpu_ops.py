@@ -170,6 +170,16 @@ def test_gemm_long_streams_of_few_and_many_rows(torch, mode, N, K, narrow):
         assert torch.equal(c.view(torch.int16), whole[:M].view(torch.int16)), M
 
 
+@pytest.mark.parametrize("mode,M,N,K,cols,ranges", [(0, 5, 17100, 264, 40, 1), (1, 33, 17100, 320, 40, 1), (2, 64, 8708, 192, 40, 1),
+                                                   (0, 31, 8708, 1536, 40, 1), (2, 33, 5004, 520, 40, 1), (1, 64, 1020, 2048, 32, 8)])
+def test_gemm_short_streams_in_narrow_tiles(torch, mode, M, N, K, cols, ranges):
+    """Short streams whose tiles narrow down to 40 and 32 of 64 rows, in several rounds of workgroups and in one, K cut and not."""
+    from paper_2412_17246_amd import op_gemm_plan
+    p = op_gemm_plan(mode, M, N, K)
+    assert (p.tile_cols, p.ranges) == (cols, ranges)
+    test_gemm(torch, False, mode, M, N, K)
+
+
 @pytest.mark.parametrize("mode,M,N,K", [(0, 300, 8300, 1984), (0, 300, 8300, 2048), (1, 300, 8300, 2112), (2, 420, 8300, 2496),
                                         (0, 700, 4100, 2112)])
 def test_gemm_mid_sized_walks(torch, mode, M, N, K):

@@ -116,6 +116,18 @@ def test_short_k_tails_are_one_launch(mode, M, N, K, kernel):
         assert B.op_gemm_workspace_bytes(mode, M, N, K) == 0
 
 
+@pytest.mark.parametrize("mode,N,K,cols,tiles", [
+    # short streams in one round, in several, and long streams
+    (0, 8704, 1536, 40, 218), (1, 10240, 2048, 40, 256), (2, 5120, 1024, 40, 256), (0, 1024, 2048, 32, 32), (0, 12000, 1024, 48, 250),
+    (0, 20400, 1536, 40, 510), (2, 8704, 512, 40, 436), (2, 11008, 4096, 88, 251), (1, 33000, 1024, 72, 459),
+    # half of the rows would not do, or the grid is full
+    (0, 7700, 1024, 64, 121), (0, 16384, 1024, 64, 256)])
+def test_decode_sized_tiles_narrow_down_to_fill_the_chip(mode, N, K, cols, tiles):
+    for M in (5, 32, 64):
+        p = B.op_gemm_plan(mode, M, N, K)
+        assert (p.kernel, p.tile_cols, p.tiles_n) == (B.BZ_GEMM_DECODE, cols, tiles)
+
+
 def test_gemm_plans_stay_within_the_workspace():
     """Every plan uses no more than it is given, and the reported size buys the plan that any larger one does."""
     rng = np.random.default_rng(3)
