@@ -57,7 +57,7 @@ GEMM_SHAPES = [
     # a few hundred rows, fewer tiles than CUs
     (200, 4096, 2048), (600, 1376, 4096),
     # one row of tiles, a power-of-two row pitch and 32 k-tiles per workgroup: tiles start their walk over K at different
-    # places (and two rows of tiles, which walk in step)
+    # places (and two rows of tiles, which start by XCD)
     (40, 7168, 4096), (150, 7168, 4096),
 ]
 
@@ -189,6 +189,19 @@ def test_gemm_mid_sized_walks(torch, mode, M, N, K):
     from paper_2412_17246_amd.binding import BZ_GEMM_MID
     p = op_gemm_plan(mode, M, N, K)
     assert p.kernel == BZ_GEMM_MID and p.tiles_m > 1 and p.ranges == 1
+    test_gemm(torch, False, mode, M, N, K)
+
+
+@pytest.mark.parametrize("mode,M,N,K,cols,ranges", [(0, 210, 2048, 16384, 64, 4), (2, 150, 4096, 4096, 64, 1), (2, 170, 2048, 16384, 128, 4),
+                                                   (2, 300, 1536, 16384, 128, 5)])
+def test_gemm_mid_sized_walks_in_step(torch, mode, M, N, K, cols, ranges):
+    """Two rows of tiles at distances at which all XCDs start at the same place: tiles 2^11 and 2^8 times the starts apart, or 2 MiB."""
+    from paper_2412_17246_amd import op_gemm_plan
+    from paper_2412_17246_amd.binding import BZ_GEMM_MID
+    p = op_gemm_plan(mode, M, N, K)
+    assert (p.kernel, p.tile_cols, p.ranges) == (BZ_GEMM_MID, cols, ranges) and p.tiles_m in (2, 3)
+    apart, start = (cols // 2 if mode == 2 else cols) * K * 2, K // 64 // ranges * 128 // 8
+    assert apart in (start << 11, start << 8, 2 << 20)
     test_gemm(torch, False, mode, M, N, K)
 
 
