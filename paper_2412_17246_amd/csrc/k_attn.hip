@@ -438,15 +438,18 @@ constexpr int kDecodeMaxG = 8;
 // A sequence with a single chunk gets its output here; the combine kernel leaves it alone.
 //
 // SRC: what the new token's values come as: the projection, its partial sums, or rotated and appended already
-// (decode_append_apart).  In the last case the queries, too, are requested before the stream and go through LDS: requested behind
-// it by every wave, they held the score product back until all of K and V had arrived (7B shape, 161 sequences 273 -> 264 us,
-// 13B, 83 sequences 300 -> 295; 150 of the 7B shape on long caches 469 -> 466, 161 caches that all end with a chunk 211 -> 214).  By
-// every wave into registers, its products starting as K arrives: 264, 301, 473, 222.
+// (decode_append_apart).  In the last case the queries come in one of two ways.  On caches of up to four chunks on average (kAppended)
+// they are requested before the stream, by the first 128 threads, and go through LDS; the store waits for the wave's whole stream (not
+// all waves request one), so the scores start when K and V are there.  On longer ones (kAppendedLong) every wave requests them for
+// itself, behind its stream.  A pass of two layers, behind the stream against through LDS, same memory: 7B shape, 161 sequences of
+// 128 to 1024 positions 919 / 902 us, of 511 806 / 802, of 900 to 1023 1193 / 1187, of 1023 1240 / 1245, 150 of 1500 to 3000 2094 / 2104; 13B
+// shape, 83 of 512 to 4096 1561 / 1575, of 2047 1423 / 1440.  Products that start as K arrives are slower than either where
+// chunks are full: stored behind a counted wait 1272 (of 1023), 2108, 1590, 1477; by every wave into LDS of its own 1250, 2110, 1571, 1449.
 // WAVES per SIMD, that is workgroups per CU, set outright: for d = 128 two keep the memory streams in longer runs than three,
 // which the registers would allow where the projection is plain (83 sequences of 40 heads, 402 -> 392 us; 240 of 8 with four
 // query heads each 371 -> 366), except where most caches end within their first chunk (250 sequences of 40 heads 178 -> 170 with
 // three).
-enum { kProjection = 0, kPartialSums = 1, kAppended = 2 };
+enum { kProjection = 0, kPartialSums = 1, kAppended = 2, kAppendedLong = 3 };
 template <int D, int SRC, int WAVES>
 __global__ __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) __launch_bounds__(256) void attn_decode_kernel(QkvSource src, const float* __restrict__ tab,
                                                              float* __restrict__ partial, bf16* __restrict__ out,
@@ -454,7 +457,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) __launch_bounds__(
                                                              int combine) {
     constexpr int CH = kDecodeChunk;
     constexpr int KS = D / 16, DB = D / 32, BLK = 32 * D;
-    constexpr bool REDUCE = SRC == kPartialSums, FUSED = SRC != kAppended;
+    constexpr bool REDUCE = SRC == kPartialSums, FUSED = SRC < kAppended, HANDED = SRC != kAppendedLong;
     __shared__ float wmx[4][kDecodeMaxG];
     __shared__ float wsum[4][kDecodeMaxG];
     __shared__ float osh[4][kDecodeMaxG][D];
@@ -512,7 +515,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) __launch_bounds__(
     if (FUSED) {
         cs0 = *reinterpret_cast<const f32x4*>(cs);
         cs1 = *reinterpret_cast<const f32x4*>(cs + 4);
-    } else {
+    } else if (HANDED) {
         const int i = tid < G * (D / 8) ? tid : G * (D / 8) - 1;
         qr = *reinterpret_cast<const bf16x8*>(src.qkv + (size_t)t * nqkv + kvh * G * D + i * 8);
     }
@@ -547,6 +550,17 @@ __global__ __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) __launch_bounds__(
                 for (int db = 0; db < DB; ++db)
                     vf[b][tt][db] =
                         stream_load(reinterpret_cast<const bf16x8*>(Vc + boff[b] + lane_v + (2 * tt * D + db * 32) * 8));
+    }
+    bf16x8 qa[KS];
+    if (!HANDED && live) {
+        const bf16* q = src.qkv + (size_t)t * nqkv + kvh * G * D;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            if (lq < G) qa[ks] = *reinterpret_cast<const bf16x8*>(q + lq * D + ks * 16 + lh * 8);
+            else
+#pragma unroll
+                for (int i = 0; i < 8; ++i) qa[ks][i] = (bf16)0.f;
+        }
     }
     __builtin_amdgcn_sched_barrier(0);
     if (FUSED) {
@@ -600,9 +614,9 @@ __global__ __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) __launch_bounds__(
             }
         }
     }
-    if (!FUSED && tid < G * (D / 8)) *reinterpret_cast<bf16x8*>(&qs[0][0] + tid * 8) = qr;
-    {
-        // hand-over through LDS without waiting for the stream (a full barrier would drain it)
+    if (!FUSED && HANDED && tid < G * (D / 8)) *reinterpret_cast<bf16x8*>(&qs[0][0] + tid * 8) = qr;
+    if (HANDED) {
+        // hand-over through LDS; a full barrier would drain the stream
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
@@ -625,7 +639,8 @@ __global__ __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) __launch_bounds__(
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             bf16x8 qf = {};
-            if (lq < G) qf = *reinterpret_cast<const bf16x8*>(&qs[lq][ks * 16 + lh * 8]);
+            if (!HANDED) qf = qa[ks];
+            else if (lq < G) qf = *reinterpret_cast<const bf16x8*>(&qs[lq][ks * 16 + lh * 8]);
 #pragma unroll
             for (int b = 0; b < 2; ++b) sacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[b][ks], qf, sacc[b], 0, 0, 0);
         }
@@ -908,7 +923,9 @@ static void launch_decode_d(const QkvSource& qkv, [[maybe_unused]] const float* 
 #ifndef BZ_FP32_DEBUG
     constexpr int MANY = D == 128 ? 3 : 4;          // what the registers allow
     constexpr int FEW = D == 128 ? 2 : 4;
-    auto kern = decode_append_apart(bv, kv, Hq)     ? attn_decode_kernel<D, kAppended, FEW>
+    const bool apart = decode_append_apart(bv, kv, Hq);
+    auto kern = apart && bv.n_decode_work > 4 * bv.n_decode ? attn_decode_kernel<D, kAppendedLong, FEW>
+                : apart                             ? attn_decode_kernel<D, kAppended, FEW>
                 : qkv.partial                       ? attn_decode_kernel<D, kPartialSums, FEW>
                 : bv.n_decode_work < 2 * bv.n_decode ? attn_decode_kernel<D, kProjection, MANY>
                                                     : attn_decode_kernel<D, kProjection, FEW>;

@@ -138,11 +138,12 @@ def test_decode_weights_below_the_normal_range_count(torch, d):
     assert 2.0 ** -0.8 < factor.min() and factor.max() < 2.0 ** 0.8, (factor.min(), factor.max())
 
 
-@pytest.mark.parametrize("d,prompt,single", [(64, 0, 60), (128, 0, 60), (64, 4, 60), (128, 40, 80), (64, 0, 130)])
+@pytest.mark.parametrize("d,prompt,single", [(64, 0, 60), (128, 0, 60), (64, 4, 60), (128, 40, 80), (64, 0, 130), (128, 0, 130)])
 def test_many_decode_workgroups(torch, d, prompt, single):
     """Above 9600 workgroups per query head of a kv head the single new tokens are appended by a launch of its own.  The same batch in
     two halves takes the other kernel: same cache, bit for bit where the projection's plan is the same (up to 64 rows), and the
-    same output within the gates; four sequences against the oracle."""
+    same output within the gates; four sequences against the oracle.  60 sequences have more than four chunks each on average, 80
+    and 130 fewer: their queries reach the products in different ways."""
     s = W.DecoderShape("wide%d" % d, L=1, H=512, Hq=40, Hkv=40, d=d, F=256, rope_base=10000.0, seed=90 + d)
     rng = np.random.default_rng([d, single])
     edges = [1023, 1024, 1055, 1056, 1279, 1280, 1281]
@@ -150,6 +151,7 @@ def test_many_decode_workgroups(torch, d, prompt, single):
              (edges + rng.integers(513, 800, single - len(edges)).tolist())
     news = [1] * single + ([prompt] if prompt else [])
     befores = before + ([700] if prompt else [])
+    assert (sum(b // 256 + 1 for b in before) > 4 * single) == (single == 60)
     assert sum(b // 256 + 1 for b in before) * 40 > 9600 > sum(b // 256 + 1 for b in before[:(single + 1) // 2]) * 40
     n, T = len(news), sum(news)
     gen = torch.Generator(device="cuda")
