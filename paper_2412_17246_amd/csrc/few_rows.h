@@ -11,7 +11,8 @@ constexpr int kFewRows = 4;                  // most rows of a batch
 inline int few_vectors(int H) { return (H / 8 + kFewThreads - 1) / kFewThreads; }       // 8-element vectors per thread and row
 
 // M rows on a model of hidden size H, qd = query heads * d, nqkv rows of the QKV projection, feed-forward width F.  The norm keeps
-// up to two vectors per thread and row (H <= 8192), and the weights are addressed with 32-bit byte offsets: every one of the four
+// up to two vectors per thread and row (H <= 8192, by which the products with a residual, of H weight rows, are also one tile per
+// workgroup), and the weights are addressed with 32-bit byte offsets: every one of the four
 // matrices has to end below 2^32 bytes, as in the kernels for more rows.
 inline bool few_rows([[maybe_unused]] int M, [[maybe_unused]] int H, [[maybe_unused]] int qd, [[maybe_unused]] int nqkv,
                      [[maybe_unused]] int F) {

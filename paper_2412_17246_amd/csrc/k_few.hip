@@ -105,7 +105,7 @@ __global__ __launch_bounds__(kFewThreads, 2) void gemm_few_kernel(const FewArgs 
     const int s0 = steps * wave / NW, count = steps * (wave + 1) / NW - s0;      // this wave's steps of a tile
     const int n0 = blockIdx.x * a.per_wg * 4;                         // this workgroup's rows (features) n0 .. n1 - 1
     const int n1 = n0 + a.per_wg * 4 < N ? n0 + a.per_wg * 4 : N;
-    const int ntiles = (n1 - n0 + kTile - 1) / kTile;
+    const int ntiles = EPI == 1 ? 1 : (n1 - n0 + kTile - 1) / kTile;
 
     // what the rows are made of is requested before the weights (loads complete in order)
     const int nvec = K >> 3;
@@ -150,15 +150,14 @@ __global__ __launch_bounds__(kFewThreads, 2) void gemm_few_kernel(const FewArgs 
         for (int m = 0; m < TOK; ++m) nch[m] = a.kv_before[m] / kDecodeChunk + 1;
         load_parts(c0 + lane * 8);
     }
-    bf16x4 rv;
     // block j of tile t is finished by wave (t * NB + j) % NW
     auto block_of = [&](int t) { return (wave - t * NB) & (NW - 1); };
-    auto load_r = [&](int t) {
-        int n = n0 + t * kTile + block_of(t) * 16 + 4 * g;
+    bf16x4 rv;
+    if (EPI == 1) {                                                   // one tile only: N is the hidden size, 32 rows per workgroup at most
+        int n = n0 + wave * 16 + 4 * g;
         if (n > N - 4) n = N - 4;                                     // value unused
         rv = *reinterpret_cast<const bf16x4*>(a.r + (size_t)tok * N + n);
-    };
-    if (EPI == 1) load_r(0);
+    }
     __builtin_amdgcn_sched_barrier(0);
 
     // A step's loads of 1 KiB: NR times 8 weight rows of one cache line each, and (kRows) the line of every row.  The 16-byte
@@ -332,7 +331,6 @@ __global__ __launch_bounds__(kFewThreads, 2) void gemm_few_kernel(const FewArgs 
                 *reinterpret_cast<bf16x4*>(a.c + (size_t)col * N + n) = o;
             }
         }
-        if (EPI == 1 && t + 1 < ntiles) load_r(t + 1);
     }
     __builtin_amdgcn_s_waitcnt(few_vmcnt(0));                         // no LDS write may be in flight when the workgroup ends
 }
@@ -393,6 +391,9 @@ void launch_few(int mode, const act_t* x, const bf16* gain, float eps, const bf1
                 int K, hipStream_t st) {
     FewArgs a{x, gain, eps, w, r, c, M, N, K, 0, 0, nullptr, nullptr, 0, 0};
     const int nr = few_cut(a);
+    // Up to 1024 columns a wave has two steps of a tile at most: two slots do (hidden 256: 3.80 / 3.88 us with two / three for QKV, 3.88 /
+    // 4.02 for gate/up; 1024: 3.84 / 4.07 and 5.35 / 5.57, four rows 5.10 / 5.28 and 6.64 / 6.69).  From 2048 on they win nothing (16-row tiles of
+    // QKV 4.77 / 4.76) and lose on long streams (8B-GQA gate/up 38.7 / 38.4).
     const bool small = K <= 1024 && nr == 2;
     if (mode == 2) {
         if (small) launch_few_norm<2, 2, 2>(a, st);
