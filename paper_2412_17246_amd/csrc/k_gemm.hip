@@ -1085,9 +1085,9 @@ static bool launch_mid(int mode, const MidPlan& p, const bf16* x, const bf16* w,
 //
 // RB = 1: 64-row tiles, four 16 KiB stages, two workgroups per CU: short streams (small matrices),
 // where many small workgroups start and finish faster.
-// RB = 2: 128-row tiles, one workgroup per CU: long streams.  Every tile re-reads
-// the activations from L2, which costs about a tenth of the time at 64 rows; twice the rows halve
-// that.  Measured against RB = 1 on the decode shapes (64 rows, five stages): 8B-GQA down projection 31.4 -> 28.0 us, gate/up
+// RB = 2: 128-row tiles: long streams.  Every tile re-reads the activations from L2, which costs about a tenth of the time at 64
+// rows; twice the rows halve that.  Workgroups per CU: two with TB = 1 (four 20 KiB stages), one with TB = 2 and four 24 KiB stages,
+// two with three of them.  Measured against RB = 1 on the decode shapes (64 rows, five stages): 8B-GQA down projection 31.4 -> 28.0 us, gate/up
 // unchanged; 70B qkv 40.9 -> 37.1, o 36.1 -> 37.8, gate/up 185 -> 168, down 96.5 -> 78.5 us.
 //
 // TB: 32-row blocks of the activations in a stage; with one (up to 32 rows) the four waves share out the weight rows alone.
@@ -1097,7 +1097,7 @@ static bool launch_mid(int mode, const MidPlan& p, const bf16* x, const bf16* w,
 // 29.6 (with the tiles as many as CUs, below), 19.2 -> 17.7, 18.7 -> 17.6; at 24: 8B-GQA 37.1 -> 36.4, 20.6 -> 20.4.  Above 32 rows four
 // stages instead of five: 13B (48) 49.9 -> 49.5, 30.9 -> 30.4, 27.2 -> 26.7, 7B gate/up (64) 36.8 -> 35.5.  Where there are more
 // tiles than CUs three, which leave room for two workgroups: 70B gate/up (64) 172 -> 161; elsewhere they lose (13B 52.5, 31.1, 27.6).
-template <int RB, int TB = 2, int ST = RB == 1 ? 4 : 5> struct SkCfg {
+template <int RB, int TB, int ST> struct SkCfg {
     static constexpr int kXBytes = 32 * TB * kBK * (int)sizeof(bf16);         // activations of a stage: 4 KiB * TB
     static constexpr int kStage = kXBytes + 64 * RB * kBK * (int)sizeof(bf16);  // + weights 8 KiB * RB
     static constexpr int kStages = ST;
@@ -1127,6 +1127,7 @@ __global__ __launch_bounds__(256, (SkCfg<RB, TB, ST>::kPerCu)) void gemm_skinny_
     constexpr int LPS = TB + 2 * RB;                  // loads per wave and stage
     constexpr int NB = TB == 2 ? RB : RB / 2;         // 32-row blocks of a wave
     static_assert(NB >= 1, "TB = 1: the four waves share out the weight rows alone");
+    static_assert(kStages == 3 || kStages == 4, "the waits count up to two later tiles");
     constexpr int HALF = 32 * RB;                     // rows per wave along the features (GU: rows per factor)
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
     const int tile_n = blockIdx.x % n_tiles, split = blockIdx.x / n_tiles;
@@ -1218,8 +1219,7 @@ __global__ __launch_bounds__(256, (SkCfg<RB, TB, ST>::kPerCu)) void gemm_skinny_
     for (int i = 0; i < n; ++i) {
         // tile i must have landed; the tiles requested after it (LPS loads each) may still be in flight
         const int later = (n - 1 - i < kStages - 2) ? n - 1 - i : kStages - 2;
-        if (later >= 3) __builtin_amdgcn_s_waitcnt(lds_wait(3 * LPS));
-        else if (later == 2) __builtin_amdgcn_s_waitcnt(lds_wait(2 * LPS));
+        if (later == 2) __builtin_amdgcn_s_waitcnt(lds_wait(2 * LPS));
         else if (later == 1) __builtin_amdgcn_s_waitcnt(lds_wait(LPS));
         else __builtin_amdgcn_s_waitcnt(lds_wait(0));
         __builtin_amdgcn_s_barrier();                              // everyone's part landed; the stage of tile i-1 is free
@@ -1335,14 +1335,13 @@ struct SkinnyPlan {
 template <int RB>
 static void skinny_plan_rb(SkinnyPlan& p, int Nrows, int nk) {
     constexpr int kTile = 64 * RB;
-    // Units one round hands out.  The long streams fill every workgroup slot of the chip.  The short ones (64-row tiles)
-    // aim at one unit per CU although two fit: half as many K slices halve the partial sums
-    // written here and re-read by the consumer (8B decode at 64 tokens: qkv 17.7 -> 16.5 us, o 14.8 -> 12.0 us; a
+    // Units (tiles times K slices) of one round: one per CU, although two fit in most forms.  Half as many K slices halve the partial
+    // sums written here and re-read by the consumer (8B decode at 64 tokens, 64-row tiles: qkv 17.7 -> 16.5 us, o 14.8 -> 12.0 us; a
     // target of 128 or 192 units is slower again, 384 and more as well).
-    constexpr int kSlots = 256;
+    constexpr int kUnits = 256;
     p.rb = RB;
     p.n_tiles = (Nrows + kTile - 1) / kTile;
-    int target = kSlots / p.n_tiles;              // aim at filling every workgroup slot once
+    int target = kUnits / p.n_tiles;              // aim at one round
     if (target < 1) target = 1;
     p.kt_per_split = (nk + target - 1) / target;
     const int min_kt = nk < 4 * RB ? nk : 4 * RB; // keep the ring worth filling
@@ -1356,8 +1355,8 @@ static void skinny_plan_rb(SkinnyPlan& p, int Nrows, int nk) {
     // at 5, 16, 40 and 64 rows; in a single round (44) 1.003, 1.002, 0.984, 0.955 there, the worst 1.02 at 5 rows (8704 x 3072).
     p.rows = kTile;
     const int total = p.n_tiles * p.ksplit;
-    const int rounds = (total + kSlots - 1) / kSlots;
-    const int want_tiles = rounds * kSlots / p.ksplit;
+    const int rounds = (total + kUnits - 1) / kUnits;
+    const int want_tiles = rounds * kUnits / p.ksplit;
     if (want_tiles > p.n_tiles) {
         const int r = ((Nrows + want_tiles - 1) / want_tiles + 7) / 8 * 8;
         if (r >= kTile / 2 && r < kTile) {
