@@ -140,9 +140,12 @@ typedef struct bz_stats {
  * decode workgroups, the single new tokens.  Otherwise these are rotated and appended inside BZ_K_ATTN_DECODE,
  * as other queries are inside BZ_K_ATTN_PREFILL, and neither class counts that: a batch of decode steps alone
  * mostly has no BZ_K_ROPE_APPEND launches.  (fp32 debug build: every row, queries
- * included, in BZ_K_ROPE_APPEND.)  BZ_K_ATTN_DECODE includes the merge of a sequence's chunks.  Batches of one to four rows
- * have no BZ_K_RMSNORM launches: the norms are part of BZ_K_GEMM_QKV and BZ_K_GEMM_GATEUP, and in batches of one or two decode
- * rows the merge is part of BZ_K_GEMM_O. */
+ * included, in BZ_K_ROPE_APPEND.)  BZ_K_ATTN_DECODE includes the merge of a sequence's chunks.
+ * Batches of one to four rows have no BZ_K_RMSNORM launches in the bf16 build where hidden <= 8192, the feed-forward width is a
+ * multiple of 8 and each projection's weights (gate and up together) take less than 4 GiB: the norms are part of BZ_K_GEMM_QKV and
+ * BZ_K_GEMM_GATEUP then.  In such a batch of one or two sequences with one new token each, query heads * d <= 8192, several chunks in
+ * some sequence and at most 16 in all (the longer sequence's counted for both; a chunk is 256 positions), the merge is part of
+ * BZ_K_GEMM_O. */
 enum {
     BZ_K_RMSNORM = 0, BZ_K_GEMM_QKV, BZ_K_ROPE_APPEND, BZ_K_ATTN_PREFILL, BZ_K_ATTN_DECODE,
     BZ_K_ATTN_COMBINE, BZ_K_GEMM_O, BZ_K_GEMM_GATEUP, BZ_K_GEMM_DOWN, BZ_K_COUNT
@@ -316,7 +319,9 @@ int bz_batch_advance(bz_instance* inst, bz_batch* batch);
  * MLP weights arrive.  A sharded layer is waited for as a whole.  With BZ_RUN_NOWAIT the call
  * returns BZ_ENOTREADY instead if any layer of [a,b) is not resident yet.  Results do not depend on
  * a, b, the frontier or timing: running [a,k) then [k,b) (on this or another instance holding the
- * same weights) is bit-identical to running [a,b).
+ * same weights) is bit-identical to running [a,b).  They may depend, within rounding, on what else is in the
+ * batch: the kernels and the order of their sums are chosen by its number of rows (one to four, up to 64, more)
+ * and by the lengths of its sequences.
  * BZ_ENOTLOADED if a layer of [a,b) was never requested, BZ_ECAPACITY if the batch has more rows than
  * max_tokens or a sequence outgrows its slot, BZ_ESTATE if a slot of the batch is not reserved. */
 int bz_run_layers(bz_instance* inst, int a, int b, const bz_batch* batch, void* hidden, int flags);
