@@ -843,16 +843,17 @@ __global__ __launch_bounds__(256, 1) void gemm_mid_kernel(const bf16* __restrict
     // qkv 34.5 in step, 40.8 shifted each by itself), so with two or three each XCD, where the sharing is, has one start (three layers of
     // the 7B shape, 301 rows 605 -> 586 us, 250 rows 549 -> 542, two of 70B, 250 rows 1008 -> 1002; two starts per XCD the same); with
     // more, all are in step (shifted by XCD, 13B 700 rows 991 -> 995, 8B-GQA 1200 rows 1548 -> 1553).
-    // They also are where the pitch is a power of two and neighbouring tiles lie 2^11, or (starts a KiB apart and more) 2^8, times as far
-    // apart as the starts, or 2 MiB: the two differences then cancel in the choice of the channel.  Shifted against in step, cold weights:
+    // They also are where the pitch is a power of two and neighbouring tiles lie 2^11 or 2^8 times as far apart as the starts (of a KiB
+    // and more), or 2 MiB (starts of more than 512 bytes): the two differences then cancel in the choice of the channel.  Shifted against in step, cold weights:
     // 8192 rows of 8192 at 257 rows 55.8 -> 61.8 us, 28672 of 4096 at 270 rows 76.1 -> 85.5, gate/up of 4096 features of 8192 at 240 rows
     // 55.3 -> 63.2, of 8192 of 16384 at 330 rows 186 -> 199 (2 MiB; 70B gate/up 0 to 1.7 % there).  Other orders of the eight starts
-    // lose elsewhere.  Over 1300 other products of 2 or 3 rows of tiles shifted takes 0.985 of the time.
+    // lose elsewhere.  And they are from eight ranges of K on, whose workgroups are at eight places anyway (2048 rows of 16384 at 390 rows
+    // 45.4 -> 49.2).  Over the 1300 other products of 2 or 3 rows of tiles that were measured shifted takes 0.96 to 0.985 of the time.
     constexpr int kApart = GU ? BN / 2 : BN;                    // weight rows between neighbouring tiles
     const long long apart = (long long)kApart * K;              // starts: n / 8 k-tiles of 64 columns
     const bool cancel = (K & (K - 1)) == 0 &&
-                        (apart == (long long)n << 14 || (n >= 64 && apart == (long long)n << 11) || (n > 32 && apart == 1 << 20));
-    const int rot = n < 32 || m_tiles > 3 || (m_tiles > 1 && cancel) ? 0 : m_tiles > 1 ? xcd * n / 8 : (K & (K - 1)) == 0 ? (int)(((long long)tile_n * n) / n_tiles) : 0;
+                        ((n >= 64 && (apart == (long long)n << 14 || apart == (long long)n << 11)) || (n > 32 && apart == 1 << 20));
+    const int rot = n < 32 || m_tiles > 3 || (m_tiles > 1 && (cancel || n * 8 <= nk)) ? 0 : m_tiles > 1 ? xcd * n / 8 : (K & (K - 1)) == 0 ? (int)(((long long)tile_n * n) / n_tiles) : 0;
     auto koff_of = [&](int j) { const int r = j + rot; return (kt0 + (r >= n ? r - n : r)) * (kBK * 2); };
     const int first = n < S ? n : S;
 #pragma unroll

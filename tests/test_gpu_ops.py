@@ -193,15 +193,17 @@ def test_gemm_mid_sized_walks(torch, mode, M, N, K):
 
 
 @pytest.mark.parametrize("mode,M,N,K,cols,ranges", [(0, 210, 2048, 16384, 64, 4), (2, 150, 4096, 4096, 64, 1), (2, 170, 2048, 16384, 128, 4),
-                                                   (2, 300, 1536, 16384, 128, 5)])
+                                                   (2, 300, 1536, 16384, 128, 5), (0, 330, 1536, 16384, None, 8)])
 def test_gemm_mid_sized_walks_in_step(torch, mode, M, N, K, cols, ranges):
-    """Two rows of tiles at distances at which all XCDs start at the same place: tiles 2^11 and 2^8 times the starts apart, or 2 MiB."""
+    """Two rows of tiles at distances at which all XCDs start at the same place: tiles 2^11 and 2^8 times the starts apart, or 2 MiB;
+    eight ranges."""
     from paper_2412_17246_amd import op_gemm_plan
     from paper_2412_17246_amd.binding import BZ_GEMM_MID
     p = op_gemm_plan(mode, M, N, K)
-    assert (p.kernel, p.tile_cols, p.ranges) == (BZ_GEMM_MID, cols, ranges) and p.tiles_m in (2, 3)
-    apart, start = (cols // 2 if mode == 2 else cols) * K * 2, K // 64 // ranges * 128 // 8
-    assert apart in (start << 11, start << 8, 2 << 20)
+    assert (p.kernel, p.ranges) == (BZ_GEMM_MID, ranges) and p.tiles_m in (2, 3)
+    if cols:
+        apart, start = (cols // 2 if mode == 2 else cols) * K * 2, K // 64 // ranges * 128 // 8
+        assert p.tile_cols == cols and apart in (start << 11, start << 8, 2 << 20)
     test_gemm(torch, False, mode, M, N, K)
 
 
