@@ -1352,8 +1352,9 @@ static void skinny_plan_rb(SkinnyPlan& p, int Nrows, int nk) {
     // Narrower tiles (down to half of the rows, in steps of 8) bring the count up to the multiple; narrower than that, the
     // activations would be re-read by too many tiles.  (88 of 128 rows: 7B gate/up 172 -> 251 workgroups, 30.8 -> 29.6 us at
     // 12 rows, 39.2 -> 37.5 at 64.)  Half against three quarters of the rows, cold weights, time ratios of products whose plan
-    // that changes: long streams (26) 0.77 at 8 rows, 0.79 at 32, 0.87 at 64.  Short streams in several rounds (16) 0.95, 0.94, 0.91, 0.91
-    // at 5, 16, 40 and 64 rows; in a single round (44) 1.003, 1.002, 0.984, 0.955 there, the worst 1.02 at 5 rows (8704 x 3072).
+    // that changes: long streams (26) 0.77 at 8 rows, 0.79 at 32, 0.87 at 64.  Short streams in several rounds (16) 0.95 to 0.97 at 6 rows,
+    // 0.94 at 24, 0.91 to 0.94 at 64; in a single round (44) 1.005 up to 24 rows (0.1 us; the worst 8704 x 512 9.7 -> 10.0), 0.96 to 0.97
+    // at 64.  (The tiles do not look at the rows, so that a row's sums are the same in every batch of up to 64.)
     p.rows = kTile;
     const int total = p.n_tiles * p.ksplit;
     const int rounds = (total + kUnits - 1) / kUnits;
